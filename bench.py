@@ -151,8 +151,7 @@ def parse():
                     help="1D tiling 'threads,rows,flags' instead of autotuning (rows 0 = whole cycle)")
     ap.add_argument("--pass-shape", type=int, default=None, metavar="BITS",
                     help="2D: transform-pass shape bits (1: 64-column waves, 2: 32-wide split-BF16 "
-                         "slices, 4: row-major intermediates instead of prefolded planes) instead "
-                         "of autotuning")
+                         "slices) instead of autotuning")
     ap.add_argument("--batch-tile", default=None,
                     help="batched 1D: grouped-launch tiling 'threads,rows' instead of autotuning "
                          "(rows 0 = whole cycles)")
@@ -446,8 +445,7 @@ def shape_name(shape):
     bits = shape[2]
     return {"bits": bits, "threads": shape[0], "wave_columns": 64 if bits & 1 else 32,
             "k_slice": "32 (two LDS stages)" if bits & 2 else "default",
-            "intermediates": "row-major, folded while staging" if bits & 4
-            else "prefolded planes (n a multiple of 256)"}
+            "intermediates": "row-major, folded while staging"}
 
 
 def stencil_roofline(ridc, s, x0, nt, reps):

@@ -1936,7 +1936,7 @@ int ridc_kernel_time(ridc_handle* h, int32_t reps, double* us_per_launch, double
   if (h->p.dim == 2) {
     rc = plan2d_time_pass(h->p2, s, reps, h->stream, us_per_launch);
     if (rc != RIDC_OK) return rc;
-    const int passes = h->p.prec == RIDC_PREC_FP64 ? 4 : 8;
+    const int passes = h->p.prec == RIDC_PREC_FP64 ? 2 : 4;
     if (work_per_launch) *work_per_launch = flops / passes;   // one pass over every level
     return RIDC_OK;
   }

@@ -11,24 +11,24 @@
 // the transforms scales with the increment, not with u; the sums and level differences are
 // FP64 in every precision.
 //
-// Solve: fast diagonalisation.  With the orthonormal type-I sine matrix Q (symmetric,
-// Q_{ik} = sqrt(2/(n+1)) sin(pi (i+1)(k+1)/(n+1))) and mu_k = (4/h^2) sin^2(pi (k+1)/(2(n+1))),
-// (I - dt nu Lap_h)^{-1} B = Q [(Q B Q) ./ (1 + dt nu (mu_i + mu_k))] Q.
-// Each product by Q is one pass C = (A Q)^T: two passes give Q B Q in the original orientation.
-// A pass is a GEMM on the matrix cores (v_mfma_f64_16x16x4f64, v_mfma_f32_16x16x4f32, or three
-// v_mfma_f32_16x16x32_bf16 products of hi/lo BF16 splits), batched over every active level of
-// every instance in one launch; the eigenvalue divide and the final update are fused into the
-// epilogues of passes 2 and 4.  Sides that are multiples of 64 fold Q by its reflection
-// symmetry, Q_{n-1-k, j} = (-1)^j Q_{k, j}, which halves the contraction (k_pass2d).  When n is
-// a multiple of 256 the passes of a solve hand each other their intermediates already folded
-// (sums and differences of mirrored columns; split into BF16 hi/lo on the split-BF16 path);
-// otherwise, and for the first pass of a solve, the intermediates are row-major (FP32 on the
-// reduced-precision paths) and a pass folds (and splits) its operand while staging it.
+// Solve: diagonalisation along the rows only.  With the orthonormal type-I sine matrix Q
+// (symmetric, Q_{ik} = sqrt(2/(n+1)) sin(pi (i+1)(k+1)/(n+1))) and mu_k = (4/h^2) sin^2(pi (k+1) /
+// (2(n+1))), T = B Q turns (I - dt nu Lap_h) X = B into one constant tridiagonal system down each
+// column j of T, (1 + dt nu mu_j) x - dt nu D2 x = T_j, and X is the solutions times Q.
+// Diagonalising the columns as well would take two more products by Q, the cost of a pass each
+// (75 us at 1024^2 over four levels in FP64); the line solves read and write each vector once
+// (k_lines2d, 20 us there, which took the step from 305 to 205 us).
+// Each product by Q is one pass C = A Q, a GEMM on the matrix cores (v_mfma_f64_16x16x4f64,
+// v_mfma_f32_16x16x4_f32, or three v_mfma_f32_16x16x32_bf16 products of hi/lo BF16 splits),
+// batched over every active level of every instance in one launch; the final update is fused
+// into the epilogue of the second pass.  Sides that are multiples of 64 fold Q by its reflection
+// symmetry, Q_{n-1-k, j} = (-1)^j Q_{k, j}, which halves the contraction (k_pass2d): a pass folds
+// (and splits) its operand while staging it.
 //
 // Reduced precision (FP32 or split BF16) adds one FP64 residual refinement:
 //   x1 = S~(b),  rho = b - (x1 - dt nu Lap_h x1)  (FP64 5-point),  x = x1 + S~(rho);
-// x1 is held in FP32: the pass that produces it accumulates in FP32 (no divide), so x1 is an
-// FP32 value and storing it in FP32 loses nothing.
+// x1 is held in FP32: the pass that produces it accumulates in FP32, so x1 is an FP32 value and
+// storing it in FP32 loses nothing.  The line solves compute in FP64 and store FP32.
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -48,7 +48,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16;
 
 enum { PREC_F64 = 0, PREC_F32 = 1, PREC_BF16 = 2 };
-enum { OUT_F64 = 0, OUT_F32 = 1, OUT_FINAL = 3, OUT_FOLD = 4 };
+enum { OUT_F64 = 0, OUT_F32 = 1, OUT_FINAL = 3 };
 
 // One (instance, level) of the 2D pipeline: static for a handle.
 struct Lvl2D {
@@ -56,10 +56,10 @@ struct Lvl2D {
   const double* prev;   // ring of level j-1 (null for j = 0)
   const double* W;      // weights, j rows x (j+1)
   double* b64;          // FP64 right-hand side (kept for the residual)
-  double* x64;          // FP64 first solve (refinement) or FP64 intermediate
-  void* lo0;            // FP32-sized buffers of the reduced-precision paths (row-major FP32 or
-                        // folded planes)
-  void* lo1;
+  double* x64;          // FP64 sine coefficients, or (refined paths) the FP32 first solve
+  float* lo0;           // reduced precision: the right-hand side or residual the solve takes
+  float* lo1;           // reduced precision: its sine coefficients
+  const double* col;    // line-solve constants of every column: lambda, g, kappa (n each)
   int64_t nt, sigma0;
   int32_t n, j, R_own, R_prev, fe, prec;
   double dt, nu_h2;
@@ -67,14 +67,11 @@ struct Lvl2D {
 
 // One batch entry of a transform pass.
 struct Pass2D {
-  const void* A;        // input: row-major n x n (FP64, or FP32 in the reduced-precision paths),
-                        // or the folded planes of the previous pass
+  const void* A;        // input: row-major n x n (FP64, or FP32 in the reduced-precision paths)
   void* C;              // output (unless final)
   const float* add;     // final epilogue: extra term (x1 of the refinement, FP32), nullable
   const void* Q;        // transform matrix in the input precision (BF16: hi, lo at +n*n)
-  const double* lam;    // dt nu mu_k (divide epilogue)
   int32_t level;        // index into the level table
-  int32_t divide;       // divide by 1 + lam_i + lam_k
 };
 
 struct Plan2D {
@@ -92,7 +89,7 @@ struct Plan2D {
   const double* Q64 = nullptr;
   const float* Q32 = nullptr;
   const u16* Qbf = nullptr;         // hi then lo
-  double* lam = nullptr;
+  double* col = nullptr;            // line-solve constants (Lvl2D::col)
   hipStream_t stream = nullptr;
   int tile = 0;                     // pass launch shape: kPassWide64 | kPassNarrowK (results
                                     // are bitwise the same for every shape)
@@ -126,19 +123,18 @@ __device__ __forceinline__ void gst(void* p, V v) {
 
 // The FP32 copy of a right-hand side or residual that the first pass of a reduced-precision
 // solve reads (row-major; that pass folds it, and the split-BF16 pass splits it, while staging).
-__device__ __forceinline__ void store_lo(void* base, int64_t idx, double v) {
-  gst<float>((float*)base + idx, (float)v);
+__device__ __forceinline__ void store_lo(float* base, int64_t idx, double v) {
+  gst<float>(base + idx, (float)v);
 }
 
 // ---------------------------------------------------------------------------------------------
-// stencil kernels: a wave owns 64 columns of ST_RY consecutive rows and walks down them, keeping
+// stencil kernels: a wave owns 64 columns of RY consecutive rows and walks down them, keeping
 // the rows above and below in registers, so each stencil vector is read once per point.  Column
 // neighbours come from the adjacent lanes (DPP wave shifts); the columns just outside the wave's
 // 64, which lanes 0 and 63 take, come from one load per half-wave at one address.  Columns at or
 // beyond n hold zero, which is also the Dirichlet ghost value, so a wave that straddles the last
 // column needs no special case.
 // ---------------------------------------------------------------------------------------------
-constexpr int ST_RY = 16;    // rows per wave
 constexpr int ST_WAVES = 4;  // waves per block, stacked in rows
 
 __device__ __forceinline__ double lane_below(double v) {   // lane l gets lane l-1's v (lane 0: 0)
@@ -175,9 +171,10 @@ __device__ __forceinline__ StBlock stencil_block() {
 }
 
 // Where a block's wave sits: the first row and column it owns, or false when it owns none.
+template <int RY>
 __device__ __forceinline__ bool stencil_tile(int n, const StBlock& b, int* iy0, int* ix0) {
   *ix0 = (int)b.x * 64;
-  *iy0 = ((int)b.y * ST_WAVES + (int)(threadIdx.x >> 6)) * ST_RY;
+  *iy0 = ((int)b.y * ST_WAVES + (int)(threadIdx.x >> 6)) * RY;
   return *ix0 < n && *iy0 < n;
 }
 
@@ -199,7 +196,7 @@ struct RhsRow {
 // predictor), or -1: any j, up to the largest order.  This kernel uses no LDS, and its plain
 // (flat) loads measured faster than global ones (31.2 against 33.2 us per launch at 1024^2,
 // FP64).
-template <int JT>
+template <int JT, int RY>
 __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, int ix0) {
   constexpr int JN = JT < 0 ? RIDC_MAX_ORDER : (JT == 0 ? 1 : JT);
   const int n = L.n;
@@ -237,7 +234,7 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   // The walk down the strip goes RG rows at a time, each group unrolled and without a branch,
   // so that the loads of a group's rows are issued together: lanes past n and rows outside the
   // grid load a clamped in-range address and take zero instead, lanes 0 and 63 take their edge
-  // column by a select, and the stores follow each group.  Every wave has ST_RY rows (n is a
+  // column by a select, and the stores follow each group.  Every wave has RY rows (n is a
   // multiple of 32).  Measured at 1024^2, FP64: 29.1 us per launch with a branch per row and
   // edge, 22.6 us with RG = 2 (114 registers), 22.8 with 1, 26.5 with 4 (148), 27.7 with 8
   // (228), 38.5 with the whole strip unrolled (388 registers, one wave per SIMD).
@@ -278,7 +275,7 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   RhsRow mid = load(iy0);
   constexpr int RG = 2;
 #pragma unroll
-  for (int q = 0; q < ST_RY; q += RG) {
+  for (int q = 0; q < RY; q += RG) {
     double bs[RG];
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
@@ -306,19 +303,20 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   }
 }
 
+template <int RY>
 __global__ __launch_bounds__(256) void k_rhs2d(const Lvl2D* __restrict__ levels, int64_t sigma) {
   const StBlock blk = stencil_block();
   const Lvl2D& L = levels[blk.z];
   int64_t m;
   if (!level_active(L, sigma, &m)) return;
   int iy0, ix0;
-  if (!stencil_tile(L.n, blk, &iy0, &ix0)) return;
+  if (!stencil_tile<RY>(L.n, blk, &iy0, &ix0)) return;
   switch (L.j) {
-    case 0: rhs_level<0>(L, m, iy0, ix0); break;
-    case 1: rhs_level<2>(L, m, iy0, ix0); break;
-    case 2: rhs_level<3>(L, m, iy0, ix0); break;
-    case 3: rhs_level<4>(L, m, iy0, ix0); break;
-    default: rhs_level<-1>(L, m, iy0, ix0); break;
+    case 0: rhs_level<0, RY>(L, m, iy0, ix0); break;
+    case 1: rhs_level<2, RY>(L, m, iy0, ix0); break;
+    case 2: rhs_level<3, RY>(L, m, iy0, ix0); break;
+    case 3: rhs_level<4, RY>(L, m, iy0, ix0); break;
+    default: rhs_level<-1, RY>(L, m, iy0, ix0); break;
   }
 }
 
@@ -326,6 +324,7 @@ __global__ __launch_bounds__(256) void k_rhs2d(const Lvl2D* __restrict__ levels,
 // FP32 (in the x64 buffer; it leaves an FP32 accumulator, so nothing is lost).  Every row of the
 // wave's column strip is loaded before any is used, so all of a wave's loads are in flight at
 // once.
+template <int RY>
 __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ levels, int64_t sigma) {
   const StBlock blk = stencil_block();
   const Lvl2D& L = levels[blk.z];
@@ -333,7 +332,7 @@ __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ level
   if (!level_active(L, sigma, &m)) return;
   const int n = L.n;
   int iy0, ix0;
-  if (!stencil_tile(n, blk, &iy0, &ix0)) return;
+  if (!stencil_tile<RY>(n, blk, &iy0, &ix0)) return;
   const int lane = threadIdx.x & 63;
   const int ix = ix0 + lane;
   const bool col = ix < n;
@@ -341,31 +340,31 @@ __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ level
   // No load sits behind a branch, so that all of them issue back to back: lanes past n and the
   // rows beyond the grid read a clamped in-range address and take zero instead, and the column
   // just outside the strip, which lane 0 (west) or 63 (east) takes, is read by every lane of
-  // its half at that one address.  Every wave has ST_RY rows (n is a multiple of 32).
+  // its half at that one address.  Every wave has RY rows (n is a multiple of 32).
   const int ixc = col ? ix : n - 1;
   const int xo = lane < 32 ? ix0 - 1 : ix0 + 64;
   const bool xok = xo >= 0 && xo < n;
   const int xoc = xok ? xo : ixc;
-  float xr[ST_RY + 2], xe[ST_RY];
-  double br[ST_RY];
+  float xr[RY + 2], xe[RY];
+  double br[RY];
 #pragma unroll
-  for (int r = 0; r < ST_RY + 2; ++r) {
+  for (int r = 0; r < RY + 2; ++r) {
     const int iy = iy0 - 1 + r;
     const int iyc = iy < 0 ? 0 : (iy < n ? iy : n - 1);
     const float v = gld<float>(x1 + (int64_t)iyc * n + ixc);
     xr[r] = iy >= 0 && iy < n && col ? v : 0.0f;
   }
 #pragma unroll
-  for (int r = 0; r < ST_RY; ++r) {
+  for (int r = 0; r < RY; ++r) {
     const int64_t row = (int64_t)(iy0 + r) * n;
     const double b = gld<double>(L.b64 + row + ixc);
     const float e = gld<float>(x1 + row + xoc);
     br[r] = col ? b : 0.0;
     xe[r] = xok ? e : 0.0f;
   }
-  double res[ST_RY];
+  double res[RY];
 #pragma unroll
-  for (int r = 0; r < ST_RY; ++r) {
+  for (int r = 0; r < RY; ++r) {
     double xw = (double)lane_below(xr[r + 1]), xa = (double)lane_above(xr[r + 1]);
     xw = lane == 0 ? (double)xe[r] : xw;
     xa = lane == 63 ? (double)xe[r] : xa;
@@ -375,30 +374,248 @@ __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ level
   }
   if (col) {
 #pragma unroll
-    for (int r = 0; r < ST_RY; ++r) store_lo(L.lo0, (int64_t)(iy0 + r) * n + ix, res[r]);
+    for (int r = 0; r < RY; ++r) store_lo(L.lo0, (int64_t)(iy0 + r) * n + ix, res[r]);
   }
 }
 
-// one launch of a stencil kernel over `cnt` levels of sides up to nmax
-static void launch_stencil(void (*k)(const Lvl2D*, int64_t), const Lvl2D* lv, int cnt, int64_t nmax,
-                    int64_t sigma, hipStream_t st) {
-  const unsigned gx = (unsigned)((nmax + 63) / 64);
-  const unsigned gy = (unsigned)((nmax + ST_RY * ST_WAVES - 1) / (ST_RY * ST_WAVES));
-  hipLaunchKernelGGL(k, dim3(gx, gy, cnt), dim3(64 * ST_WAVES), 0, st, lv, sigma);
+// One launch of a stencil kernel over `cnt` levels of sides up to nmax.  Rows per wave: 16 when
+// that gives every SIMD two waves or more, else 4, so that a small grid's loads spread over more
+// compute units and a wave's walk down its rows is a quarter as long (the bits are the same).
+template <int RY>
+static dim3 stencil_grid(int cnt, int64_t nmax) {
+  return dim3((unsigned)((nmax + 63) / 64), (unsigned)((nmax + RY * ST_WAVES - 1) / (RY * ST_WAVES)),
+              cnt);
+}
+static bool short_strips(int cnt, int64_t nmax) {
+  return (nmax + 63) / 64 * (nmax / 16) * cnt < 2048;
+}
+static void launch_rhs(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, hipStream_t st) {
+  if (short_strips(cnt, nmax))
+    hipLaunchKernelGGL(k_rhs2d<4>, stencil_grid<4>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv, sigma);
+  else
+    hipLaunchKernelGGL(k_rhs2d<16>, stencil_grid<16>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv,
+                       sigma);
+}
+static void launch_resid(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, hipStream_t st) {
+  if (short_strips(cnt, nmax))
+    hipLaunchKernelGGL(k_resid2d<4>, stencil_grid<4>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv,
+                       sigma);
+  else
+    hipLaunchKernelGGL(k_resid2d<16>, stencil_grid<16>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv,
+                       sigma);
 }
 
 // ---------------------------------------------------------------------------------------------
-// transform pass C = (A Q)^T on the matrix cores
-//   block tile 128 x 128, 8 waves in 2 (rows) x 4 (columns), each wave 64 x 32 = 4 x 2 MFMA
-//   tiles of 16 x 16; k staged through LDS in slices of BK with 16-byte global loads
+// line solves: (1 + lam_j + 2r) x_y - r (x_{y-1} + x_{y+1}) = T_y down every column j
+//
+// The matrix is constant along a column, so up to its first row it is (1/g)(1 - lambda E^-1)
+// (1 - lambda E) (E: the shift by a row; lambda = 2r / (b + sqrt(b^2 - 4r^2)) < 1, b = 1 + lam_j +
+// 2r, g = lambda / r): a first-order recurrence down the column, one back up, and a factor.  The
+// upward recurrence starts from zero past the last row, the zero ghost there; the downward one
+// starts from c_0 = -kappa z_0, kappa = lambda (1 - lambda^2) / (1 - lambda^{2n+2}), which makes the
+// value at the other ghost row zero (z_0: what the two recurrences leave in the first row when
+// c_0 = 0).  Every term of a recurrence has lambda's sign, so nothing cancels.
+//
+// A thread holds M consecutive rows of one column (a segment) in registers and runs both
+// recurrences over them from zero; two numbers per segment (its last value going down and its
+// first value coming back up) go through LDS, every thread chains them over the column's
+// segments, and the recurrences run again from the true carries.  A block is 16 columns (128
+// bytes of a row, a cache line in FP64) of the whole height: 64 segments of M = 16 rows at
+// n = 1024, one block per compute unit for four levels.  Bound: HBM, one read and one write of
+// each vector; the arithmetic is FP64 also where the coefficients are stored in FP32.
 // ---------------------------------------------------------------------------------------------
-constexpr int BT = 128;      // block tile (rows of A x columns of Q)
-// A wave computes 64 rows x WC columns of the block tile: WC = 32 (8 waves of 512 threads, two
-// per SIMD) or WC = 64 (4 waves of 256 threads, one per SIMD with the whole register file,
-// fewer LDS reads per MFMA).
-template <int WC>
+constexpr int LS_COLS = 16;   // columns per block
+constexpr int LS_SEGS = 64;   // segments in registers at a time
+
+// Blocks go to the 8 XCDs round-robin by linear id; each XCD takes a contiguous run of column
+// blocks, so that two blocks sharing a 128-byte line (FP32 columns) share its L2.
+__device__ __forceinline__ unsigned xcd_run(unsigned id, unsigned total) {
+  return total % 8 == 0 ? (id % 8) * (total / 8) + id / 8 : id;
+}
+
+// The recurrences over one segment from zero: its last value going down (t) and the first value
+// coming back up (h); v keeps the downward values.
+template <int M>
+__device__ __forceinline__ void line_down(double lam, double (&v)[M], double* t, double* h) {
+#pragma unroll
+  for (int k = 1; k < M; ++k) v[k] = __builtin_fma(lam, v[k - 1], v[k]);
+  double up = v[M - 1];
+#pragma unroll
+  for (int k = M - 2; k >= 0; --k) up = __builtin_fma(lam, up, v[k]);
+  *t = v[M - 1];
+  *h = up;
+}
+
+// Add the true downward carry c and come back up from the true upward carry z, storing g z_k.
+template <typename T, int M>
+__device__ __forceinline__ void line_up(double lam, double g, double (&v)[M], double c, double z,
+                                        T* __restrict__ col, int n) {
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    c *= lam;
+    v[k] += c;
+  }
+#pragma unroll
+  for (int k = M - 1; k >= 0; --k) {
+    z = __builtin_fma(lam, z, v[k]);
+    gst<T>(col + (int64_t)k * n, (T)(g * z));
+  }
+}
+
+// P = lambda^M and G = sum_{k<M} lambda^(2k+1) = lambda (1 + lambda^2)(1 + lambda^4) .. (1 +
+// lambda^M), M a power of two: what a carry becomes over a segment, down, and down and back up.
+template <int M>
+__device__ __forceinline__ void line_powers(double lam, double* P, double* G) {
+  double p = lam, g = lam;
+#pragma unroll
+  for (int k = 1; k < M; k *= 2) {
+    p *= p;
+    g = __builtin_fma(g, p, g);
+  }
+  *P = p;
+  *G = g;
+}
+
+// ns = blockDim.x / 16 segments of M rows: n = ns M.
+template <typename T, int M>
+__global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d(const Lvl2D* __restrict__ levels,
+                                                               int64_t sigma) {
+  __shared__ double ex[2][LS_SEGS * LS_COLS];
+  const unsigned q = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  const Lvl2D& L = levels[q / gridDim.x];
+  int64_t m;
+  if (!level_active(L, sigma, &m)) return;
+  const int n = L.n, cl = threadIdx.x % LS_COLS;
+  const int j = (int)(q % gridDim.x) * LS_COLS + cl;
+  const int seg = threadIdx.x / LS_COLS, ns = blockDim.x / LS_COLS;
+  T* __restrict__ col =
+      (sizeof(T) == 8 ? (T*)L.x64 : (T*)L.lo1) + (int64_t)seg * M * n + j;
+  double v[M];
+#pragma unroll
+  for (int k = 0; k < M; ++k) v[k] = (double)gld<T>(col + (int64_t)k * n);
+  const double lam = gld<double>(L.col + j), g = gld<double>(L.col + n + j);
+  const double kappa = gld<double>(L.col + 2 * n + j);
+  double t, h, P, G;
+  line_down<M>(lam, v, &t, &h);
+  line_powers<M>(lam, &P, &G);
+  ex[0][threadIdx.x] = t;
+  ex[1][threadIdx.x] = h;
+  __syncthreads();
+  // first row with c_0 = 0, hence the true c_0; then this segment's carries
+  double c = 0.0, z = 0.0, w = 1.0, mine = 0.0;
+  for (int s = 0; s < ns; ++s) {
+    z = __builtin_fma(w, __builtin_fma(c, G, ex[1][s * LS_COLS + cl]), z);
+    c = __builtin_fma(P, c, ex[0][s * LS_COLS + cl]);
+    w *= P;
+  }
+  c = -kappa * z;
+  z = 0.0;
+  w = 1.0;
+  for (int s = 0; s < ns; ++s) {
+    if (s == seg) mine = c;
+    if (s > seg) {
+      z = __builtin_fma(w, __builtin_fma(c, G, ex[1][s * LS_COLS + cl]), z);
+      w *= P;
+    }
+    c = __builtin_fma(P, c, ex[0][s * LS_COLS + cl]);
+  }
+  line_up<T, M>(lam, g, v, mine, z, col, n);
+}
+
+// Columns of more than 64 segments of 32 rows (n > 2048): the block walks its columns 2048 rows
+// at a time, twice (the second walk reads the rows again instead of keeping them); t and h of
+// all n / 32 segments stay in LDS (at most 128 KB), where one thread per column turns them into
+// the segments' carries.
+template <typename T>
+__global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d_long(const Lvl2D* __restrict__ levels,
+                                                                    int64_t sigma) {
+  constexpr int M = 32;
+  extern __shared__ double exl[];
+  const unsigned q = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  const Lvl2D& L = levels[q / gridDim.x];
+  int64_t m;
+  if (!level_active(L, sigma, &m)) return;
+  const int n = L.n, cl = threadIdx.x % LS_COLS, ns = n / M;
+  const int j = (int)(q % gridDim.x) * LS_COLS + cl;
+  T* __restrict__ col0 = (sizeof(T) == 8 ? (T*)L.x64 : (T*)L.lo1) + j;
+  double* tt = exl;
+  double* hh = exl + ns * LS_COLS;
+  const double lam = gld<double>(L.col + j), g = gld<double>(L.col + n + j);
+  const double kappa = gld<double>(L.col + 2 * n + j);
+  double v[M];
+  for (int seg = threadIdx.x / LS_COLS; seg < ns; seg += LS_SEGS) {
+    const T* __restrict__ col = col0 + (int64_t)seg * M * n;
+#pragma unroll
+    for (int k = 0; k < M; ++k) v[k] = (double)gld<T>(col + (int64_t)k * n);
+    line_down<M>(lam, v, &tt[seg * LS_COLS + cl], &hh[seg * LS_COLS + cl]);
+  }
+  __syncthreads();
+  if (threadIdx.x < LS_COLS) {
+    double P, G, c = 0.0, z = 0.0, w = 1.0;
+    line_powers<M>(lam, &P, &G);
+    for (int s = 0; s < ns; ++s) {
+      z = __builtin_fma(w, __builtin_fma(c, G, hh[s * LS_COLS + cl]), z);
+      c = __builtin_fma(P, c, tt[s * LS_COLS + cl]);
+      w *= P;
+    }
+    c = -kappa * z;
+    for (int s = 0; s < ns; ++s) {           // tt: the carry before a segment; hh: its first value
+      const double t = tt[s * LS_COLS + cl];
+      hh[s * LS_COLS + cl] = __builtin_fma(c, G, hh[s * LS_COLS + cl]);
+      tt[s * LS_COLS + cl] = c;
+      c = __builtin_fma(P, c, t);
+    }
+    z = 0.0;
+    for (int s = ns - 1; s >= 0; --s) {      // hh: the carry after a segment
+      const double h = hh[s * LS_COLS + cl];
+      hh[s * LS_COLS + cl] = z;
+      z = __builtin_fma(P, z, h);
+    }
+  }
+  __syncthreads();
+  for (int seg = threadIdx.x / LS_COLS; seg < ns; seg += LS_SEGS) {
+    T* __restrict__ col = col0 + (int64_t)seg * M * n;
+#pragma unroll
+    for (int k = 0; k < M; ++k) v[k] = (double)gld<T>(col + (int64_t)k * n);
+    double t, h;
+    line_down<M>(lam, v, &t, &h);
+    line_up<T, M>(lam, g, v, tt[seg * LS_COLS + cl], hh[seg * LS_COLS + cl], col, n);
+  }
+}
+
+// Rows per segment: the fewest (8, 16 or 32) that keep a column within 64 segments; n is a
+// multiple of 32.
+template <typename T>
+static void launch_lines(const Lvl2D* lv, int cnt, int64_t n, int64_t sigma, hipStream_t st) {
+  const dim3 grid((unsigned)(n / LS_COLS), (unsigned)cnt);
+  const unsigned t8 = (unsigned)(n / 8 * LS_COLS);
+  if (n <= 8 * LS_SEGS)
+    hipLaunchKernelGGL((k_lines2d<T, 8>), grid, dim3(t8), 0, st, lv, sigma);
+  else if (n <= 16 * LS_SEGS)
+    hipLaunchKernelGGL((k_lines2d<T, 16>), grid, dim3(t8 / 2), 0, st, lv, sigma);
+  else if (n <= 32 * LS_SEGS)
+    hipLaunchKernelGGL((k_lines2d<T, 32>), grid, dim3(t8 / 4), 0, st, lv, sigma);
+  else
+    hipLaunchKernelGGL((k_lines2d_long<T>), grid, dim3(LS_COLS * LS_SEGS),
+                       2 * (size_t)(n / 32) * LS_COLS * sizeof(double), st, lv, sigma);
+}
+
+// ---------------------------------------------------------------------------------------------
+// transform pass C = A Q along the rows, on the matrix cores
+//   block tile BT x BT (128: 8 waves of 64 x 32 or 4 of 64 x 64; 64: 4 waves of 32 x 32; 32: 2
+//   waves of 32 x 16), each wave a grid of 16 x 16 MFMA tiles; k staged through LDS in slices of
+//   BK with 16-byte global loads
+// ---------------------------------------------------------------------------------------------
+constexpr int BT0 = 128;     // largest block tile (rows of A x columns of Q)
+// Rows per wave, and threads per block of waves of WC columns.  WC = 32 at BT = 128 puts two
+// waves on a SIMD; WC = 64 one, with the whole register file and fewer LDS reads per MFMA.
+template <int BT>
+constexpr int wave_rows() {
+  return BT == 128 ? 64 : 32;
+}
+template <int BT, int WC>
 constexpr int pass_threads() {
-  return WC == 64 ? 256 : 512;
+  return (BT / wave_rows<BT>()) * (BT / WC) * 64;
 }
 
 template <int PREC>
@@ -425,7 +642,7 @@ struct Tr<PREC_BF16> {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef float flt2 __attribute__((ext_vector_type(2)));
 
 // Folding by the reflection symmetry of the sine matrix, Q_{n-1-k, j} = (-1)^j Q_{k, j}:
 //   (A Q)_{ij} = sum_{k < n/2} (A_{ik} + (-1)^j A_{i, n-1-k}) Q_{kj},
@@ -455,19 +672,6 @@ __device__ __forceinline__ void split4_bf16(flt4 v, uint2* hi, uint2* lo) {
   *lo = uint2{(unsigned)l[0] | ((unsigned)l[1] << 16), (unsigned)l[2] | ((unsigned)l[3] << 16)};
 }
 
-// only the sums (sg = 1) or only the differences (sg = -1), for blocks whose output columns all
-// have one parity
-__device__ __forceinline__ u32x4 fold1_f64(u32x4 a, u32x4 m, double sg) {
-  const dbl2 x = __builtin_bit_cast(dbl2, a), y = __builtin_bit_cast(dbl2, m);
-  return __builtin_bit_cast(u32x4, dbl2{x[0] + sg * y[1], x[1] + sg * y[0]});
-}
-__device__ __forceinline__ u32x4 fold1_f32(u32x4 a, u32x4 m, float sg) {
-  const flt4 x = __builtin_bit_cast(flt4, a), y = __builtin_bit_cast(flt4, m);
-  return __builtin_bit_cast(u32x4, flt4{x[0] + sg * y[3], x[1] + sg * y[2], x[2] + sg * y[1],
-                                        x[3] + sg * y[0]});
-}
-
-
 // Instruction order of one pipelined k-slice step (a single basic block): NR LDS reads, then
 // NW LDS writes and global loads, each placed after one of the step's NM MFMAs, and the rest of
 // the MFMAs after them.  Groups with no instruction left to take stay empty.
@@ -489,38 +693,37 @@ __device__ __forceinline__ void interleave_step() {
 
 // FOLD (n a multiple of 64): the contraction runs over k < n/2 with the folded A operands and
 // E.Q the folded transform: row j' (n rows) holds Q_{k, perm(j')} for k < n/2, perm(j') = 2j'
-// for j' < n/2 and 2(j' - n/2) + 1 above; output column j' of the block grid is column perm(j').
-// KX = 2 doubles the k-slice (one slice in flight instead of two).  A k-slice has two LDS stages
-// (the next slice is stored while the current one feeds the matrix cores, one barrier per
-// slice), except the wide split-BF16 slices, whose operands fill one stage's worth of the LDS
-// twice over.  Most variants need more than 64 KB, so every variant takes its LDS dynamically
-// (pass_lds_bytes).
+// for j' < n/2 and 2(j' - n/2) + 1 above.  A block takes BT consecutive output columns, its
+// first BT/2 local columns the even ones (against the sums), the others the odd ones (against
+// the differences); a wave's columns are all of one parity.
+// KX = 2 doubles the k-slice (split BF16: one slice in flight instead of two).  A k-slice has
+// two LDS stages (the next slice is stored while the current one feeds the matrix cores, one
+// barrier per slice), except the wide split-BF16 slices, whose operands fill one stage's worth of
+// the LDS twice over.  Most variants need more than 64 KB, so every variant takes its LDS
+// dynamically (pass_lds_bytes).
 template <int PREC, int KX>
 constexpr int lds_stages() {
   return PREC == PREC_BF16 && KX == 2 ? 1 : 2;
 }
-// A operand tiles per LDS stage: the folded sums and differences when the pass folds while
-// staging (a block with output columns on both sides of n/2 needs both), else one
-template <int FOLD, int AIN>
-constexpr int a_tiles() {
-  return FOLD && !AIN ? 2 : 1;
-}
-template <int PREC, int KX, int AIN>
+template <int PREC, int KX, int BT>
 constexpr size_t pass_lds_bytes(int fold) {
   typedef typename Tr<PREC>::T T;
+  typedef typename std::conditional<PREC == PREC_F64, double, float>::type ST;
   constexpr int BK = Tr<PREC>::BK * KX;
   constexpr int LDE = (BK * (int)sizeof(T) + 16) / (int)sizeof(T);
   constexpr int NSPLIT = PREC == PREC_BF16 ? 2 : 1;
-  const int na = fold && !AIN ? 2 : 1;
-  return (size_t)lds_stages<PREC, KX>() * (na * NSPLIT + NSPLIT) * BT * LDE * sizeof(T);
+  const size_t k = (size_t)lds_stages<PREC, KX>() * ((fold ? 2 : 1) * NSPLIT + NSPLIT) * BT * LDE *
+                   sizeof(T);
+  const size_t ep = (size_t)(BT / wave_rows<BT>()) * 16 * (BT * sizeof(ST) + 16);
+  return k > ep ? k : ep;
 }
 
-template <int PREC, int OUT, int FOLD, int KX, int WC, int AIN>
-__global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __restrict__ passes,
-                                                               const Lvl2D* __restrict__ levels,
-                                                               int64_t sigma) {
-  constexpr int NTHR = pass_threads<WC>();
-  constexpr int NB = WC / 16;                         // 16-column MFMA tiles per wave
+template <int PREC, int OUT, int FOLD, int KX, int BT, int WC>
+__global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
+    const Pass2D* __restrict__ passes, const Lvl2D* __restrict__ levels, int64_t sigma) {
+  constexpr int NTHR = pass_threads<BT, WC>();
+  constexpr int WM = wave_rows<BT>();
+  constexpr int MT = WM / 16, NB = WC / 16;           // 16 x 16 MFMA tiles per wave
   typedef Tr<PREC> TR;
   typedef typename TR::T T;
   typedef typename TR::Acc Acc;
@@ -530,9 +733,8 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
   constexpr int CH = BK * (int)sizeof(T) / 16;        // 16-byte chunks per row
   constexpr int NSPLIT = PREC == PREC_BF16 ? 2 : 1;
   constexpr int CPT = BT * CH / NTHR;                 // chunks per thread per operand and split
-  constexpr int NA = a_tiles<FOLD, AIN>();           // A operands in LDS (folded sums, diffs)
-  static_assert(!AIN || FOLD, "prefolded operands exist for folded transforms only");
-  static_assert(OUT != OUT_FOLD || FOLD, "a folded output needs the folded transform");
+  constexpr int NA = FOLD ? 2 : 1;                    // A operands in LDS (sums, differences)
+  static_assert(BT * CH % NTHR == 0, "whole chunks per thread");
   extern __shared__ __attribute__((aligned(16))) unsigned char pass_smem[];
   // LDS stage b of a k-slice: the A operands, then Q
   constexpr size_t A_BYTES = (size_t)NA * NSPLIT * BT * LDE * sizeof(T);
@@ -543,93 +745,80 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
   auto stage_b = [&](int b) {
     return reinterpret_cast<T (*)[BT * LDE]>(pass_smem + b * STAGE_BYTES + A_BYTES);
   };
-  T (*As)[NSPLIT][BT * LDE] = stage_a(0);      // also the epilogue's staging area
 
-  // XCD-aware tile order: workgroups go to the 8 XCDs round-robin by linear id, so tile q of
-  // XCD x is x * (T / 8) + (id / 8): each XCD takes a contiguous run of tiles, and the column
-  // tiles of one row tile of A meet in one L2 (identity when T is not a multiple of 8)
-  unsigned bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  // XCD-aware tile order: each XCD takes a contiguous run of tiles, and the column tiles of one
+  // row tile of A meet in one L2
+  unsigned bx, by, bz;
   {
     const unsigned t = gridDim.x;
-    const unsigned tiles = t * gridDim.y * gridDim.z;
-    const unsigned id = bx + t * (by + gridDim.y * bz);
-    if (tiles % 8 == 0) {
-      const unsigned q = (id % 8) * (tiles / 8) + id / 8;
-      bx = q % t;
-      by = (q / t) % gridDim.y;
-      bz = q / (t * gridDim.y);
-    }
+    const unsigned q = xcd_run(blockIdx.x + t * (blockIdx.y + gridDim.y * blockIdx.z),
+                               t * gridDim.y * gridDim.z);
+    bx = q % t;
+    by = (q / t) % gridDim.y;
+    bz = q / (t * gridDim.y);
   }
   const Pass2D& E = passes[bz];
   const Lvl2D& L = levels[E.level];
   int64_t m;
   if (!level_active(L, sigma, &m)) return;
   const int n = L.n;
-  // Rows of A (i) of the block: BT consecutive rows from row0, or, when the epilogue folds its
-  // output for the next pass, the mirrored pairs row0 + t and n-1-row0-t (t < BT/2) at local
-  // rows t and BT/2 + t, so that the block holds both columns of every folded pair of C^T.
-  constexpr bool MIRROR = OUT == OUT_FOLD;
-  constexpr int HB = BT / 2;
-  const int row0 = MIRROR ? by * HB : by * BT;
-  const int col0 = bx * BT;                  // columns of Q (j)
-  if ((MIRROR ? 2 * row0 : row0) >= n || col0 >= n) return;
-  auto a_row = [&](int r) { return MIRROR ? (r < HB ? row0 + r : n - 1 - row0 - (r - HB)) : row0 + r; };
+  const int row0 = by * BT, col0 = bx * BT;
+  if (row0 >= n || col0 >= n) return;
   const int64_t nn = (int64_t)n * n;
-  // A arrives row-major in FP64 or FP32 (the split-BF16 pass splits it while staging), or as
-  // prefolded planes of T (AIN); Q in T
+  const int half = n >> 1;
+  // A arrives row-major in FP64 or FP32 (the split-BF16 pass splits it while staging); Q in T
   typedef typename std::conditional<PREC == PREC_BF16, float, T>::type TA;
   constexpr int EA = 16 / (int)sizeof(TA);          // A elements per 16-byte chunk
   constexpr int CHA = BK * (int)sizeof(TA) / 16;    // A chunks per row
   constexpr int NAC = BT * CHA / NTHR;              // A chunks per thread
+  static_assert(BT * CHA % NTHR == 0, "whole A chunks per thread");
   const TA* A = (const TA*)E.A;
   const T* Q = (const T*)E.Q;
-  const int K = FOLD ? n / 2 : n;                   // contraction length
+  const int K = FOLD ? half : n;                    // contraction length
   const int64_t qsplit = (int64_t)n * K;            // BF16: lo part of the transform
   constexpr int E16 = 16 / (int)sizeof(T);          // elements per 16-byte chunk
-  // prefolded operands: planes (side, split) of n rows x n/2 elements of T, side 0 the sums
-  // A_{i,k} + A_{i,n-1-k} and side 1 the differences (BF16: split into hi, lo), each n x n/2
-  const T* Ap = (const T*)E.A;
-  const int64_t plane = (int64_t)n * K;
+  // row of Q of local column c (rows past n read a row in range; their columns are never stored)
+  auto q_row = [&](int c) {
+    if constexpr (FOLD) {
+      const int e = (col0 >> 1) + (c < BT / 2 ? c : c - BT / 2);
+      return (c < BT / 2 ? 0 : half) + (e < half ? e : half - 1);
+    } else {
+      return col0 + c < n ? col0 + c : n - 1;
+    }
+  };
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wm = (wave / (BT / WC)) * 64;    // wave tile origin inside the block
+  const int wm = (wave / (BT / WC)) * WM;    // wave tile origin inside the block
   const int wn = (wave % (BT / WC)) * WC;
 
-  Acc acc[4][NB];
+  // The FP32 accumulators go to the accumulation registers (the empty asm asks for the class):
+  // left among the vector registers, the allocator renamed some of them through registers that
+  // the next fragment loads write, which the build rejects.
+  Acc acc[MT][NB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[a][b] = Acc{0, 0, 0, 0};
+    for (int b = 0; b < NB; ++b) {
+      Acc z = Acc{0, 0, 0, 0};
+      if constexpr (PREC != PREC_F64) asm volatile("" : "+a"(z));
+      acc[a][b] = z;
+    }
 
   // global -> register staging of one k-slice (A, its mirrored columns when folding, Q); a
   // slice's loads are issued one MFMA phase before they are stored into LDS.  Rows past n (a
-  // partial block tile) read row n-1 instead: they only reach output rows or columns past n,
-  // which the epilogue never stores, and no select on the loaded values makes a step wait for
-  // its loads.
+  // partial block tile) read row n-1 instead: they only reach output rows past n, which the
+  // epilogue never stores, and no select on the loaded values makes a step wait for its loads.
   struct Slice {
-    u32x4 ra[NAC], rm[NAC], rp[NSPLIT][CPT], rb[NSPLIT][CPT];
+    u32x4 ra[NAC], rm[FOLD ? NAC : 1], rb[NSPLIT][CPT];
   };
-  Slice sl0;
-  const int side = FOLD && col0 >= (n >> 1) ? 1 : 0;
   auto gload = [&](Slice& S, int k0) {
-    if constexpr (AIN) {
 #pragma unroll
-      for (int s = 0; s < NSPLIT; ++s)
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-          const int id = tid + c * NTHR;
-          const int r = id / CH, q = id % CH;
-          S.rp[s][c] = gld<u32x4>(Ap + (side * NSPLIT + s) * plane + (int64_t)a_row(r) * K + k0 +
-                                  q * E16);
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < (AIN ? 0 : NAC); ++c) {
+    for (int c = 0; c < NAC; ++c) {
       const int id = tid + c * NTHR;
       const int r = id / CHA, q = id % CHA;
-      const int ga = a_row(r);
+      const int ga = row0 + r;
       const int64_t ko = k0 + q * EA;
       const TA* arow = A + (int64_t)(ga < n ? ga : n - 1) * n;
       S.ra[c] = gld<u32x4>(arow + ko);
@@ -641,23 +830,9 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
       for (int c = 0; c < CPT; ++c) {
         const int id = tid + c * NTHR;
         const int r = id / CH, q = id % CH;
-        const int gb = col0 + r;                        // Q symmetric: row j of Q = column j
         const int64_t ko = k0 + q * E16;
-        S.rb[s][c] = gld<u32x4>(Q + s * qsplit + (int64_t)(gb < n ? gb : n - 1) * K + ko);
+        S.rb[s][c] = gld<u32x4>(Q + s * qsplit + (int64_t)q_row(r) * K + ko);
       }
-  };
-  // a block whose output columns all lie on one side of n/2 needs only the sums (side 0) or
-  // only the differences (side 1)
-  const bool one_side = FOLD && (col0 + BT <= (n >> 1) || col0 >= (n >> 1));
-  // The main loops take one_side at compile time (os: std::true_type when the block needs one
-  // side of the fold), so that a pipelined step holds no branch.
-  auto with_side = [&](auto&& loop) {
-    if constexpr (FOLD && !AIN) {
-      if (one_side) loop(std::true_type{});
-      else loop(std::false_type{});
-    } else {
-      loop(std::false_type{});
-    }
   };
   // FP32/FP64 operand rows keep a k-slice permuted, k at (k % 4) * KQ + k / 4, so that the KQ
   // values one lane consumes over the slice (k = 4i + lane/16) are contiguous; BF16 rows keep
@@ -679,57 +854,34 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
       }
     }
   };
-  auto sstore = [&](const Slice& S, int stage, auto os) {
+  auto sstore = [&](const Slice& S, int stage) {
     T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
     T (*Bs)[BT * LDE] = stage_b(stage);
-    if constexpr (AIN) {
 #pragma unroll
-      for (int s = 0; s < NSPLIT; ++s)
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-          const int id = tid + c * NTHR;
-          const int r = id / CH, q = id % CH;
-          put(As[0][s] + r * LDE, q, S.rp[s][c]);
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < (AIN ? 0 : NAC); ++c) {
+    for (int c = 0; c < NAC; ++c) {
       const int id = tid + c * NTHR;
       const int r = id / CHA, q = id % CHA;
       const int ro = r * LDE;                        // row start, in elements
+      u32x4 su = S.ra[c], di = S.ra[c];
+      if constexpr (FOLD) {
+        if constexpr (PREC == PREC_F64)
+          fold_f64(S.ra[c], S.rm[c], &su, &di);
+        else
+          fold_f32(S.ra[c], S.rm[c], &su, &di);
+      }
       if constexpr (PREC == PREC_BF16) {
-        // 4 FP32 values (folded when FOLD) -> BF16 hi and lo at elements 4q .. 4q+3
+        // 4 FP32 values -> BF16 hi and lo at elements 4q .. 4q+3
         auto put4 = [&](int a, u32x4 v) {
           uint2 hi, lo;
           split4_bf16(__builtin_bit_cast(flt4, v), &hi, &lo);
           *(uint2*)(As[a][0] + ro + q * 4) = hi;
           *(uint2*)(As[a][1] + ro + q * 4) = lo;
         };
-        if constexpr (!FOLD) {
-          put4(0, S.ra[c]);
-        } else if constexpr (decltype(os)::value) {
-          put4(side, fold1_f32(S.ra[c], S.rm[c], side ? -1.0f : 1.0f));
-        } else {
-          u32x4 su, di;
-          fold_f32(S.ra[c], S.rm[c], &su, &di);
-          put4(0, su);
-          put4(1, di);
-        }
-      } else if constexpr (!FOLD) {
-        put(As[0][0] + ro, q, S.ra[c]);
-      } else if constexpr (decltype(os)::value) {
-        if constexpr (PREC == PREC_F64)
-          put(As[side][0] + ro, q, fold1_f64(S.ra[c], S.rm[c], side ? -1.0 : 1.0));
-        else
-          put(As[side][0] + ro, q, fold1_f32(S.ra[c], S.rm[c], side ? -1.0f : 1.0f));
+        put4(0, su);
+        if constexpr (FOLD) put4(1, di);
       } else {
-        u32x4 su, di;
-        if constexpr (PREC == PREC_F64)
-          fold_f64(S.ra[c], S.rm[c], &su, &di);
-        else
-          fold_f32(S.ra[c], S.rm[c], &su, &di);
         put(As[0][0] + ro, q, su);
-        put(As[1][0] + ro, q, di);
+        if constexpr (FOLD) put(As[1][0] + ro, q, di);
       }
     }
 #pragma unroll
@@ -742,46 +894,11 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
       }
   };
 
-  // the A operand of this wave's WC output columns: sums (0) for even output columns,
-  // differences (1) for odd ones -- uniform per wave, since n/2 and the wave's first column are
-  // multiples of WC (the launcher takes WC = 64 only when n/2 is a multiple of 64)
-  const int half = n >> 1;
-  const int pa0 = FOLD && !AIN && col0 + wn >= half ? 1 : 0;
+  // the A operand of this wave's columns: sums (0) for even output columns, differences (1) for
+  // odd ones
+  const int pa0 = FOLD && wn >= BT / 2 ? 1 : 0;
   const int KT = K / BK;
   const int r16 = lane & 15;
-  auto mfma_slice = [&](int stage) {
-    T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
-    T (*Bs)[BT * LDE] = stage_b(stage);
-    if constexpr (PREC == PREC_BF16) {
-#pragma unroll
-    for (int ks = 0; ks < KX; ++ks) {
-      // lane holds 8 consecutive k of row (l % 16), k offset 8 (l / 16), of k-step ks of 32
-      const int kb = (lane >> 4) * 16 + ks * 64;       // byte offset of the 8 k values
-      static_assert(NB == 2, "the split-BF16 pass takes 32-column waves");
-      bf16x8 ahi[4], alo[4], bhi[2], blo[2];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int ro = (wm + t * 16 + r16) * ROWB + kb;
-        ahi[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)As[pa0][0] + ro));
-        alo[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)As[pa0][1] + ro));
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int ro = (wn + t * 16 + r16) * ROWB + kb;
-        bhi[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)Bs[0] + ro));
-        blo[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)Bs[1] + ro));
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[a], bhi[b], acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[a], blo[b], acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[a], bhi[b], acc[a][b], 0, 0, 0);
-        }
-    }
-    }
-  };
   // FP32/FP64 k-steps of 4: lane holds element (row l % 16, k 4i + l / 16) of step i; its KQ
   // values of a slice are contiguous in the permuted rows, read 16 bytes at a time
   constexpr int EV = 16 / (int)sizeof(T);
@@ -803,21 +920,21 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
     }
     return f;
   };
-  // this wave's fragments of the slice in LDS stage `stage`: 4 tiles of A rows, 2 of Q rows
-  auto read_frags = [&](int stage, Frag (&fa)[4], Frag (&fb)[NB]) {
+  // this wave's fragments of the slice in LDS stage `stage`: MT tiles of A rows, NB of Q rows
+  auto read_frags = [&](int stage, Frag (&fa)[MT], Frag (&fb)[NB]) {
     T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
     T (*Bs)[BT * LDE] = stage_b(stage);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) fa[t] = frag(As[pa0][0] + (wm + t * 16 + r16) * LDE);
+    for (int t = 0; t < MT; ++t) fa[t] = frag(As[pa0][0] + (wm + t * 16 + r16) * LDE);
 #pragma unroll
     for (int t = 0; t < NB; ++t) fb[t] = frag(Bs[0] + (wn + t * 16 + r16) * LDE);
   };
-  auto mfma_frags = [&](const Frag (&fa)[4], const Frag (&fb)[NB]) {
+  auto mfma_frags = [&](const Frag (&fa)[MT], const Frag (&fb)[NB]) {
     if constexpr (PREC != PREC_BF16) {
 #pragma unroll
       for (int i = 0; i < KQ; ++i)
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < MT; ++a)
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             if constexpr (PREC == PREC_F64)
@@ -829,7 +946,93 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
           }
     }
   };
-  if constexpr (PREC != PREC_BF16) {
+  // split BF16: the hi/lo fragments of one 32-wide k-step ks of a slice (lane holds 8
+  // consecutive k of row l % 16, k offset 8 (l / 16)), and its three products: each accumulator
+  // takes lo*hi, hi*lo, hi*hi in that order; the accumulators are independent, so one kind of
+  // product is issued over all of them before the next
+  struct FragB {
+    bf16x8 ahi[MT], alo[MT], bhi[NB], blo[NB];
+  };
+  auto read_frags_bf = [&](int stage, int ks, FragB& f) {
+    T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
+    T (*Bs)[BT * LDE] = stage_b(stage);
+    const int kb = (lane >> 4) * 16 + ks * 64;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int ro = (wm + t * 16 + r16) * ROWB + kb;
+      f.ahi[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)As[pa0][0] + ro));
+      f.alo[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)As[pa0][NSPLIT - 1] + ro));
+    }
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const int ro = (wn + t * 16 + r16) * ROWB + kb;
+      f.bhi[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)Bs[0] + ro));
+      f.blo[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)Bs[NSPLIT - 1] + ro));
+    }
+  };
+  auto mfma_bf = [&](const FragB& f) {
+    if constexpr (PREC == PREC_BF16) {
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.alo[a], f.bhi[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.ahi[a], f.blo[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.ahi[a], f.bhi[b], acc[a][b], 0, 0, 0);
+    }
+  };
+  auto kslice = [&](int k) { return (k < KT ? k : KT - 1) * BK; };
+  if constexpr (PREC == PREC_BF16 && lds_stages<PREC, KX>() == 1) {
+    // wide slices: one in flight, its loads cover a whole MFMA phase of twice the length
+    Slice sl;
+    gload(sl, 0);
+    for (int kt = 0; kt < KT; ++kt) {
+      __syncthreads();
+      sstore(sl, 0);
+      __syncthreads();
+      if (kt + 1 < KT) gload(sl, (kt + 1) * BK);
+#pragma unroll
+      for (int ks = 0; ks < KX; ++ks) {
+        FragB f;
+        read_frags_bf(0, ks, f);
+        mfma_bf(f);
+      }
+    }
+  } else if constexpr (BT < 128) {
+    // small tiles: a pass is a few slices long and bound by the latency of its loads, so two
+    // slices' loads are in flight from the start
+    Slice s0, s1;
+    gload(s0, 0);
+    if (KT > 1) gload(s1, BK);
+    sstore(s0, 0);
+    __syncthreads();
+    auto step = [&](int kt, Slice& mine, Slice& next) {
+      if (kt + 2 < KT) gload(mine, (kt + 2) * BK);
+      if constexpr (PREC == PREC_BF16) {
+        FragB f;
+        read_frags_bf(kt & 1, 0, f);
+        mfma_bf(f);
+      } else {
+        Frag fa[MT], fb[NB];
+        read_frags(kt & 1, fa, fb);
+        mfma_frags(fa, fb);
+      }
+      if (kt + 1 < KT) sstore(next, (kt + 1) & 1);
+      __syncthreads();
+    };
+    for (int kt = 0; kt < KT; kt += 2) {
+      step(kt, s0, s1);
+      if (kt + 1 < KT) step(kt + 1, s1, s0);
+    }
+  } else {
     // Two LDS stages and two register sets of fragments.  Step kt issues the MFMAs of slice kt
     // from registers while the fragments of slice kt+1 are read from LDS, slice kt+2 is stored
     // into the stage slice kt came from (read into registers before the previous barrier) and
@@ -837,123 +1040,57 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
     // block (the slices past the end re-read the last one and are never used), so that its LDS
     // and global memory instructions can be issued one between each pair of MFMAs
     // (interleave_step): the memory work runs under the matrix cores instead of between them.
-    with_side([&](auto os) {
-      Frag fa0[4], fb0[NB], fa1[4], fb1[NB];
-      auto kslice = [&](int k) { return (k < KT ? k : KT - 1) * BK; };
-      gload(sl0, 0);
-      sstore(sl0, 0, os);
-      gload(sl0, kslice(1));
+    Slice sl;
+    auto run = [&](auto read, auto mfma, auto& f0, auto& f1, auto interleave) {
+      gload(sl, 0);
+      sstore(sl, 0);
+      gload(sl, kslice(1));
       __syncthreads();
-      read_frags(0, fa0, fb0);
-      sstore(sl0, 1, os);
-      gload(sl0, kslice(2));
+      read(0, f0);
+      sstore(sl, 1);
+      gload(sl, kslice(2));
       __syncthreads();
-      auto step = [&](int kt, const Frag (&ca)[4], const Frag (&cb)[NB], Frag (&na)[4],
-                      Frag (&nb)[NB]) {
-        read_frags((kt + 1) & 1, na, nb);
-        sstore(sl0, kt & 1, os);
-        gload(sl0, kslice(kt + 3));
-        mfma_frags(ca, cb);
-        constexpr int NM = KQ * 4 * NB, NR = 2 * (4 + NB);   // MFMAs, 16-byte fragment reads
-        interleave_step<NM, NR, (NM - NR < 24 ? NM - NR : 24)>();
+      auto step = [&](int kt, const auto& cur, auto& next) {
+        read((kt + 1) & 1, next);
+        sstore(sl, kt & 1);
+        gload(sl, kslice(kt + 3));
+        mfma(cur);
+        interleave();
         __syncthreads();
       };
       for (int kt = 0; kt < KT; kt += 2) {
-        step(kt, fa0, fb0, fa1, fb1);
-        if (kt + 1 < KT) step(kt + 1, fa1, fb1, fa0, fb0);
-      }
-    });
-  } else if constexpr (lds_stages<PREC, KX>() == 2) {
-    // split BF16, 32-wide slices in two LDS stages: the schedule of the FP32/FP64 passes, with
-    // the hi/lo fragments of a slice (one 32-wide k-step) double-buffered in registers
-    struct FragB {
-      bf16x8 ahi[4], alo[4], bhi[2], blo[2];
-    };
-    auto read_frags_bf = [&](int stage, FragB& f) {
-      T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
-      T (*Bs)[BT * LDE] = stage_b(stage);
-      const int kb = (lane >> 4) * 16;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int ro = (wm + t * 16 + r16) * ROWB + kb;
-        f.ahi[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)As[pa0][0] + ro));
-        f.alo[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)As[pa0][1] + ro));
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int ro = (wn + t * 16 + r16) * ROWB + kb;
-        f.bhi[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)Bs[0] + ro));
-        f.blo[t] = __builtin_bit_cast(bf16x8, *(const u32x4*)((const char*)Bs[1] + ro));
+        step(kt, f0, f1);
+        if (kt + 1 < KT) step(kt + 1, f1, f0);
       }
     };
-    // each accumulator takes lo*hi, hi*lo, hi*hi in that order; the eight accumulators are
-    // independent, so one kind of product is issued over all of them before the next
-    auto mfma_bf = [&](const FragB& f) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.alo[a], f.bhi[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.ahi[a], f.blo[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.ahi[a], f.bhi[b], acc[a][b], 0, 0, 0);
-    };
-    with_side([&](auto os) {
+    if constexpr (PREC == PREC_BF16) {
       FragB f0, f1;
-      auto kslice = [&](int k) { return (k < KT ? k : KT - 1) * BK; };
-      gload(sl0, 0);
-      sstore(sl0, 0, os);
-      gload(sl0, kslice(1));
-      __syncthreads();
-      read_frags_bf(0, f0);
-      sstore(sl0, 1, os);
-      gload(sl0, kslice(2));
-      __syncthreads();
-      auto step_bf = [&](int kt, const FragB& cur, FragB& next) {
-        read_frags_bf((kt + 1) & 1, next);
-        sstore(sl0, kt & 1, os);
-        gload(sl0, kslice(kt + 3));
-        mfma_bf(cur);
-        interleave_step<24, 12, 12>();
-        __syncthreads();
+      run([&](int st, FragB& f) { read_frags_bf(st, 0, f); }, [&](const FragB& f) { mfma_bf(f); },
+          f0, f1, [] { interleave_step<3 * MT * NB, 2 * (MT + NB), MT * NB * 3 - 2 * (MT + NB)>(); });
+    } else {
+      struct Fr {
+        Frag a[MT], b[NB];
       };
-      for (int kt = 0; kt < KT; kt += 2) {
-        step_bf(kt, f0, f1);
-        if (kt + 1 < KT) step_bf(kt + 1, f1, f0);
-      }
-    });
-  } else {
-    // wide slices: one in flight, its loads cover a whole MFMA phase of twice the length
-    with_side([&](auto os) {
-      gload(sl0, 0);
-      for (int kt = 0; kt < KT; ++kt) {
-        __syncthreads();
-        sstore(sl0, 0, os);
-        __syncthreads();
-        if (kt + 1 < KT) gload(sl0, (kt + 1) * BK);
-        mfma_slice(0);
-      }
-    });
+      Fr f0, f1;
+      constexpr int NM = KQ * MT * NB, NR = KQ / EV * (MT + NB);   // MFMAs, 16-byte reads
+      run([&](int st, Fr& f) { read_frags(st, f.a, f.b); },
+          [&](const Fr& f) { mfma_frags(f.a, f.b); }, f0, f1,
+          [] { interleave_step<NM, NR, (NM - NR < 24 ? NM - NR : 24)>(); });
+    }
   }
 
-  // epilogue: acc[a][b] holds C[i][j] for the 16 x 16 tile at local rows wm + 16a (A row
-  // a_row(.)), columns col0 + wn + 16b (column l%16 of lane l); the pass stores the transpose,
-  // out[j][i].  The tile goes through LDS (the A staging area) RJ output rows at a time, so that
-  // each thread then finishes and writes a contiguous run of ET elements of one output row (or,
-  // folding, EF mirrored pairs of one output row).
+  // epilogue: acc[a][b] holds the 16 x 16 tile at local rows wm + 16a, local columns wn + 16b
+  // (column l%16 of lane l).  Round a takes tile row a of every wave through LDS, 16 rows per
+  // wave row, the columns put back in their natural order; each thread then finishes and writes
+  // 16-byte chunks, consecutive threads consecutive chunks of a row.
   typedef typename std::conditional<PREC == PREC_F64, double, float>::type ST;
-  constexpr int RJ = PREC == PREC_F64 ? 16 : 32;              // output rows per round
+  constexpr int RW = BT / WM * 16;                            // output rows per round
   constexpr int SS = BT + 16 / (int)sizeof(ST);               // LDS row stride, 16-byte rows
-  constexpr int ET = RJ * BT / NTHR;                          // elements per thread: 4 to 16
-  static_assert(RJ * SS * sizeof(ST) <= sizeof(As[0]), "staging fits the A buffer");
-  ST* stg = reinterpret_cast<ST*>(&As[0][0][0]);
+  constexpr int EC = OUT == OUT_F32 ? 4 : 2;                  // elements per chunk
+  constexpr int CPR = BT / EC;                                // chunks per row
+  constexpr int NC = RW * CPR / NTHR;                         // chunks per thread and round
+  static_assert(RW * CPR % NTHR == 0, "whole chunks per thread");
+  ST* stg = reinterpret_cast<ST*>(pass_smem);
   double* out64 = nullptr;
   const double* base = nullptr;
   if constexpr (OUT == OUT_FINAL) {
@@ -963,152 +1100,63 @@ __global__ __launch_bounds__(pass_threads<WC>()) void k_pass2d(const Pass2D* __r
   // output row of accumulator element r: FP32 tiles hold rows 4(l/16) + r, FP64 tiles hold
   // rows (l/16) + 4r (measured lane layouts of the two instructions)
   const int i_base = PREC == PREC_F64 ? (lane >> 4) : 4 * (lane >> 4);
-  // folded output: thread's output row in a round and its first pair (pairs t, HB + t of the
-  // local rows, i.e. A rows row0 + t and n-1-row0-t, fold into element row0 + t of the planes)
-  constexpr int EF = RJ * HB / NTHR;                          // pairs per thread: 2 to 8
-  const int frow = tid / (HB / EF);
-  const int ft = (tid % (HB / EF)) * EF;
   constexpr int i_step = PREC == PREC_F64 ? 4 : 1;
-  const int j_l = lane & 15;
-  const int orow = tid / (BT / ET);                   // this thread's output row in a round
-  const int oc = (tid % (BT / ET)) * ET;              // and its first element
-  // the final update's FP64 operands (base, add) of this thread's run, loaded one round ahead
-  dbl2 bq[2][ET / 2];
-  typedef float flt2 __attribute__((ext_vector_type(2)));
-  flt2 aq[2][ET / 2];
-  auto fetch = [&](int jr, int slot) {
+  auto chunk_at = [&](int a, int c, int* lr, int* lc, int64_t* o) {
+    const int id = tid + c * NTHR;
+    *lr = id / CPR;
+    *lc = (id % CPR) * EC;
+    const int row = row0 + (*lr / 16) * WM + 16 * a + *lr % 16;
+    *o = (int64_t)row * n + col0 + *lc;
+    return row < n && col0 + *lc < n;                // n is a multiple of 32: whole chunks
+  };
+  // the final update's FP64 operands (base, add) of this thread's chunks, one round ahead
+  dbl2 bq[2][NC];
+  flt2 aq[2][NC];
+  auto fetch = [&](int a, int slot) {
     if constexpr (OUT == OUT_FINAL) {
-      const int jp = col0 + jr + orow;
-      const int i0 = row0 + oc;
-      if (jp >= n || i0 >= n) return;
-      const int j = FOLD ? (jp < half ? 2 * jp : 2 * (jp - half) + 1) : jp;
-      const int64_t o = (int64_t)j * n + i0;
 #pragma unroll
-      for (int e = 0; e < ET / 2; ++e) {
-        bq[slot][e] = gld<dbl2>(base + o + 2 * e);
-        aq[slot][e] = E.add ? gld<flt2>(E.add + o + 2 * e) : flt2{0.0f, 0.0f};
+      for (int c = 0; c < NC; ++c) {
+        int lr, lc;
+        int64_t o;
+        if (!chunk_at(a, c, &lr, &lc, &o)) continue;
+        bq[slot][c] = gld<dbl2>(base + o);
+        aq[slot][c] = PREC != PREC_F64 && E.add ? gld<flt2>(E.add + o) : flt2{0.0f, 0.0f};
       }
     }
   };
   fetch(0, 0);
-  for (int jr = 0; jr < BT; jr += RJ) {
-    const int cur = (jr / RJ) & 1;
+#pragma unroll
+  for (int a = 0; a < MT; ++a) {
     __syncthreads();                                  // the buffer is free
-    if (wn <= jr && jr < wn + WC) {                   // this wave holds rows jr .. jr + RJ
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int jl0 = wn + 16 * b;
-        if (jl0 < jr || jl0 >= jr + RJ) continue;
+    for (int b = 0; b < NB; ++b) {
+      const int c = wn + 16 * b + r16;
+      const int nat = FOLD ? (c < BT / 2 ? 2 * c : 2 * (c - BT / 2) + 1) : c;
+      ST* dst = stg + (wm / WM * 16 + i_base) * SS + nat;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          ST* dst = stg + (jl0 - jr + j_l) * SS + wm + 16 * a + i_base;
-          if constexpr (PREC == PREC_F64) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) dst[i_step * r] = acc[a][b][r];
-          } else {
-            // FP32 tiles hold 4 consecutive rows per lane: one 16-byte store (16-byte aligned:
-            // SS, wm, 16a and i_base are multiples of 4)
-            *(flt4*)dst = acc[a][b];
-          }
-        }
-      }
+      for (int r = 0; r < 4; ++r) dst[i_step * r * SS] = acc[a][b][r];
     }
     __syncthreads();
-    if (jr + RJ < BT) fetch(jr + RJ, cur ^ 1);
-    if constexpr (OUT == OUT_FOLD) {
-      // sums (side 0) and differences (side 1) of out[j][i] over mirrored i, in the precision
-      // the next pass would fold in: FP64, else the FP32 values it would have loaded (BF16:
-      // then split into hi, lo)
-      const int jp = col0 + jr + frow;
-      const int j = jp < half ? 2 * jp : 2 * (jp - half) + 1;
-      double x[EF], y[EF];
+    if (a + 1 < MT) fetch(a + 1, (a + 1) & 1);
 #pragma unroll
-      for (int e = 0; e < EF; ++e) {
-        x[e] = (double)stg[frow * SS + ft + e];
-        y[e] = (double)stg[frow * SS + HB + ft + e];
-      }
-      if (E.divide) {
-        const double lj = gld<double>(E.lam + j);
-#pragma unroll
-        for (int e = 0; e < EF; ++e) {
-          x[e] = x[e] / (1.0 + (gld<double>(E.lam + row0 + ft + e) + lj));
-          y[e] = y[e] / (1.0 + (gld<double>(E.lam + n - 1 - row0 - ft - e) + lj));
-        }
-      }
-      T* Cp = (T*)E.C + (int64_t)j * K + row0 + ft;   // plane (0, 0); side s, split p at
-      if constexpr (PREC == PREC_F64) {                 // + (s * NSPLIT + p) * plane
-#pragma unroll
-        for (int e = 0; e < EF; e += 2) {
-          gst<dbl2>(Cp + e, dbl2{x[e] + y[e], x[e + 1] + y[e + 1]});
-          gst<dbl2>(Cp + plane + e, dbl2{x[e] - y[e], x[e + 1] - y[e + 1]});
-        }
+    for (int c = 0; c < NC; ++c) {
+      int lr, lc;
+      int64_t o;
+      if (!chunk_at(a, c, &lr, &lc, &o)) continue;
+      const ST* src = stg + lr * SS + lc;
+      if constexpr (OUT == OUT_F64) {
+        gst<dbl2>((double*)E.C + o, *(const dbl2*)src);
+      } else if constexpr (OUT == OUT_F32) {
+        gst<flt4>((float*)E.C + o, *(const flt4*)src);
       } else {
-#pragma unroll
-        for (int e = 0; e < EF; e += 4) {
-          flt4 su, di;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const float xf = (float)x[e + t], yf = (float)y[e + t];
-            su[t] = xf + yf;
-            di[t] = xf - yf;
-          }
-          if constexpr (PREC == PREC_F32) {
-            gst<flt4>(Cp + e, su);
-            gst<flt4>(Cp + plane + e, di);
-          } else {
-            typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-            uint2 hi, lo;
-            split4_bf16(su, &hi, &lo);
-            gst<u32x2>(Cp + e, __builtin_bit_cast(u32x2, hi));
-            gst<u32x2>(Cp + plane + e, __builtin_bit_cast(u32x2, lo));
-            split4_bf16(di, &hi, &lo);
-            gst<u32x2>(Cp + 2 * plane + e, __builtin_bit_cast(u32x2, hi));
-            gst<u32x2>(Cp + 3 * plane + e, __builtin_bit_cast(u32x2, lo));
-          }
+        const dbl2 bs = bq[a & 1][c];
+        if constexpr (PREC == PREC_F64) {
+          gst<dbl2>(out64 + o, dbl2{bs[0] + src[0], bs[1] + src[1]});
+        } else {
+          const flt2 ad = aq[a & 1][c];
+          gst<dbl2>(out64 + o, dbl2{bs[0] + ((double)ad[0] + (double)src[0]),
+                                    bs[1] + ((double)ad[1] + (double)src[1])});
         }
-      }
-      continue;
-    }
-    const int jp = col0 + jr + orow;                  // column of the block grid
-    const int i0 = row0 + oc;
-    if (jp >= n || i0 >= n) continue;                 // n is a multiple of 32: whole runs
-    const int j = FOLD ? (jp < half ? 2 * jp : 2 * (jp - half) + 1) : jp;
-    const int64_t o = (int64_t)j * n + i0;
-    double v[ET];
-    if constexpr (PREC == PREC_F64) {
-#pragma unroll
-      for (int e = 0; e < ET; e += 2) {
-        const dbl2 w = *(const dbl2*)(stg + orow * SS + oc + e);
-        v[e] = w[0];
-        v[e + 1] = w[1];
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < ET; e += 4) {
-        const flt4 w = *(const flt4*)(stg + orow * SS + oc + e);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[e + t] = (double)w[t];
-      }
-    }
-    if (E.divide) {
-      const double lj = gld<double>(E.lam + j);
-#pragma unroll
-      for (int e = 0; e < ET; ++e) v[e] = v[e] / (1.0 + (gld<double>(E.lam + i0 + e) + lj));
-    }
-    if constexpr (OUT == OUT_F64) {
-#pragma unroll
-      for (int e = 0; e < ET; e += 2) gst<dbl2>((double*)E.C + o + e, dbl2{v[e], v[e + 1]});
-    } else if constexpr (OUT == OUT_F32) {
-#pragma unroll
-      for (int e = 0; e < ET; e += 4)
-        gst<flt4>((float*)E.C + o + e,
-                  flt4{(float)v[e], (float)v[e + 1], (float)v[e + 2], (float)v[e + 3]});
-    } else {
-#pragma unroll
-      for (int e = 0; e < ET; e += 2) {
-        const dbl2 bs = bq[cur][e / 2];
-        const dbl2 ad = dbl2{(double)aq[cur][e / 2][0], (double)aq[cur][e / 2][1]};
-        gst<dbl2>(out64 + o + e, dbl2{bs[0] + (ad[0] + v[e]), bs[1] + (ad[1] + v[e + 1])});
       }
     }
   }
@@ -1220,102 +1268,81 @@ bool wide_waves(int64_t n, int tile) {
   return PREC != PREC_BF16 && (tile & kPassWide64) && (!folded(n) || n % 128 == 0);
 }
 
-// Prefolded operands: when n/2 is a multiple of the block tile (every block's output columns
-// lie on one side of n/2) the passes exchange their intermediates as folded planes, written by
-// the previous pass's epilogue, unless tile bit kPassPlainA asks for row-major intermediates
-// folded while staging.  Both give bitwise the same results.
-bool prefold(int64_t n, int tile) { return folded(n) && n % (2 * BT) == 0 && !(tile & kPassPlainA); }
+// Block tile of a pass over `cnt` levels of side n: the largest whose blocks cover about half
+// of the 256 compute units, so that a small grid is not left to a few of them.  The tile does
+// not change an output element's MFMA sequence, hence no bit of it.
+int block_tile(int64_t n, int cnt) {
+  auto blocks = [&](int64_t t) { return ((n + t - 1) / t) * ((n + t - 1) / t) * cnt; };
+  if (blocks(128) >= 128) return 128;
+  return blocks(64) >= 128 ? 64 : 32;
+}
 
-// One transform pass.  AIN: the A operand is prefolded planes (1) or row-major (0); OUT_FOLD
-// writes prefolded planes for the next pass.
-template <int PREC, int OUT, int AIN>
-void launch_pass(const Pass2D* d, const Lvl2D* lv, int count, int64_t nmax, int64_t sigma,
-                 int tile, hipStream_t st) {
-  const unsigned t = (unsigned)((nmax + BT - 1) / BT);
-  const dim3 grid(t, t, count);
-  if constexpr (AIN == 1) {
-    const size_t planes = pass_lds_bytes<PREC, 1, 1>(1);
+// One transform pass.
+template <int PREC, int OUT>
+void launch_pass(const Pass2D* d, const Lvl2D* lv, int count, int64_t n, int64_t sigma, int tile,
+                 hipStream_t st) {
+  auto go = [&](auto kern, int bt, unsigned threads, size_t lds) {
+    const unsigned t = (unsigned)((n + bt - 1) / bt);
+    hipLaunchKernelGGL(kern, dim3(t, t, count), dim3(threads), lds, st, d, lv, sigma);
+  };
+  const int bt = block_tile(n, count);
+  const bool fold = folded(n);
+  if (bt == 128) {
+    constexpr size_t full = pass_lds_bytes<PREC, 1, 128>(0), half = pass_lds_bytes<PREC, 1, 128>(1);
     if constexpr (PREC != PREC_BF16) {
-      if (tile & kPassWide64) {
-        hipLaunchKernelGGL((k_pass2d<PREC, OUT, 1, 1, 64, 1>), grid, dim3(pass_threads<64>()),
-                           planes, st, d, lv, sigma);
+      if (wide_waves<PREC>(n, tile)) {
+        if (fold) go(k_pass2d<PREC, OUT, 1, 1, 128, 64>, 128, pass_threads<128, 64>(), half);
+        else go(k_pass2d<PREC, OUT, 0, 1, 128, 64>, 128, pass_threads<128, 64>(), full);
         return;
       }
+    } else if (wide_slices<PREC>(n) && !(tile & kPassNarrowK)) {
+      go(k_pass2d<PREC, OUT, 1, 2, 128, 32>, 128, pass_threads<128, 32>(),
+         pass_lds_bytes<PREC, 2, 128>(1));
+      return;
     }
-    hipLaunchKernelGGL((k_pass2d<PREC, OUT, 1, 1, 32, 1>), grid, dim3(pass_threads<32>()), planes,
-                       st, d, lv, sigma);
+    if (fold) go(k_pass2d<PREC, OUT, 1, 1, 128, 32>, 128, pass_threads<128, 32>(), half);
+    else go(k_pass2d<PREC, OUT, 0, 1, 128, 32>, 128, pass_threads<128, 32>(), full);
+  } else if (bt == 64) {
+    if (fold) go(k_pass2d<PREC, OUT, 1, 1, 64, 32>, 64, pass_threads<64, 32>(), pass_lds_bytes<PREC, 1, 64>(1));
+    else go(k_pass2d<PREC, OUT, 0, 1, 64, 32>, 64, pass_threads<64, 32>(), pass_lds_bytes<PREC, 1, 64>(0));
   } else {
-    const size_t full = pass_lds_bytes<PREC, 1, 0>(0), fold = pass_lds_bytes<PREC, 1, 0>(1);
-    const size_t wide = pass_lds_bytes<PREC, 2, 0>(1);
-    if constexpr (PREC != PREC_BF16) {
-      if (wide_waves<PREC>(nmax, tile)) {
-        if constexpr (OUT != OUT_FOLD)
-          if (!folded(nmax)) {
-            hipLaunchKernelGGL((k_pass2d<PREC, OUT, 0, 1, 64, 0>), grid, dim3(pass_threads<64>()),
-                               full, st, d, lv, sigma);
-            return;
-          }
-        hipLaunchKernelGGL((k_pass2d<PREC, OUT, 1, 1, 64, 0>), grid, dim3(pass_threads<64>()),
-                           fold, st, d, lv, sigma);
-        return;
-      }
-    }
-    if constexpr (OUT != OUT_FOLD)
-      if (!folded(nmax)) {
-        hipLaunchKernelGGL((k_pass2d<PREC, OUT, 0, 1, 32, 0>), grid, dim3(pass_threads<32>()),
-                           full, st, d, lv, sigma);
-        return;
-      }
-    if (!wide_slices<PREC>(nmax) || (tile & kPassNarrowK)) {
-      hipLaunchKernelGGL((k_pass2d<PREC, OUT, 1, 1, 32, 0>), grid, dim3(pass_threads<32>()), fold,
-                         st, d, lv, sigma);
-    } else {
-      if constexpr (PREC == PREC_BF16)
-        hipLaunchKernelGGL((k_pass2d<PREC, OUT, 1, 2, 32, 0>), grid, dim3(pass_threads<32>()),
-                           wide, st, d, lv, sigma);
-    }
+    if (fold) go(k_pass2d<PREC, OUT, 1, 1, 32, 16>, 32, pass_threads<32, 16>(), pass_lds_bytes<PREC, 1, 32>(1));
+    else go(k_pass2d<PREC, OUT, 0, 1, 32, 16>, 32, pass_threads<32, 16>(), pass_lds_bytes<PREC, 1, 32>(0));
   }
 }
 
-// Allow a pass variant its LDS (host call, outside any stream capture).
-template <int PREC, int OUT, int FOLD, int KX, int WC, int AIN>
-hipError_t allow_one() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass2d<PREC, OUT, FOLD, KX, WC, AIN>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)pass_lds_bytes<PREC, KX, AIN>(FOLD));
-}
-// every variant launch_pass<PREC, OUT, AIN> can launch
-template <int PREC, int OUT, int AIN>
+// Allow every variant launch_pass<PREC, OUT> can launch its LDS (host call, outside any stream
+// capture).
+template <int PREC, int OUT>
 hipError_t allow_lds() {
   hipError_t e = hipSuccess;
-  auto add = [&](hipError_t r) {
-    if (e == hipSuccess) e = r;
+  auto add = [&](auto kern, size_t lds) {
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   };
-  if constexpr (AIN == 1) {
-    add(allow_one<PREC, OUT, 1, 1, 32, 1>());
-    if constexpr (PREC != PREC_BF16) add(allow_one<PREC, OUT, 1, 1, 64, 1>());
+  add(&k_pass2d<PREC, OUT, 0, 1, 128, 32>, pass_lds_bytes<PREC, 1, 128>(0));
+  add(&k_pass2d<PREC, OUT, 1, 1, 128, 32>, pass_lds_bytes<PREC, 1, 128>(1));
+  add(&k_pass2d<PREC, OUT, 0, 1, 64, 32>, pass_lds_bytes<PREC, 1, 64>(0));
+  add(&k_pass2d<PREC, OUT, 1, 1, 64, 32>, pass_lds_bytes<PREC, 1, 64>(1));
+  add(&k_pass2d<PREC, OUT, 0, 1, 32, 16>, pass_lds_bytes<PREC, 1, 32>(0));
+  add(&k_pass2d<PREC, OUT, 1, 1, 32, 16>, pass_lds_bytes<PREC, 1, 32>(1));
+  if constexpr (PREC == PREC_BF16) {
+    add(&k_pass2d<PREC, OUT, 1, 2, 128, 32>, pass_lds_bytes<PREC, 2, 128>(1));
   } else {
-    if constexpr (OUT != OUT_FOLD) add(allow_one<PREC, OUT, 0, 1, 32, 0>());
-    add(allow_one<PREC, OUT, 1, 1, 32, 0>());
-    if constexpr (PREC == PREC_BF16) {
-      add(allow_one<PREC, OUT, 1, 2, 32, 0>());
-    } else {
-      if constexpr (OUT != OUT_FOLD) add(allow_one<PREC, OUT, 0, 1, 64, 0>());
-      add(allow_one<PREC, OUT, 1, 1, 64, 0>());
-    }
+    add(&k_pass2d<PREC, OUT, 0, 1, 128, 64>, pass_lds_bytes<PREC, 1, 128>(0));
+    add(&k_pass2d<PREC, OUT, 1, 1, 128, 64>, pass_lds_bytes<PREC, 1, 128>(1));
   }
   return e;
 }
 template <int PREC>
 hipError_t allow_pass() {
-  constexpr int OWN = PREC == PREC_F64 ? OUT_F64 : OUT_F32;
-  hipError_t e = allow_lds<PREC, OWN, 0>();
-  if (e == hipSuccess) e = allow_lds<PREC, OUT_FINAL, 0>();
-  if (e == hipSuccess) e = allow_lds<PREC, OUT_FOLD, 0>();
-  if (e == hipSuccess) e = allow_lds<PREC, OUT_FOLD, 1>();
-  if (e == hipSuccess) e = allow_lds<PREC, OUT_FINAL, 1>();
-  if constexpr (PREC != PREC_F64)
-    if (e == hipSuccess) e = allow_lds<PREC, OUT_F32, 1>();
+  typedef typename std::conditional<PREC == PREC_F64, double, float>::type T;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lines2d_long<T>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     2 * (16384 / 32) * LS_COLS * (int)sizeof(double));
+  if (e == hipSuccess) e = allow_lds<PREC, PREC == PREC_F64 ? OUT_F64 : OUT_F32>();
+  if (e == hipSuccess) e = allow_lds<PREC, OUT_FINAL>();
   return e;
 }
 
@@ -1324,6 +1351,9 @@ hipError_t prepare_pass_kernels(int prec) {
          : prec == PREC_F32 ? allow_pass<PREC_F32>()
                             : allow_pass<PREC_F64>();
 }
+
+// transform passes of one step: two per solve, two solves on the refined paths
+int passes_of(int prec) { return prec == PREC_F64 ? 2 : 4; }
 
 }  // namespace
 
@@ -1338,9 +1368,8 @@ size_t plan2d_workspace_bytes(const ridc_problem* p) {
   const int prec = prec_of(p);
   size_t b = 0;
   b += align256(sizeof(Lvl2D) * P);
-  const int npass = prec == PREC_F64 ? 4 : 8;
-  b += align256(sizeof(Pass2D) * P * npass);
-  b += align256(sizeof(double) * (size_t)p->n);                     // lam
+  b += align256(sizeof(Pass2D) * P * passes_of(prec));
+  b += align256(3 * sizeof(double) * (size_t)p->n);                 // line-solve constants
   b += (size_t)P * align256(level_ws_bytes(p->n, prec));
   return b;
 }
@@ -1371,20 +1400,29 @@ int plan2d_create(const ridc_problem* p, double h, double* const* ring, const in
   char* cur = ws;
   pl->d_levels = (Lvl2D*)cur;
   cur += align256(sizeof(Lvl2D) * P);
-  pl->npass = pl->prec == PREC_F64 ? 4 : 8;
+  pl->npass = passes_of(pl->prec);
   pl->d_passes = (Pass2D*)cur;
   cur += align256(sizeof(Pass2D) * P * pl->npass);
-  pl->lam = (double*)cur;
-  cur += align256(sizeof(double) * n);
-  // lam_k = dt nu (4/h^2) sin^2(pi (k+1) / (2(n+1)))
+  pl->col = (double*)cur;
+  cur += align256(3 * sizeof(double) * n);
+  // line-solve constants of column k (k_lines2d), lam_k = dt nu (4/h^2) sin^2(pi (k+1) / (2(n+1)))
   {
-    std::vector<double> lam(n);
+    std::vector<double> col(3 * n);
     const long double pi = 3.141592653589793238462643383279502884L;
+    const long double r = (long double)p->dt * p->nu / ((long double)h * h);
     for (int64_t k = 0; k < n; ++k) {
       const long double s = std::sin(pi * (long double)(k + 1) / (2.0L * (n + 1)));
-      lam[k] = (double)((long double)p->dt * p->nu * 4.0L / ((long double)h * h) * s * s);
+      const long double d = 1.0L + 4.0L * r * s * s;                // 1 + lam_k
+      const long double g = 2.0L / (d + 2.0L * r + std::sqrt(d * (d + 4.0L * r)));
+      const long double lam = r * g;
+      // kappa = lambda (1 - lambda^2) / (1 - lambda^{2n+2})
+      col[k] = (double)lam;
+      col[n + k] = (double)g;
+      long double e = lam > 0.0L ? (2 * n + 2) * std::log(lam) : -100.0L;   // below e^-50: nothing
+      e = e < -50.0L ? 0.0L : std::exp(e);
+      col[2 * n + k] = (double)(lam * (1.0L - lam * lam) / (1.0L - e));
     }
-    RIDC_HIP_TRY(hipMemcpy(pl->lam, lam.data(), n * sizeof(double), hipMemcpyHostToDevice));
+    RIDC_HIP_TRY(hipMemcpy(pl->col, col.data(), col.size() * sizeof(double), hipMemcpyHostToDevice));
   }
   pl->levels.assign(P, Lvl2D{});
   const size_t lws = align256(level_ws_bytes(n, pl->prec));
@@ -1397,9 +1435,10 @@ int plan2d_create(const ridc_problem* p, double h, double* const* ring, const in
     L.b64 = (double*)lw;
     L.x64 = (double*)(lw + nn * sizeof(double));
     if (pl->prec != PREC_F64) {
-      L.lo0 = lw + 2 * nn * sizeof(double);
-      L.lo1 = lw + 2 * nn * sizeof(double) + nn * sizeof(float);
+      L.lo0 = (float*)(lw + 2 * nn * sizeof(double));
+      L.lo1 = L.lo0 + nn;
     }
+    L.col = pl->col;
     L.nt = 0;
     L.sigma0 = 0;
     L.n = (int32_t)n;
@@ -1423,23 +1462,17 @@ int plan2d_create(const ridc_problem* p, double h, double* const* ring, const in
     for (int k = 0; k < pl->npass; ++k) {
       Pass2D& E = pl->passes[k * P + j];
       E.level = j;
-      E.lam = pl->lam;
-      E.divide = (k % 4) == 1;
+      // even passes: the right-hand side or residual to its sine coefficients; odd ones back, to
+      // the level's new value or (first solve of a refined path) to x1, kept in FP32
       if (pl->prec == PREC_F64) {
         E.Q = pl->Q64;
-        const void* ins[4] = {L.b64, L.x64, L.b64, L.x64};
-        void* outs[4] = {L.x64, L.b64, L.x64, nullptr};
-        E.A = ins[k];
-        E.C = outs[k];
+        E.A = k == 0 ? L.b64 : L.x64;
+        E.C = k == 0 ? L.x64 : nullptr;
       } else {
         E.Q = pl->prec == PREC_F32 ? (const void*)pl->Q32 : (const void*)pl->Qbf;
-        const int kk = k % 4;
-        const void* ins[4] = {L.lo0, L.lo1, L.lo0, L.lo1};
-        void* outs[4] = {L.lo1, L.lo0, L.lo1, nullptr};
-        E.A = ins[kk];
-        E.C = outs[kk];
-        if (k == 3) E.C = L.x64;             // first solve, kept in FP32 in this buffer
-        if (k == 7) E.add = (const float*)L.x64;   // x = x1 + S~(rho)
+        E.A = k % 2 == 0 ? L.lo0 : L.lo1;
+        E.C = k % 2 == 0 ? (void*)L.lo1 : k == 1 ? (void*)L.x64 : nullptr;
+        if (k == 3) E.add = (const float*)L.x64;   // x = x1 + S~(rho)
       }
     }
   }
@@ -1464,16 +1497,13 @@ void plan2d_tile_candidates(const Plan2D* pl, std::vector<int>* out) {
   out->push_back(0);
   if (pl->prec != PREC_BF16 && (!folded(pl->n) || pl->n % 128 == 0)) out->push_back(kPassWide64);
   if (pl->prec == PREC_BF16 && wide_slices<PREC_BF16>(pl->n)) out->push_back(kPassNarrowK);
-  if (prefold(pl->n, 0)) {
-    const size_t c = out->size();
-    for (size_t i = 0; i < c; ++i) out->push_back((*out)[i] | kPassPlainA);
-  }
 }
 
 int plan2d_set_tile(Plan2D* pl, int tile) {
   std::vector<int> c;
   plan2d_tile_candidates(pl, &c);
-  if (std::find(c.begin(), c.end(), tile) == c.end())
+  const int shape = pl->n % 256 == 0 ? tile & ~kPassPlainA : tile;
+  if (std::find(c.begin(), c.end(), shape) == c.end())
     return fail(RIDC_E_INVAL, "launch shape not available for this side and precision");
   pl->tile = tile;
   return RIDC_OK;
@@ -1491,41 +1521,34 @@ int plan2d_arm(Plan2D* pl, int64_t nt, hipStream_t stream) {
 
 namespace {
 
-// The four passes of one solve (passes d[0 .. 3 cnt)): the last writes LAST.  With prefolded
-// operands the first three write folded planes and the later three read them.
+// One solve (passes d[0], d[cnt]): to sine coefficients along the rows, line solves down the
+// columns, and back; the last pass writes LAST.
 template <int PREC, int LAST>
-void run_solve(const Lvl2D* lv, const Pass2D* d, int cnt, int64_t nmax, int64_t s, int tile,
+void run_solve(const Lvl2D* lv, const Pass2D* d, int cnt, int64_t n, int64_t s, int tile,
                hipStream_t st) {
   constexpr int OWN = PREC == PREC_F64 ? OUT_F64 : OUT_F32;
-  if (prefold(nmax, tile)) {
-    launch_pass<PREC, OUT_FOLD, 0>(d + 0 * cnt, lv, cnt, nmax, s, tile, st);
-    launch_pass<PREC, OUT_FOLD, 1>(d + 1 * cnt, lv, cnt, nmax, s, tile, st);
-    launch_pass<PREC, OUT_FOLD, 1>(d + 2 * cnt, lv, cnt, nmax, s, tile, st);
-    launch_pass<PREC, LAST, 1>(d + 3 * cnt, lv, cnt, nmax, s, tile, st);
-  } else {
-    launch_pass<PREC, OWN, 0>(d + 0 * cnt, lv, cnt, nmax, s, tile, st);
-    launch_pass<PREC, OWN, 0>(d + 1 * cnt, lv, cnt, nmax, s, tile, st);
-    launch_pass<PREC, OWN, 0>(d + 2 * cnt, lv, cnt, nmax, s, tile, st);
-    launch_pass<PREC, LAST, 0>(d + 3 * cnt, lv, cnt, nmax, s, tile, st);
-  }
+  typedef typename std::conditional<PREC == PREC_F64, double, float>::type T;
+  launch_pass<PREC, OWN>(d, lv, cnt, n, s, tile, st);
+  launch_lines<T>(lv, cnt, n, s, st);
+  launch_pass<PREC, LAST>(d + cnt, lv, cnt, n, s, tile, st);
 }
 
 // Every stage of one pipeline step for `cnt` (plan, level) entries of one precision: the
-// right-hand side, the transform passes and (reduced precision) the residual, one launch each.
+// right-hand side, the solve and (reduced precision) the residual and a second solve.
 // passes is pass-major: passes[k * cnt + e].
-void run_stages(int prec, const Lvl2D* lv, const Pass2D* d, int cnt, int64_t nmax, int64_t s,
+void run_stages(int prec, const Lvl2D* lv, const Pass2D* d, int cnt, int64_t n, int64_t s,
                 int tile, hipStream_t st) {
-  launch_stencil(k_rhs2d, lv, cnt, nmax, s, st);
+  launch_rhs(lv, cnt, n, s, st);
   if (prec == PREC_F64) {
-    run_solve<PREC_F64, OUT_FINAL>(lv, d, cnt, nmax, s, tile, st);
+    run_solve<PREC_F64, OUT_FINAL>(lv, d, cnt, n, s, tile, st);
   } else if (prec == PREC_F32) {
-    run_solve<PREC_F32, OUT_F32>(lv, d, cnt, nmax, s, tile, st);
-    launch_stencil(k_resid2d, lv, cnt, nmax, s, st);
-    run_solve<PREC_F32, OUT_FINAL>(lv, d + 4 * cnt, cnt, nmax, s, tile, st);
+    run_solve<PREC_F32, OUT_F32>(lv, d, cnt, n, s, tile, st);
+    launch_resid(lv, cnt, n, s, st);
+    run_solve<PREC_F32, OUT_FINAL>(lv, d + 2 * cnt, cnt, n, s, tile, st);
   } else {
-    run_solve<PREC_BF16, OUT_F32>(lv, d, cnt, nmax, s, tile, st);
-    launch_stencil(k_resid2d, lv, cnt, nmax, s, st);
-    run_solve<PREC_BF16, OUT_FINAL>(lv, d + 4 * cnt, cnt, nmax, s, tile, st);
+    run_solve<PREC_BF16, OUT_F32>(lv, d, cnt, n, s, tile, st);
+    launch_resid(lv, cnt, n, s, st);
+    run_solve<PREC_BF16, OUT_FINAL>(lv, d + 2 * cnt, cnt, n, s, tile, st);
   }
 }
 
@@ -1635,7 +1658,7 @@ int plan2d_advance(Plan2D* const* pls, int count, const int64_t* sigma_before, i
   size_t lo = 0, po = 0;
   for (auto& g : groups) {
     const int prec = g.first.first & 0xff;
-    const int npass = prec == PREC_F64 ? 4 : 8;
+    const int npass = passes_of(prec);
     int cnt = 0;
     for (int i : g.second) cnt += pls[i]->P;
     G gg{prec, cnt, g.first.second, lo, po, g.first.first >> 8};
@@ -1677,33 +1700,23 @@ int plan2d_time_pass(Plan2D* pl, int64_t sigma, int reps, hipStream_t stream, do
   const int P = pl->P;
   const int64_t n = pl->n;
   const int tile = pl->tile;
-  const bool pf = prefold(n, tile);
-  // inputs of the second pass of this step (the right-hand side and the first pass), then
-  // `reps` back-to-back launches of the second pass, which only rewrites an intermediate
-  launch_stencil(k_rhs2d, pl->d_levels, P, n, sigma, stream);
-  auto pass = [&](int k) {
-    const Pass2D* d = pl->d_passes + k * P;
-    if (pl->prec == PREC_F64) {
-      if (pf && k == 0) launch_pass<PREC_F64, OUT_FOLD, 0>(d, pl->d_levels, P, n, sigma, tile, stream);
-      else if (pf) launch_pass<PREC_F64, OUT_FOLD, 1>(d, pl->d_levels, P, n, sigma, tile, stream);
-      else launch_pass<PREC_F64, OUT_F64, 0>(d, pl->d_levels, P, n, sigma, tile, stream);
-    } else if (pl->prec == PREC_F32) {
-      if (pf && k == 0) launch_pass<PREC_F32, OUT_FOLD, 0>(d, pl->d_levels, P, n, sigma, tile, stream);
-      else if (pf) launch_pass<PREC_F32, OUT_FOLD, 1>(d, pl->d_levels, P, n, sigma, tile, stream);
-      else launch_pass<PREC_F32, OUT_F32, 0>(d, pl->d_levels, P, n, sigma, tile, stream);
-    } else {
-      if (pf && k == 0) launch_pass<PREC_BF16, OUT_FOLD, 0>(d, pl->d_levels, P, n, sigma, tile, stream);
-      else if (pf) launch_pass<PREC_BF16, OUT_FOLD, 1>(d, pl->d_levels, P, n, sigma, tile, stream);
-      else launch_pass<PREC_BF16, OUT_F32, 0>(d, pl->d_levels, P, n, sigma, tile, stream);
-    }
+  // the right-hand side of this step, then `reps` back-to-back launches of its first pass, which
+  // rewrite the sine coefficients only
+  launch_rhs(pl->d_levels, P, n, sigma, stream);
+  auto pass = [&] {
+    if (pl->prec == PREC_F64)
+      launch_pass<PREC_F64, OUT_F64>(pl->d_passes, pl->d_levels, P, n, sigma, tile, stream);
+    else if (pl->prec == PREC_F32)
+      launch_pass<PREC_F32, OUT_F32>(pl->d_passes, pl->d_levels, P, n, sigma, tile, stream);
+    else
+      launch_pass<PREC_BF16, OUT_F32>(pl->d_passes, pl->d_levels, P, n, sigma, tile, stream);
   };
-  pass(0);
   hipEvent_t a, b;
   RIDC_HIP_TRY(hipEventCreate(&a));
   RIDC_HIP_TRY(hipEventCreate(&b));
-  pass(1);
+  pass();
   (void)hipEventRecord(a, stream);
-  for (int r = 0; r < reps; ++r) pass(1);
+  for (int r = 0; r < reps; ++r) pass();
   (void)hipEventRecord(b, stream);
   hipError_t e = hipEventSynchronize(b);
   float ms = 0;
@@ -1720,13 +1733,13 @@ int plan2d_time_rhs(Plan2D* pl, int64_t sigma, int reps, hipStream_t stream, dou
   const int P = pl->P;
   const int64_t n = pl->n;
   // the right-hand side of this step, launched repeatedly (it rewrites the same values)
-  launch_stencil(k_rhs2d, pl->d_levels, P, n, sigma, stream);
+  launch_rhs(pl->d_levels, P, n, sigma, stream);
   hipEvent_t a, b;
   RIDC_HIP_TRY(hipEventCreate(&a));
   RIDC_HIP_TRY(hipEventCreate(&b));
   (void)hipEventRecord(a, stream);
   for (int r = 0; r < reps; ++r)
-    launch_stencil(k_rhs2d, pl->d_levels, P, n, sigma, stream);
+    launch_rhs(pl->d_levels, P, n, sigma, stream);
   (void)hipEventRecord(b, stream);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipEventSynchronize(b);
@@ -1748,11 +1761,8 @@ int plan2d_time_rhs(Plan2D* pl, int64_t sigma, int reps, hipStream_t stream, dou
 
 void plan2d_cost(const Plan2D* pl, double* bytes, double* flops) {
   const double n = (double)pl->n;
-  const int passes = pl->prec == PREC_F64 ? 4 : 8;
-  const double products = pl->prec == PREC_BF16 ? 3.0 : 1.0;
-  // algorithmic flops of the transforms at steady state: P level solves of 4 (or 8) n^3 GEMMs
-  *flops = 2.0 * n * n * n * passes * pl->P;
-  (void)products;
+  // algorithmic flops of the transforms at steady state: P level solves of 2 (or 4) n^3 GEMMs
+  *flops = 2.0 * n * n * n * passes_of(pl->prec) * pl->P;
   (void)bytes;
 }
 

@@ -97,6 +97,45 @@ def test_mixed_precision_parity(env, prec, n, nt):
         assert err <= tol_of(prec, j) and emax <= tol_of(prec, j), (j, err, emax)
 
 
+# the line solves: one segment row count per range of n (8 rows up to n = 512, 16 up to 1024, 32 up
+# to 2048, the two-walk kernel above), at the smallest side, at the edges of the ranges and with
+# segment counts that are not powers of two; nu = 1 makes r = dt nu / h^2 up to 8.7e3, so that a
+# carry reaches across the whole column, nu = 0 leaves no coupling at all.  Bars: TOL64 and TOL (the
+# latter was derived for nu <= 1e-3).
+@pytest.mark.parametrize("n,nu,prec", [(32, 1.0, "fp64"), (96, 0.0, "fp64"), (512, 1.0, "fp64"),
+                                       (544, 1e-3, "fp64"), (544, 1e-3, "bf16x3"),
+                                       (1024, 1.0, "fp64"), (1056, 1.0, "fp64"),
+                                       (2080, 1.0, "fp64"), (2080, 1e-3, "fp32")])
+def test_line_solves_over_their_ranges(env, n, nu, prec):
+    prob, u0 = workloads.config_reacdiff_2d(n=n, nt=2, order=2, T=4e-3, nu=nu)
+    _say(f"case: 2D {prec} line solves n={n} nu={nu}")
+    ref = oracle2d(prob, u0)
+    top, lvs = run2d(env, prob, u0, prec=prec)
+    for j in range(2):
+        err, emax = errs(lvs[j], ref[j])
+        _say(f"  level {j}: rel L2 {err:.3e}, max {emax:.3e}")
+        assert err <= tol_of(prec, j) and emax <= tol_of(prec, j), (j, err, emax)
+
+
+# the block tile of a pass follows the number of blocks it gives (n and the levels in a launch):
+# alone and in a group a handle may take different tiles, and must keep its bits
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+def test_block_tiles_are_bitwise_equal(env, prec):
+    torch, ridc = env
+    prob, u0 = workloads.config_reacdiff_2d(n=384, nt=4, order=1, T=8e-3, nu=1e-3)
+    x0 = torch.tensor(u0.reshape(-1), dtype=torch.float64, device="cuda")
+    for count in (4, 15):          # 9 blocks of 128 x 128 per level: 32-, 64- and 128-tiles
+        solvers = [ridc.Ridc(prob, prec=prec) for _ in range(count)]
+        uTs = [torch.empty_like(x0) for _ in range(count)]
+        alone = solvers[0].integrate(x0, prob["nt"]).cpu().numpy()
+        ridc.integrate_batch(solvers, [x0] * count, [prob["nt"]] * count, uTs)
+        torch.cuda.synchronize()
+        for u in uTs:
+            np.testing.assert_array_equal(u.cpu().numpy(), alone)
+        for s in solvers:
+            s.close()
+
+
 @pytest.mark.parametrize("prec", ["fp64", "bf16x3"])
 def test_kernel_time_leaves_the_integration_unchanged(env, prec):
     """ridc_kernel_time runs the next step's stages again and again around its timed pass; the
