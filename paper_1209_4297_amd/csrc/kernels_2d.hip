@@ -418,14 +418,15 @@ static void launch_resid(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, 
 //
 // A thread holds M consecutive rows of one column (a segment) in registers and runs both
 // recurrences over them from zero; two numbers per segment (its last value going down and its
-// first value coming back up) go through LDS, every thread chains them over the column's
-// segments, and the recurrences run again from the true carries.  A block is 16 columns (128
+// first value coming back up) go through LDS, a wave chains them over a column's
+// segments (line_chain), and the recurrences run again from the true carries.  A block is 16 columns (128
 // bytes of a row, a cache line in FP64) of the whole height: 64 segments of M = 16 rows at
 // n = 1024, one block per compute unit for four levels.  Bound: HBM, one read and one write of
 // each vector; the arithmetic is FP64 also where the coefficients are stored in FP32.
 // ---------------------------------------------------------------------------------------------
 constexpr int LS_COLS = 16;   // columns per block
 constexpr int LS_SEGS = 64;   // segments in registers at a time
+constexpr int LS_STRIDE = LS_COLS + 1;   // LDS row of a segment's values over the columns
 
 // Blocks go to the 8 XCDs round-robin by linear id; each XCD takes a contiguous run of column
 // blocks, so that two blocks sharing a 128-byte line (FP32 columns) share its L2.
@@ -476,11 +477,76 @@ __device__ __forceinline__ void line_powers(double lam, double* P, double* G) {
   *G = g;
 }
 
+// The value of lane l - N or l + N of the same row of 16 lanes, 0 past the row's end.
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Chain the segments of a column over the lanes of a wave: lane s holds t and h of segment s (t,
+// h and G zero past the last), and leaves with its carries (the downward value before, the upward value after
+// the segment).  The two recurrences over the lanes are scans with the weights P, P^2, P^4, P^8
+// inside the rows of 16 lanes; WIDE carries them from row to row (one column of up to 64 segments
+// per wave), otherwise each row is a column of its own.
+template <bool WIDE>
+__device__ __forceinline__ void line_chain(int lane, double P, double G, double kappa, double* t,
+                                           double* h) {
+  const int r = lane & 15;
+  const double P2 = P * P, P4 = P2 * P2, P8 = P4 * P4, P16 = P8 * P8;
+  const double up = (r & 1 ? P : 1.0) * (r & 2 ? P2 : 1.0) * ((r & 4 ? P4 : 1.0) * (r & 8 ? P8 : 1.0));
+  const int q = 15 - r;
+  const double dn = (q & 1 ? P : 1.0) * (q & 2 ? P2 : 1.0) * ((q & 4 ? P4 : 1.0) * (q & 8 ? P8 : 1.0));
+  // sum_{k <= s} P^(s-k) t_k, then the carry before each segment (c_0 = 0)
+  double c = *t;
+  c = __builtin_fma(P, row_move<0x111>(c), c);
+  c = __builtin_fma(P2, row_move<0x112>(c), c);
+  c = __builtin_fma(P4, row_move<0x114>(c), c);
+  c = __builtin_fma(P8, row_move<0x118>(c), c);
+  double first = 1.0;                                // P^s
+  if constexpr (WIDE) {
+    const double c1 = lane_value(c, 15), c2 = __builtin_fma(P16, c1, lane_value(c, 31));
+    const double c3 = __builtin_fma(P16, c2, lane_value(c, 47));
+    const double cr = lane < 16 ? 0.0 : (lane < 32 ? c1 : (lane < 48 ? c2 : c3));
+    c = __builtin_fma(up * P, cr, c);
+    c = lane_below(c);
+    first = up * (lane < 16 ? 1.0 : (lane < 32 ? P16 : (lane < 48 ? P16 * P16 : P16 * P16 * P16)));
+  } else {
+    c = row_move<0x111>(c);
+    first = up;
+  }
+  // sum_{k >= s} P^(k-s) x_k
+  auto sums_above = [&](double x) {
+    x = __builtin_fma(P, row_move<0x101>(x), x);
+    x = __builtin_fma(P2, row_move<0x102>(x), x);
+    x = __builtin_fma(P4, row_move<0x104>(x), x);
+    x = __builtin_fma(P8, row_move<0x108>(x), x);
+    if constexpr (WIDE) {
+      const double d2 = lane_value(x, 48), d1 = __builtin_fma(P16, d2, lane_value(x, 32));
+      const double d0 = __builtin_fma(P16, d1, lane_value(x, 16));
+      const double dr = lane < 16 ? d0 : (lane < 32 ? d1 : (lane < 48 ? d2 : 0.0));
+      x = __builtin_fma(dn * P, dr, x);
+    }
+    return x;
+  };
+  const double z = sums_above(__builtin_fma(c, G, *h));
+  const double z0 = WIDE ? lane_value(z, 0) : __shfl(z, lane & 48, 64);
+  c = __builtin_fma(-kappa * z0, first, c);
+  const double v = sums_above(__builtin_fma(c, G, *h));
+  *t = c;
+  *h = WIDE ? lane_above(v) : row_move<0x101>(v);
+}
+
 // ns = blockDim.x / 16 segments of M rows: n = ns M.
 template <typename T, int M>
 __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d(const Lvl2D* __restrict__ levels,
                                                                int64_t sigma) {
-  __shared__ double ex[2][LS_SEGS * LS_COLS];
+  __shared__ double ex[2][LS_SEGS * LS_STRIDE], pw[3][LS_COLS];
   const unsigned q = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
   const Lvl2D& L = levels[q / gridDim.x];
   int64_t m;
@@ -498,28 +564,45 @@ __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d(const Lvl2D* __re
   double t, h, P, G;
   line_down<M>(lam, v, &t, &h);
   line_powers<M>(lam, &P, &G);
-  ex[0][threadIdx.x] = t;
-  ex[1][threadIdx.x] = h;
+  ex[0][seg * LS_STRIDE + cl] = t;
+  ex[1][seg * LS_STRIDE + cl] = h;
+  if (seg == 0) {
+    pw[0][cl] = P;
+    pw[1][cl] = G;
+    pw[2][cl] = kappa;
+  }
   __syncthreads();
-  // first row with c_0 = 0, hence the true c_0; then this segment's carries
-  double c = 0.0, z = 0.0, w = 1.0, mine = 0.0;
-  for (int s = 0; s < ns; ++s) {
-    z = __builtin_fma(w, __builtin_fma(c, G, ex[1][s * LS_COLS + cl]), z);
-    c = __builtin_fma(P, c, ex[0][s * LS_COLS + cl]);
-    w *= P;
-  }
-  c = -kappa * z;
-  z = 0.0;
-  w = 1.0;
-  for (int s = 0; s < ns; ++s) {
-    if (s == seg) mine = c;
-    if (s > seg) {
-      z = __builtin_fma(w, __builtin_fma(c, G, ex[1][s * LS_COLS + cl]), z);
-      w *= P;
+  // the waves share the block's 16 columns: a column of more than 16 segments takes a wave's 64
+  // lanes, four shorter ones take its four rows of 16
+  {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    if (wave >= nw) {
+      // the last wave may be a part of one: it takes no column (its lanes cannot all move)
+    } else if (ns > 16) {
+      for (int cc = wave; cc < LS_COLS; cc += nw) {
+        const bool in = lane < ns;
+        double a = in ? ex[0][lane * LS_STRIDE + cc] : 0.0, b = in ? ex[1][lane * LS_STRIDE + cc] : 0.0;
+        line_chain<true>(lane, pw[0][cc], in ? pw[1][cc] : 0.0, pw[2][cc], &a, &b);
+        if (in) {
+          ex[0][lane * LS_STRIDE + cc] = a;
+          ex[1][lane * LS_STRIDE + cc] = b;
+        }
+      }
+    } else {
+      for (int c4 = wave; c4 < LS_COLS / 4; c4 += nw) {
+        const int cc = c4 * 4 + (lane >> 4), sg = lane & 15;
+        const bool in = sg < ns;
+        double a = in ? ex[0][sg * LS_STRIDE + cc] : 0.0, b = in ? ex[1][sg * LS_STRIDE + cc] : 0.0;
+        line_chain<false>(lane, pw[0][cc], in ? pw[1][cc] : 0.0, pw[2][cc], &a, &b);
+        if (in) {
+          ex[0][sg * LS_STRIDE + cc] = a;
+          ex[1][sg * LS_STRIDE + cc] = b;
+        }
+      }
     }
-    c = __builtin_fma(P, c, ex[0][s * LS_COLS + cl]);
   }
-  line_up<T, M>(lam, g, v, mine, z, col, n);
+  __syncthreads();
+  line_up<T, M>(lam, g, v, ex[0][seg * LS_STRIDE + cl], ex[1][seg * LS_STRIDE + cl], col, n);
 }
 
 // Columns of more than 64 segments of 32 rows (n > 2048): the block walks its columns 2048 rows
