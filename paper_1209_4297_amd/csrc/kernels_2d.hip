@@ -17,7 +17,7 @@
 // column j of T, (1 + dt nu mu_j) x - dt nu D2 x = T_j, and X is the solutions times Q.
 // Diagonalising the columns as well would take two more products by Q, the cost of a pass each
 // (75 us at 1024^2 over four levels in FP64); the line solves read and write each vector once
-// (k_lines2d, 20 us there, which took the step from 305 to 205 us).
+// (k_lines2d, 14 us there, which took the step from 305 to 200 us).
 // Each product by Q is one pass C = A Q, a GEMM on the matrix cores (v_mfma_f64_16x16x4f64,
 // v_mfma_f32_16x16x4_f32, or three v_mfma_f32_16x16x32_bf16 products of hi/lo BF16 splits),
 // batched over every active level of every instance in one launch; the final update is fused
@@ -65,13 +65,13 @@ struct Lvl2D {
   double dt, nu_h2;
 };
 
-// One batch entry of a transform pass.
+// One batch entry of a transform pass: entry e of a pass belongs to entry e of the level table (so
+// that a block reads both at once).
 struct Pass2D {
   const void* A;        // input: row-major n x n (FP64, or FP32 in the reduced-precision paths)
   void* C;              // output (unless final)
   const float* add;     // final epilogue: extra term (x1 of the refinement, FP32), nullable
   const void* Q;        // transform matrix in the input precision (BF16: hi, lo at +n*n)
-  int32_t level;        // index into the level table
 };
 
 struct Plan2D {
@@ -102,6 +102,13 @@ __device__ __forceinline__ bool level_active(const Lvl2D& L, int64_t sigma, int6
   const int64_t m = sigma - L.sigma0 - (int64_t)L.j * (L.j + 1) / 2;
   *m_out = m;
   return m >= 1 && m <= L.nt;
+}
+
+// m mod R.  A step's index fits 32 bits in all but the longest runs, and a 64-bit remainder is some
+// hundred dependent instructions at the head of every kernel.
+__device__ __forceinline__ int ring_slot(int64_t m, int R) {
+  if ((uint64_t)m >> 32 == 0) return (int)((uint32_t)m % (uint32_t)R);
+  return (int)(m % R);
 }
 
 __device__ __forceinline__ double fe2(int fe, double u) {
@@ -204,7 +211,7 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   const bool col = ix < n;
   const int64_t nn = (int64_t)n * n;
   const int64_t nidx = m - 1;
-  const double* __restrict__ u = L.own + (nidx % L.R_own) * nn;
+  const double* __restrict__ u = L.own + ring_slot(nidx, L.R_own) * nn;
   const int nv = JT < 0 ? L.j + 1 : JT;        // window vectors
   const double* __restrict__ vp[JN];
   double w[JN];
@@ -215,10 +222,12 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   } else {
     const int64_t s = m - L.j > 0 ? m - L.j : 0;
     rn = (int)(nidx - s);
+    int slot = ring_slot(s, L.R_prev);
 #pragma unroll
     for (int i = 0; i < JN; ++i) {
       if (i < nv) {
-        vp[i] = L.prev + ((s + i) % L.R_prev) * nn;
+        vp[i] = L.prev + slot * nn;
+        slot = slot + 1 == L.R_prev ? 0 : slot + 1;
         w[i] = gld<double>(L.W + (nidx - s) * (L.j + 1) + i);
       }
     }
@@ -273,7 +282,7 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   const double dt = L.dt;
   double up = load(iy0 - 1).V;
   RhsRow mid = load(iy0);
-  constexpr int RG = 2;
+  constexpr int RG = RY == 4 ? 4 : 2;      // short strips: every row at once
 #pragma unroll
   for (int q = 0; q < RY; q += RG) {
     double bs[RG];
@@ -841,7 +850,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
     bz = q / (t * gridDim.y);
   }
   const Pass2D& E = passes[bz];
-  const Lvl2D& L = levels[E.level];
+  const Lvl2D& L = levels[bz];
   int64_t m;
   if (!level_active(L, sigma, &m)) return;
   const int n = L.n;
@@ -917,26 +926,11 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
         S.rb[s][c] = gld<u32x4>(Q + s * qsplit + (int64_t)q_row(r) * K + ko);
       }
   };
-  // FP32/FP64 operand rows keep a k-slice permuted, k at (k % 4) * KQ + k / 4, so that the KQ
-  // values one lane consumes over the slice (k = 4i + lane/16) are contiguous; BF16 rows keep
-  // k in order (its instruction takes 8 consecutive k per lane).
+  // Rows keep a slice's k in order.  A lane of an FP32/FP64 fragment takes KQ consecutive k of its
+  // row, from KQ (l / 16), so that MFMA i of the slice multiplies k = i, KQ + i, 2 KQ + i, 3 KQ + i
+  // (the same for every shape) and rows are written and read 16 bytes at a time.
   constexpr int KQ = BK / 4;
-  auto put = [&](T* row_base, int q, u32x4 v) {
-    if constexpr (PREC == PREC_BF16) {
-      *(u32x4*)((char*)row_base + q * 16) = v;
-    } else {
-      constexpr int EV = 16 / (int)sizeof(T);
-      struct Ev {
-        T x[EV];
-      };
-      const Ev ev = __builtin_bit_cast(Ev, v);
-#pragma unroll
-      for (int e = 0; e < EV; ++e) {
-        const int k = q * EV + e;
-        row_base[(k & 3) * KQ + (k >> 2)] = ev.x[e];
-      }
-    }
-  };
+  auto put = [&](T* row_base, int q, u32x4 v) { *(u32x4*)((char*)row_base + q * 16) = v; };
   auto sstore = [&](const Slice& S, int stage) {
     T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
     T (*Bs)[BT * LDE] = stage_b(stage);
@@ -982,8 +976,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   const int pa0 = FOLD && wn >= BT / 2 ? 1 : 0;
   const int KT = K / BK;
   const int r16 = lane & 15;
-  // FP32/FP64 k-steps of 4: lane holds element (row l % 16, k 4i + l / 16) of step i; its KQ
-  // values of a slice are contiguous in the permuted rows, read 16 bytes at a time
+  // FP32/FP64: a lane's KQ values of a slice, read 16 bytes at a time
   constexpr int EV = 16 / (int)sizeof(T);
   struct Frag {
     T x[KQ];
@@ -1072,6 +1065,54 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.ahi[a], f.bhi[b], acc[a][b], 0, 0, 0);
     }
   };
+  // the epilogue's geometry: round a takes tile row a of every wave, 16 rows per wave row
+  typedef typename std::conditional<PREC == PREC_F64, double, float>::type ST;
+  constexpr int RW = BT / WM * 16;                            // output rows per round
+  constexpr int SS = BT + 16 / (int)sizeof(ST);               // LDS row stride, 16-byte rows
+  constexpr int EC = OUT == OUT_F32 ? 4 : 2;                  // elements per chunk
+  constexpr int CPR = BT / EC;                                // chunks per row
+  constexpr int NC = RW * CPR / NTHR;                         // chunks per thread and round
+  static_assert(RW * CPR % NTHR == 0, "whole chunks per thread");
+  ST* stg = reinterpret_cast<ST*>(pass_smem);
+  double* out64 = nullptr;
+  const double* base = nullptr;
+  if constexpr (OUT == OUT_FINAL) {
+    out64 = L.own + ring_slot(m, L.R_own) * nn;
+    base = L.j == 0 ? L.own + ring_slot(m - 1, L.R_own) * nn : L.prev + ring_slot(m, L.R_prev) * nn;
+  }
+  // output row of accumulator element r: FP32 tiles hold rows 4(l/16) + r, FP64 tiles hold
+  // rows (l/16) + 4r (measured lane layouts of the two instructions)
+  const int i_base = PREC == PREC_F64 ? (lane >> 4) : 4 * (lane >> 4);
+  constexpr int i_step = PREC == PREC_F64 ? 4 : 1;
+  auto chunk_at = [&](int a, int c, int* lr, int* lc, int64_t* o) {
+    const int id = tid + c * NTHR;
+    *lr = id / CPR;
+    *lc = (id % CPR) * EC;
+    const int row = row0 + (*lr / 16) * WM + 16 * a + *lr % 16;
+    *o = (int64_t)row * n + col0 + *lc;
+    return row < n && col0 + *lc < n;                // n is a multiple of 32: whole chunks
+  };
+  // the final update's FP64 operands (base, add) of this thread's chunks: one round ahead, or, in
+  // the small tiles, all of them before the k-loop, under which they arrive
+  constexpr int NF = BT < 128 ? MT : 2;
+  dbl2 bq[NF][NC];
+  flt2 aq[NF][NC];
+  auto fetch = [&](int a, int slot) {
+    if constexpr (OUT == OUT_FINAL) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        int lr, lc;
+        int64_t o;
+        if (!chunk_at(a, c, &lr, &lc, &o)) continue;
+        bq[slot][c] = gld<dbl2>(base + o);
+        aq[slot][c] = PREC != PREC_F64 && E.add ? gld<flt2>(E.add + o) : flt2{0.0f, 0.0f};
+      }
+    }
+  };
+  if constexpr (BT < 128) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a) fetch(a, a);
+  }
   auto kslice = [&](int k) { return (k < KT ? k : KT - 1) * BK; };
   if constexpr (PREC == PREC_BF16 && lds_stages<PREC, KX>() == 1) {
     // wide slices: one in flight, its loads cover a whole MFMA phase of twice the length
@@ -1166,48 +1207,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   // (column l%16 of lane l).  Round a takes tile row a of every wave through LDS, 16 rows per
   // wave row, the columns put back in their natural order; each thread then finishes and writes
   // 16-byte chunks, consecutive threads consecutive chunks of a row.
-  typedef typename std::conditional<PREC == PREC_F64, double, float>::type ST;
-  constexpr int RW = BT / WM * 16;                            // output rows per round
-  constexpr int SS = BT + 16 / (int)sizeof(ST);               // LDS row stride, 16-byte rows
-  constexpr int EC = OUT == OUT_F32 ? 4 : 2;                  // elements per chunk
-  constexpr int CPR = BT / EC;                                // chunks per row
-  constexpr int NC = RW * CPR / NTHR;                         // chunks per thread and round
-  static_assert(RW * CPR % NTHR == 0, "whole chunks per thread");
-  ST* stg = reinterpret_cast<ST*>(pass_smem);
-  double* out64 = nullptr;
-  const double* base = nullptr;
-  if constexpr (OUT == OUT_FINAL) {
-    out64 = L.own + (m % L.R_own) * nn;
-    base = L.j == 0 ? L.own + ((m - 1) % L.R_own) * nn : L.prev + (m % L.R_prev) * nn;
-  }
-  // output row of accumulator element r: FP32 tiles hold rows 4(l/16) + r, FP64 tiles hold
-  // rows (l/16) + 4r (measured lane layouts of the two instructions)
-  const int i_base = PREC == PREC_F64 ? (lane >> 4) : 4 * (lane >> 4);
-  constexpr int i_step = PREC == PREC_F64 ? 4 : 1;
-  auto chunk_at = [&](int a, int c, int* lr, int* lc, int64_t* o) {
-    const int id = tid + c * NTHR;
-    *lr = id / CPR;
-    *lc = (id % CPR) * EC;
-    const int row = row0 + (*lr / 16) * WM + 16 * a + *lr % 16;
-    *o = (int64_t)row * n + col0 + *lc;
-    return row < n && col0 + *lc < n;                // n is a multiple of 32: whole chunks
-  };
-  // the final update's FP64 operands (base, add) of this thread's chunks, one round ahead
-  dbl2 bq[2][NC];
-  flt2 aq[2][NC];
-  auto fetch = [&](int a, int slot) {
-    if constexpr (OUT == OUT_FINAL) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        int lr, lc;
-        int64_t o;
-        if (!chunk_at(a, c, &lr, &lc, &o)) continue;
-        bq[slot][c] = gld<dbl2>(base + o);
-        aq[slot][c] = PREC != PREC_F64 && E.add ? gld<flt2>(E.add + o) : flt2{0.0f, 0.0f};
-      }
-    }
-  };
-  fetch(0, 0);
+  if constexpr (BT == 128) fetch(0, 0);
 #pragma unroll
   for (int a = 0; a < MT; ++a) {
     __syncthreads();                                  // the buffer is free
@@ -1220,7 +1220,8 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
       for (int r = 0; r < 4; ++r) dst[i_step * r * SS] = acc[a][b][r];
     }
     __syncthreads();
-    if (a + 1 < MT) fetch(a + 1, (a + 1) & 1);
+    if constexpr (BT == 128)
+      if (a + 1 < MT) fetch(a + 1, (a + 1) % NF);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       int lr, lc;
@@ -1232,11 +1233,11 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
       } else if constexpr (OUT == OUT_F32) {
         gst<flt4>((float*)E.C + o, *(const flt4*)src);
       } else {
-        const dbl2 bs = bq[a & 1][c];
+        const dbl2 bs = bq[a % NF][c];
         if constexpr (PREC == PREC_F64) {
           gst<dbl2>(out64 + o, dbl2{bs[0] + src[0], bs[1] + src[1]});
         } else {
-          const flt2 ad = aq[a & 1][c];
+          const flt2 ad = aq[a % NF][c];
           gst<dbl2>(out64 + o, dbl2{bs[0] + ((double)ad[0] + (double)src[0]),
                                     bs[1] + ((double)ad[1] + (double)src[1])});
         }
@@ -1351,13 +1352,19 @@ bool wide_waves(int64_t n, int tile) {
   return PREC != PREC_BF16 && (tile & kPassWide64) && (!folded(n) || n % 128 == 0);
 }
 
-// Block tile of a pass over `cnt` levels of side n: the largest whose blocks cover about half
-// of the 256 compute units, so that a small grid is not left to a few of them.  The tile does
-// not change an output element's MFMA sequence, hence no bit of it.
+// Block tile of a pass over `cnt` levels of side n: 128 while that fills half of the 256 compute
+// units, then 64 while that gives every unit more than one block (split BF16: one, its blocks
+// being bound by LDS work and not by latency), else 32, so that a small grid is not left to a few
+// units.  Whole steps, us, for tiles of 32 / 64 / 128: 256^2 FP64 order 4 25.3 / 32.8 / 54.9, 512^2
+// FP32 order 2 57.4 / 60.0 / 108, 512^2 order 4 FP64 53.1 / 54.0 / 91.2 and split BF16 64.5 / 63.0 /
+// 80.3, 768^2 split BF16 order 3 120 / 94.4 / 106 and FP64 order 4 141 / 148 / 134, 1024^2 FP64
+// order 4 285 / 237 / 178 and order 1 79.6 / 81.7 / 149.  The tile does not change an output
+// element's MFMA sequence, hence no bit of it.
+template <int PREC>
 int block_tile(int64_t n, int cnt) {
   auto blocks = [&](int64_t t) { return ((n + t - 1) / t) * ((n + t - 1) / t) * cnt; };
   if (blocks(128) >= 128) return 128;
-  return blocks(64) >= 128 ? 64 : 32;
+  return blocks(64) >= (PREC == PREC_BF16 ? 256 : 257) ? 64 : 32;
 }
 
 // One transform pass.
@@ -1368,7 +1375,7 @@ void launch_pass(const Pass2D* d, const Lvl2D* lv, int count, int64_t n, int64_t
     const unsigned t = (unsigned)((n + bt - 1) / bt);
     hipLaunchKernelGGL(kern, dim3(t, t, count), dim3(threads), lds, st, d, lv, sigma);
   };
-  const int bt = block_tile(n, count);
+  const int bt = block_tile<PREC>(n, count);
   const bool fold = folded(n);
   if (bt == 128) {
     constexpr size_t full = pass_lds_bytes<PREC, 1, 128>(0), half = pass_lds_bytes<PREC, 1, 128>(1);
@@ -1544,7 +1551,6 @@ int plan2d_create(const ridc_problem* p, double h, double* const* ring, const in
     Lvl2D& L = pl->levels[j];
     for (int k = 0; k < pl->npass; ++k) {
       Pass2D& E = pl->passes[k * P + j];
-      E.level = j;
       // even passes: the right-hand side or residual to its sine coefficients; odd ones back, to
       // the level's new value or (first solve of a refined path) to x1, kept in FP32
       if (pl->prec == PREC_F64) {
@@ -1753,9 +1759,7 @@ int plan2d_advance(Plan2D* const* pls, int count, const int64_t* sigma_before, i
         L.sigma0 = -sigma_before[i];
         g_a2.h_lv[lo + e + j] = L;
         for (int k = 0; k < npass; ++k) {
-          Pass2D E = pl->passes[k * pl->P + j];
-          E.level = e + j;
-          g_a2.h_ps[po + (size_t)k * cnt + e + j] = E;
+          g_a2.h_ps[po + (size_t)k * cnt + e + j] = pl->passes[k * pl->P + j];
         }
       }
       e += pl->P;
