@@ -874,7 +874,8 @@ int validate_ext(const ridc_problem* p, const ridc_ext* e, ImexPlan* out) {
   for (int j = 1; j < P; ++j) pl.delay[j] = pl.delay[j - 1] + pl.S[j] - 1;
   pl.R.resize(P);
   for (int j = 0; j < P; ++j) pl.R[j] = j + 1 < P ? 2 * pl.S[j + 1] - 1 : 2;
-  const size_t vec = sizeof(double) * (size_t)p->n;
+  imex_shape(p->n, &pl.M, &pl.T);
+  const size_t vec = sizeof(double) * (size_t)pl.M * pl.T;    // vectors in block order
   for (int j = 0; j < P; ++j) {
     pl.rings += vec * pl.R[j];
     if (j + 1 < P) pl.frings += vec * pl.R[j];
@@ -888,9 +889,21 @@ int validate_ext(const ridc_problem* p, const ridc_ext* e, ImexPlan* out) {
   pl.work = align256(pl.work);
   pl.items = align256(sizeof(ImexLvl) * P);
   pl.total = pl.rings + pl.frings + pl.weights + pl.work + pl.items + 256;   // + flag
-  imex_shape(p->n, &pl.M, &pl.T);
   if (out) *out = pl;
   return RIDC_OK;
+}
+
+// Slot 0 of every level's ring from u0, and level j's final value to dst (grid order).
+int load_imex(ridc_handle* h, const double* u0_dev) {
+  ImexRings r{};
+  for (int j = 0; j < h->P; ++j) r.ring[j] = h->ring[j];
+  RIDC_HIP_TRY(launch_imex_load(u0_dev, r, h->P, (int)h->p.n, h->imex_M, h->imex_T, h->stream));
+  return RIDC_OK;
+}
+hipError_t read_imex(ridc_handle* h, int j, double* dst, int* flag) {
+  const int64_t V = (int64_t)h->imex_M * h->imex_T;
+  return launch_imex_read(h->ring[j] + (h->nt % h->R[j]) * V, dst, (int)h->p.n, h->imex_M,
+                          h->imex_T, flag, h->stream);
 }
 
 // One grouped launch per pipeline step for IMEX handles of one shape class (rows per thread,
@@ -1240,7 +1253,7 @@ int ridc_create_ext(const ridc_problem* p, const ridc_ext* e, void* hip_stream,
   }
   h->pool_bytes = pl.total;
   const int P = h->P;
-  const int64_t n = p->n;
+  const int64_t V = (int64_t)pl.M * pl.T;
   char* cur = h->pool;
   double* rp = (double*)cur;
   cur += pl.rings;
@@ -1257,10 +1270,10 @@ int ridc_create_ext(const ridc_problem* p, const ridc_ext* e, void* hip_stream,
   h->ringF.assign(P, nullptr);
   for (int j = 0; j < P; ++j) {
     h->ring[j] = rp;
-    rp += (int64_t)h->R[j] * n;
+    rp += (int64_t)h->R[j] * V;
     if (j + 1 < P) {
       h->ringF[j] = fp;
-      fp += (int64_t)h->R[j] * n;
+      fp += (int64_t)h->R[j] * V;
     }
   }
   // corrector weights: [row r][stage i][interp S, quad S], exact rationals rounded once
@@ -1297,11 +1310,11 @@ int ridc_create_ext(const ridc_problem* p, const ridc_ext* e, void* hip_stream,
     L.prevF = j > 0 ? h->ringF[j - 1] : nullptr;
     L.wt = j > 0 ? wp + woff[j] : nullptr;
     L.ks = kp;
-    kp += (int64_t)(2 * pr.s + 1) * n;
+    kp += (2 * pr.s + 1) * V;
     L.nt = 0;
     L.sigma0 = 0;
     L.delay = h->delay[j];
-    L.n = (int32_t)n;
+    L.n = (int32_t)p->n;
     L.j = j;
     L.s = pr.s;
     L.S = h->S[j];
@@ -1344,6 +1357,7 @@ int ridc_begin(ridc_handle* h, const double* u0_dev, int64_t nsteps) {
   int rc = arm_handle(h, u0_dev, nsteps);
   if (rc != RIDC_OK) return rc;
   // every level starts from the initial data (section III-E, Fig. 2): slot 0 of each ring
+  if (h->imex) return load_imex(h, u0_dev);
   for (int j = 0; j < h->P; ++j)
     RIDC_HIP_TRY(hipMemcpyAsync(h->ring[j], u0_dev, sizeof(double) * h->npts,
                                 hipMemcpyDeviceToDevice, h->stream));
@@ -1460,6 +1474,12 @@ int ridc_read(ridc_handle* h, double* uT_dev, double* levels_dev) {
   if (h->sigma != h->total) return fail(RIDC_E_STATE, "pipeline steps remain");
   const size_t bytes = sizeof(double) * h->npts;
   const int top = h->P - 1;
+  if (h->imex) {
+    if (uT_dev) RIDC_HIP_TRY(read_imex(h, top, uT_dev, h->flag));
+    for (int j = 0; levels_dev && j < h->P; ++j)
+      RIDC_HIP_TRY(read_imex(h, j, levels_dev + (int64_t)j * h->npts, nullptr));
+    return RIDC_OK;
+  }
   const double* src = h->ring[top] + (h->nt % h->R[top]) * h->npts;
   if (uT_dev) {
     RIDC_HIP_TRY(hipMemcpyAsync(uT_dev, src, bytes, hipMemcpyDeviceToDevice, h->stream));
@@ -1641,6 +1661,11 @@ int ridc_integrate_batch(ridc_handle* const* hs, int32_t count, const double* co
     rc = arm_handle(hs[i], u0[i], nsteps[i]);
     if (rc != RIDC_OK) return rc;
     most = std::max(most, hs[i]->total);
+    if (hs[i]->imex) {
+      rc = load_imex(hs[i], u0[i]);
+      if (rc != RIDC_OK) return rc;
+      continue;
+    }
     for (int j = 0; j < hs[i]->P; ++j)
       copies.push_back(CopyItem{u0[i], hs[i]->ring[j], hs[i]->npts, nullptr});
   }
@@ -1654,6 +1679,10 @@ int ridc_integrate_batch(ridc_handle* const* hs, int32_t count, const double* co
   for (int32_t i = 0; i < count; ++i) {
     ridc_handle* h = hs[i];
     const int top = h->P - 1;
+    if (h->imex) {
+      RIDC_HIP_TRY(read_imex(h, top, uT[i], h->flag));
+      continue;
+    }
     copies.push_back(CopyItem{h->ring[top] + (h->nt % h->R[top]) * h->npts, uT[i], h->npts,
                               h->flag});
   }

@@ -19,165 +19,247 @@
 // rings.
 //
 // Layout.  Thread t of T owns the M consecutive rows g0 = t M .. g0 + M - 1 in registers; rows
-// at or past n are padding (identity rows, value 0).  Stencil neighbours of loaded vectors come
-// from global memory; those of computed values from the edge exchange in LDS.
+// at or past n are padding (identity rows, value 0).  Stencil neighbours come from global memory
+// (loaded vectors) or from the adjacent lanes and, between waves, LDS (computed values).
 //
-// Tridiagonal solve (a partition method): each thread eliminates its block so that every row
-// couples only to the block's first and last unknowns, leaving a tridiagonal system of two
-// rows per thread, which parallel cyclic reduction solves in LDS (one barrier per stage, two
-// LDS buffers); the interior rows follow by back substitution.  Periodic grids (cyclic
-// systems) take the Sherman-Morrison correction: the cyclic matrix is a tridiagonal one plus
-// a rank-one term, so one solve with two right-hand sides and a scalar combination give the
-// cyclic solution.
+// Every implicit solve is a correction: a linear stage takes one solve for the difference to its
+// guess (the FP64 residual of the guess on the right), a Newton iterate one for the update, so the
+// rounding of the solver scales with the correction and not with the value.
+//
+// Tridiagonal solve (a partition method in three levels, one workgroup barrier):
+//  1. each thread eliminates its block, so that every row couples to the last unknown of the block
+//     before and of its own; substituting the next block's first row leaves one tridiagonal row
+//     per thread, in the blocks' last unknowns;
+//  2. parallel cyclic reduction with DPP moves inside the rows of 16 lanes, whose last lane stays
+//     an unknown: two equations per 16 threads (its first and its last unknown) go to LDS;
+//  3. every wave reads all of them (at most 64 groups, one per lane), joins them into a
+//     tridiagonal system of the groups' last unknowns, reduces its four rows of 16 lanes the same
+//     way and eliminates the last four in order.
+// The unknowns come back the same way: by registers, lane moves and no further barrier.
+// Periodic grids (cyclic systems) take the Sherman-Morrison correction: the cyclic matrix is a
+// tridiagonal one plus a rank-one term, so one solve with two right-hand sides and a scalar
+// combination give the cyclic solution.
+//
+// Bound: latency and FP64 issue inside one compute unit per level (a solve is some 720 FP64 and 700
+// other instructions a lane with 16 rows; the level's vectors cross its L2 port once a stage).
+// Reducing all 2 T block rows through LDS, one barrier per stage, with every vector in grid order
+// and re-read per stage, took 178 us per step of ARK3 + FBE and 184 us of RIDC4 with the cubic
+// reaction (9 Newton iterates) at n = 8192; this form takes 54 and 70.
 #include "ridc_internal.h"
 
 namespace ridc {
 
 namespace {
 
-// f_E at one point from its neighbours; ce is explicit_coeff(fe, a, h).
-__device__ __forceinline__ double fe_eval(int fe, double ce, double um, double u0, double up) {
-  if (fe == RIDC_FE_ADVECT_C2) return -ce * (up - um);
-  if (fe == RIDC_FE_LOGISTIC) return u0 * (1.0 - u0);
-  if (fe == RIDC_FE_ADVECT_UPWIND) return ce >= 0.0 ? -ce * (u0 - um) : -ce * (up - u0);
-  if (fe == RIDC_FE_BURGERS) return -ce * (up * up - um * um);
-  return 0.0;
-}
+// Global-memory views of descriptor pointers.  Pointers read from a table carry no address space,
+// so the compiler would emit flat instructions, which also count against the LDS wait counter.
+typedef __attribute__((address_space(1))) double gdbl;
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) dbl2 gdbl2;
+__device__ __forceinline__ gdbl* gp(double* p) { return (gdbl*)p; }
+__device__ __forceinline__ const gdbl* gp(const double* p) { return (const gdbl*)p; }
 
-// g and g' of the stiff reaction
+// g and g' of the stiff reaction, by selects (fs is uniform; a branch per row would cut the row
+// loops into blocks that cannot overlap)
 __device__ __forceinline__ double react(int fs, double u) {
-  if (fs == RIDC_FS_LOGISTIC) return u * (1.0 - u);
-  if (fs == RIDC_FS_CUBIC) return u - u * u * u;
-  return 0.0;
+  const double q = u * (1.0 - u), c = u - u * u * u;
+  return fs == RIDC_FS_CUBIC ? c : (fs == RIDC_FS_LOGISTIC ? q : 0.0);
 }
 __device__ __forceinline__ double react_prime(int fs, double u) {
-  if (fs == RIDC_FS_LOGISTIC) return 1.0 - 2.0 * u;
-  if (fs == RIDC_FS_CUBIC) return 1.0 - 3.0 * u * u;
-  return 0.0;
+  const double q = 1.0 - 2.0 * u, c = 1.0 - 3.0 * u * u;
+  return fs == RIDC_FS_CUBIC ? c : (fs == RIDC_FS_LOGISTIC ? q : 0.0);
 }
 
-// Per-workgroup state: problem data, thread position and the LDS regions (each region has two
-// buffers used alternately, so that one barrier per use keeps readers and writers apart).
-// Buffer k of a region is base + (k & 1) * stride (pointer arithmetic, not an indexed array,
-// so that the context stays in registers).
+// f_E of M rows: u[0] .. u[M+1] are rows g0-1 .. g0+M (the kind is branched on once)
+template <int M>
+__device__ __forceinline__ void fe_rows(int fe, double ce, const double (&u)[M + 2],
+                                        double (&out)[M]) {
+  auto all = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) out[i] = f(u[i], u[i + 1], u[i + 2]);
+  };
+  if (fe == RIDC_FE_ADVECT_C2) all([&](double a, double, double b) { return -ce * (b - a); });
+  else if (fe == RIDC_FE_LOGISTIC) all([](double, double x, double) { return x * (1.0 - x); });
+  else if (fe == RIDC_FE_ADVECT_UPWIND && ce >= 0.0)
+    all([&](double a, double x, double) { return -ce * (x - a); });
+  else if (fe == RIDC_FE_ADVECT_UPWIND) all([&](double, double x, double b) { return -ce * (b - x); });
+  else if (fe == RIDC_FE_BURGERS)
+    all([&](double a, double, double b) { return -ce * (b * b - a * a); });
+  else all([](double, double, double) { return 0.0; });
+}
+
+// Per-workgroup state: problem data, thread position and the LDS regions.  A region has two
+// buffers used alternately, so that one barrier per use keeps readers and writers apart (pointer
+// arithmetic, not an indexed array, so that the context stays in registers).
 struct Ctx {
-  int n, T, t, g0, fe, fs;
+  int n, T, t, g0, lane, wave, fe, fs;
   double ce, nu_h2, kappa;
-  double* pcr;     // PCR buffers: left coefficients (2T), right coefficients (2T), rhs (NR x 2T)
-  double* ex;      // edge exchange: first rows (NR x T), last rows (NR x T), rows 0 and n-1
-  double* red;     // workgroup reductions: 2 values per wave (32 doubles per buffer)
-  int pstride, xstride;
-  int pk, xk, rk;  // buffer toggles
+  double* grp;     // group equations: (3 + NR - 1) + (3 + NR - 1) values x kGroups, per buffer
+  double* ex;      // wave edges: first and last rows (16 waves each), rows 0 and n-1, maxima
+  double* rhs;     // stage right-hand side (M >= 16): row i of thread t at i T + t
+  int gk, xk;      // buffer toggles
 };
+constexpr int kGroups = kImexMaxThreads / 16;
+constexpr int kWaves = kImexMaxThreads / 64;
+// values of one edge buffer: per right-hand side 2 per wave and 2 rows; then 2 maxima per wave
+__host__ __device__ constexpr int ex_doubles(int NR) { return NR * (2 * kWaves + 2) + 2 * kWaves; }
+__host__ __device__ constexpr int grp_doubles(int NR) { return 2 * (2 + NR) * kGroups; }
 
-// LDS doubles of a workgroup of T threads with NR right-hand sides (layout as in imex_step)
-inline size_t lds_doubles(int NR, int T) {
-  return 2 * (size_t)(2 * T) * (2 + NR) + 2 * (size_t)(NR * (2 * T + 2)) + 2 * 32;
+// LDS doubles of a workgroup of T threads (layout as in imex_step)
+inline size_t lds_doubles(int NR, int M, int T) {
+  return 2 * (size_t)grp_doubles(NR) + 2 * (size_t)ex_doubles(NR) + (M >= 16 ? (size_t)M * T : 0);
 }
 
-// Publish this thread's first and last rows (and rows 0 and n-1 from their owners), then read
-// the neighbours of the block: xl = row g0-1, xr = row g0+M (0 past either end), w0 = row 0,
-// wn = row n-1.
-template <int M, int NR>
+// v of another lane, moved as two 32-bit halves by DPP; lanes without a source take `old`.  All
+// lanes of the wave are active.  kUp/kDown + k: the lane k below / above in the same row of 16;
+// kWaveUp / kWaveDown: the adjacent lane of the wave.
+constexpr int kUp = 0x110, kDown = 0x100, kWaveUp = 0x138, kWaveDown = 0x130;
+template <int CTRL>
+__device__ __forceinline__ double move0(double v) {   // lanes without a source take 0
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double move(double v, double old) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), CTRL, 0xF, 0xF,
+                                             false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(v), CTRL, 0xF, 0xF,
+                                             false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// 1 / b (b of moderate size) from the hardware estimate (2^-24) and two Newton steps, about an
+// ulp; NEWTON: one step, 2^-48, for solves that Newton's method repeats.  Used in the solves only,
+// whose results are corrections.
+template <bool NEWTON>
+__device__ __forceinline__ double recip(double b) {
+  double x = __builtin_amdgcn_rcp(b);
+  x = __builtin_fma(__builtin_fma(-b, x, 1.0), x, x);
+  return NEWTON ? x : __builtin_fma(__builtin_fma(-b, x, 1.0), x, x);
+}
+
+// Publish the wave's first and last rows (and rows 0 and n-1 from their owners), then read the
+// neighbours of the block: xl = row g0-1, xr = row g0+M (0 past either end), w0 = row 0, wn = row
+// n-1 (periodic grids only).  With `mx`, also the largest mx[0] and mx[1] over the workgroup.
+template <int M, int NR, bool PER>
 __device__ __forceinline__ void exchange(Ctx& c, const double (&x)[NR][M], double (&xl)[NR],
-                                         double (&xr)[NR], double (&w0)[NR], double (&wn)[NR]) {
-  double* e = c.ex + (c.xk & 1) * c.xstride;
+                                         double (&xr)[NR], double (&w0)[NR], double (&wn)[NR],
+                                         double* mx = nullptr) {
+  double* e = c.ex + (c.xk & 1) * ex_doubles(NR);
   c.xk++;
-  const int T = c.T, t = c.t;
+  double* ends = e + NR * 2 * kWaves;
+  double* red = e + NR * (2 * kWaves + 2);
+  if (mx) {
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    e[r * T + t] = x[r][0];
-    e[NR * T + r * T + t] = x[r][M - 1];
-  }
-  if (t == 0) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) e[2 * NR * T + r] = x[r][0];
-  }
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-    if (c.g0 + i == c.n - 1) {
-#pragma unroll
-      for (int r = 0; r < NR; ++r) e[2 * NR * T + NR + r] = x[r][i];
+    for (int k = 0; k < 2; ++k) {
+      double v = mx[k];
+      v = fmax(v, move<0x121>(v, v));
+      v = fmax(v, move<0x122>(v, v));
+      v = fmax(v, move<0x124>(v, v));
+      v = fmax(v, move<0x128>(v, v));
+      mx[k] = fmax(fmax(lane_value(v, 0), lane_value(v, 16)),
+                   fmax(lane_value(v, 32), lane_value(v, 48)));
     }
+  }
+  if (c.lane == 0) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) e[2 * (r * kWaves + c.wave)] = x[r][0];
+    if (mx) {
+      red[2 * c.wave] = mx[0];
+      red[2 * c.wave + 1] = mx[1];
+    }
+  }
+  if (c.lane == 63) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) e[2 * (r * kWaves + c.wave) + 1] = x[r][M - 1];
+  }
+  if constexpr (PER) {
+    if (c.t == 0) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) ends[2 * r] = x[r][0];
+    }
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+      if (c.g0 + i == c.n - 1) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) ends[2 * r + 1] = x[r][i];
+      }
+  }
   __syncthreads();
+  const int nw = c.T >> 6;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    xl[r] = t > 0 ? e[NR * T + r * T + t - 1] : 0.0;
-    xr[r] = t + 1 < T ? e[r * T + t + 1] : 0.0;
-    w0[r] = e[2 * NR * T + r];
-    wn[r] = e[2 * NR * T + NR + r];
-  }
-}
-
-// Stencil neighbours of local row i of a register block x with block neighbours xl, xr;
-// periodic grids wrap rows 0 and n-1 (w0, wn: their values).
-template <int M, bool PER>
-__device__ __forceinline__ void nbrs(const Ctx& c, const double (&x)[M], int i, double xl,
-                                     double xr, double w0, double wn, double& um, double& up) {
-  um = i > 0 ? x[i - 1] : xl;
-  up = i < M - 1 ? x[i + 1] : xr;
-  if (PER) {
-    const int g = c.g0 + i;
-    if (g == 0) um = wn;
-    if (g == c.n - 1) up = w0;
-  }
-}
-
-// Value of a global vector at row g in [-1, n]: zero ghosts (Dirichlet) or wrapped (periodic).
-template <bool PER>
-__device__ __forceinline__ double ld(const double* __restrict__ v, int g, int n) {
-  if (g >= 0 && g < n) return v[g];
-  if (PER) {
-    if (g == -1) return v[n - 1];
-    if (g == n) return v[0];
-  }
-  return 0.0;
-}
-
-// Rows g0-1 .. g0+M of a global vector (blocks away from both ends: plain loads).
-template <int M, bool PER>
-__device__ __forceinline__ void load_halo(const Ctx& c, const double* __restrict__ v,
-                                          double (&out)[M + 2]) {
-  if (c.g0 >= 1 && c.g0 + M < c.n) {
-    const double* p = v + c.g0 - 1;
-#pragma unroll
-    for (int i = 0; i < M + 2; ++i) out[i] = p[i];
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < M + 2; ++i) out[i] = ld<PER>(v, c.g0 + i - 1, c.n);
-}
-
-// Rows g0 .. g0+M-1: 16-byte loads when the block is inside the grid and 16-byte aligned.
-template <int M>
-__device__ __forceinline__ void load_rows(const Ctx& c, const double* __restrict__ v,
-                                          double (&out)[M]) {
-  if (c.g0 + M <= c.n && (reinterpret_cast<uintptr_t>(v + c.g0) & 15) == 0) {
-    const double2* p = reinterpret_cast<const double2*>(v + c.g0);
-#pragma unroll
-    for (int i = 0; i < M / 2; ++i) {
-      const double2 q = p[i];
-      out[2 * i] = q.x;
-      out[2 * i + 1] = q.y;
+    const double below = c.wave > 0 ? e[2 * (r * kWaves + c.wave - 1) + 1] : 0.0;
+    const double above = c.wave + 1 < nw ? e[2 * (r * kWaves + c.wave + 1)] : 0.0;
+    xl[r] = move<kWaveUp>(x[r][M - 1], below);
+    xr[r] = move<kWaveDown>(x[r][0], above);
+    if constexpr (PER) {
+      w0[r] = ends[2 * r];
+      wn[r] = ends[2 * r + 1];
+    } else {
+      w0[r] = wn[r] = 0.0;
     }
-    return;
   }
-#pragma unroll
-  for (int i = 0; i < M; ++i) out[i] = c.g0 + i < c.n ? v[c.g0 + i] : 0.0;
+  if (mx) {
+    double a = 0.0, b = 0.0;
+    for (int w = 0; w < nw; ++w) {
+      a = fmax(a, red[2 * w]);
+      b = fmax(b, red[2 * w + 1]);
+    }
+    mx[0] = a;
+    mx[1] = b;
+  }
 }
 
+// Vectors in global memory (rings and workspace) keep their rows in block order: row i of thread t
+// at i T + t, padding rows zero, so that a wave's access is contiguous whatever M is (with rows in
+// grid order every lane of a load touches a line of its own: 80 against 102 us per step, ARK3 + FBE
+// at n = 8192, M = 16).
+
+// This thread's rows.
 template <int M>
-__device__ __forceinline__ void store_rows(const Ctx& c, double* __restrict__ v,
+__device__ __forceinline__ void load_rows(const Ctx& c, const gdbl* __restrict__ v,
+                                          double (&out)[M]) {
+#pragma unroll
+  for (int i = 0; i < M; ++i) out[i] = (v + i * c.T)[(unsigned)c.t];
+}
+template <int M>
+__device__ __forceinline__ void store_rows(const Ctx& c, gdbl* __restrict__ v,
                                            const double (&x)[M]) {
-  if (c.g0 + M <= c.n && (reinterpret_cast<uintptr_t>(v + c.g0) & 15) == 0) {
-    double2* p = reinterpret_cast<double2*>(v + c.g0);
 #pragma unroll
-    for (int i = 0; i < M / 2; ++i) p[i] = make_double2(x[2 * i], x[2 * i + 1]);
-    return;
+  for (int i = 0; i < M; ++i) (v + i * c.T)[(unsigned)c.t] = x[i];
+}
+// The same, zero in the padding rows.
+template <int M>
+__device__ __forceinline__ void store_real(const Ctx& c, gdbl* __restrict__ v,
+                                           const double (&x)[M]) {
+#pragma unroll
+  for (int i = 0; i < M; ++i) (v + i * c.T)[(unsigned)c.t] = c.g0 + i < c.n ? x[i] : 0.0;
+}
+
+// Rows g0-1 .. g0+M: zero ghosts (Dirichlet), or wrapped (periodic).
+template <int M, bool PER>
+__device__ __forceinline__ void load_halo(const Ctx& c, const gdbl* __restrict__ v,
+                                          double (&out)[M + 2]) {
+  const unsigned lt = c.t > 0 ? c.t - 1 : 0, rt = c.t + 1 < c.T ? c.t + 1 : c.T - 1;
+  const double l = (v + (M - 1) * c.T)[lt], r = v[rt];
+#pragma unroll
+  for (int i = 0; i < M; ++i) out[i + 1] = (v + i * c.T)[(unsigned)c.t];
+  out[0] = c.t > 0 ? l : 0.0;
+  out[M + 1] = c.t + 1 < c.T ? r : 0.0;
+  if constexpr (PER) {
+    const int q = (c.n - 1) / M, k = (c.n - 1) % M;           // row n-1 sits in thread q, row k
+    const double first = v[0], last = v[k * c.T + q];
+    if (c.t == 0) out[0] = last;
+#pragma unroll
+    for (int i = 1; i <= M; ++i)
+      if (c.g0 + i == c.n) out[i + 1] = first;
   }
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-    if (c.g0 + i < c.n) v[c.g0 + i] = x[i];
 }
 
 // f^S = nu Lap_h u + kappa g(u) and f^N at one row.
@@ -185,56 +267,59 @@ __device__ __forceinline__ double fstiff(const Ctx& c, double um, double u0, dou
   return c.nu_h2 * (up - 2.0 * u0 + um) + c.kappa * react(c.fs, u0);
 }
 
-// Largest of two values over the workgroup (both non-negative).
-__device__ __forceinline__ void wg_max2(Ctx& c, double& a, double& b) {
+// One stage of parallel cyclic reduction over the lanes of a row of 16, stride S: row q,
+// a x_{q-S} + x_q + c x_{q+S} = d, takes rows q -+ S.  Past the row's ends the coupling stays (to
+// the unknown before or after the row): a missing row reads as (a, c, d) = (-1, 0, 0) below and
+// (0, -1, 0) above.
+template <int S, int NR, bool NW>
+__device__ __forceinline__ void reduce_stage(double& a, double& c, double (&d)[NR]) {
+  const double am = move<kUp + S>(a, -1.0), cm = move0<kUp + S>(c);
+  const double ap = move0<kDown + S>(a), cp = move<kDown + S>(c, -1.0);
+  double dm[NR], dp[NR];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    a = fmax(a, __shfl_xor(a, off, 64));
-    b = fmax(b, __shfl_xor(b, off, 64));
+  for (int k = 0; k < NR; ++k) {
+    dm[k] = move0<kUp + S>(d[k]);
+    dp[k] = move0<kDown + S>(d[k]);
   }
-  double* r = c.red + (c.rk & 1) * 32;
-  c.rk++;
-  const int wave = c.t >> 6, nw = c.T >> 6;
-  if ((c.t & 63) == 0) {
-    r[2 * wave] = a;
-    r[2 * wave + 1] = b;
-  }
-  __syncthreads();
-  a = 0.0;
-  b = 0.0;
-  for (int w = 0; w < nw; ++w) {
-    a = fmax(a, r[2 * w]);
-    b = fmax(b, r[2 * w + 1]);
-  }
+  const double inv = recip<NW>(__builtin_fma(-a, cm, __builtin_fma(-c, ap, 1.0)));
+#pragma unroll
+  for (int k = 0; k < NR; ++k)
+    d[k] = __builtin_fma(-a, dm[k], __builtin_fma(-c, dp[k], d[k])) * inv;
+  a = -a * am * inv;
+  c = -c * cp * inv;
+}
+template <int NR, bool NW>
+__device__ __forceinline__ void reduce_row(double& a, double& c, double (&d)[NR]) {
+  reduce_stage<1, NR, NW>(a, c, d);
+  reduce_stage<2, NR, NW>(a, c, d);
+  reduce_stage<4, NR, NW>(a, c, d);
+  reduce_stage<8, NR, NW>(a, c, d);
 }
 
 // Solve the tridiagonal system with off-diagonals -r (zero at Dirichlet ends; periodic: cyclic
-// with corners -r) whose diagonal b_g and right-hand side d_g (NR = 1) this thread's rows get
-// from rows(i, b, d).  x receives this thread's rows of the solution (padding rows: 0).
+// with corners -r) whose diagonal b_g and right-hand side d_g this thread's rows get from
+// rows(i, b, d).  x receives this thread's rows of the solution (padding rows: 0).
 // Periodic (PER): d0 is the diagonal of row 0; the second right-hand side is the rank-one
 // correction's vector.
-template <int M, bool PER, typename Rows>
+template <int M, bool PER, bool NW, typename Rows>
 __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows,
                                           double (&x)[M]) {
   constexpr int NR = PER ? 2 : 1;
   const int n = c.n, g0 = c.g0;
-  double A[M], C[M], D[NR][M];
-  double a0n = 0.0, c0n = 0.0, D0n[NR];
-  // forward: row 0 normalised; rows 1..M-1 to  A_i x_0 + x_i + C_i x_{i+1} = D_i
+  // Down the block: x_i = D_i - A_i x_{-1} + E_i x_{i+1}, x_{-1} the last row of the block before.
+  // Only E = r / pivot and D are kept: A_i = E_i A_{i-1}, and the block's first row in terms of
+  // x_{-1} and x_{M-1}, x_0 = d0 - a0 x_{-1} - c0 x_{M-1}, is summed on the way (w = E_0 .. E_{i-1}).
+  // Padding rows have E = D = 0: their value 0 is the ghost row after row n-1.
+  double E[M], D[NR][M], a0 = 0.0, d0s[NR], w = 1.0, A = 0.0;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) d0s[q] = 0.0;
 #pragma unroll
   for (int i = 0; i < M; ++i) {
     const int g = g0 + i;
-    const bool real = g < n;
-    double b = 1.0, d[NR];
+    double b, d[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) d[q] = 0.0;
-    if (real) {
-      double dd;
-      rows(i, b, dd);
-      d[0] = dd;
-    }
-    const double lo = (!real || g == 0) ? 0.0 : -r;
-    const double up = (!real || g == n - 1) ? 0.0 : -r;
+    rows(i, b, d[0]);
     if (PER) {
       if (g == 0) {
         b += d0;            // b - gamma, gamma = -d0
@@ -245,106 +330,149 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
         d[NR - 1] = -r;     // u_{n-1} = c_{n-1}
       }
     }
-    if (i == 0) {
-      const double inv = 1.0 / b;
-      a0n = lo * inv;
-      c0n = up * inv;
+    if (i > 0) b = __builtin_fma(-r, E[i - 1], b);
+    double inv = recip<NW>(b);
+    inv = g < n ? inv : 0.0;
+    E[i] = r * inv;
 #pragma unroll
-      for (int q = 0; q < NR; ++q) D0n[q] = d[q] * inv;
-    } else if (i == 1) {
-      const double inv = 1.0 / b;
-      A[1] = lo * inv;
-      C[1] = up * inv;
+    for (int q = 0; q < NR; ++q)
+      D[q][i] = (i > 0 ? __builtin_fma(r, D[q][i - 1], d[q]) : d[q]) * inv;
+    A = i > 0 ? E[i] * A : (g == 0 ? 0.0 : -E[0]);
+    if (i < M - 1) {
+      a0 = __builtin_fma(w, A, a0);
 #pragma unroll
-      for (int q = 0; q < NR; ++q) D[q][1] = d[q] * inv;
-    } else {
-      const double inv = 1.0 / (b - lo * C[i - 1]);
-      A[i] = -lo * A[i - 1] * inv;
-      C[i] = up * inv;
-#pragma unroll
-      for (int q = 0; q < NR; ++q) D[q][i] = (d[q] - lo * D[q][i - 1]) * inv;
+      for (int q = 0; q < NR; ++q) d0s[q] = __builtin_fma(w, D[q][i], d0s[q]);
+      w *= E[i];
     }
   }
-  // backward: rows M-2..1 to  A_i x_0 + x_i + C_i x_{M-1} = D_i
+  const double A0 = g0 == 0 ? 0.0 : -E[0], c0 = -w, Cl = -E[M - 1];
+  // one row per thread: the next block's first row replaces its unknown.  The last lane of a row
+  // of 16 keeps its equation for later and stands as the unknown after the others (0, -1, 0).
+  const bool tail = (c.lane & 15) == 15;
+  double ra, rc, rd[NR];
+  {
+    const double an = move0<kDown + 1>(a0), cn = move0<kDown + 1>(c0);
+    const double inv = recip<NW>(__builtin_fma(-Cl, an, 1.0));
+    ra = tail ? 0.0 : A * inv;
+    rc = tail ? -1.0 : -Cl * cn * inv;
 #pragma unroll
-  for (int i = M - 3; i >= 1; --i) {
-    A[i] -= C[i] * A[i + 1];
-#pragma unroll
-    for (int q = 0; q < NR; ++q) D[q][i] -= C[i] * D[q][i + 1];
-    C[i] = -C[i] * C[i + 1];
+    for (int q = 0; q < NR; ++q) {
+      const double dn = move0<kDown + 1>(d0s[q]);
+      rd[q] = tail ? 0.0 : __builtin_fma(-Cl, dn, D[q][M - 1]) * inv;
+    }
   }
-  // the two reduced rows of this block: (x_{-1}, x_0, x_{M-1}) and (x_0, x_{M-1}, x_M)
-  double ra[2], rc[2], rd[NR][2];
-  if (M >= 3) {
-    const double inv = 1.0 / (1.0 - c0n * A[1]);
-    ra[0] = a0n * inv;
-    rc[0] = -c0n * C[1] * inv;
+  reduce_row<NR, NW>(ra, rc, rd);
+  // the group's equations: its last unknown L + a XL + c F' = d (XL: the last unknown of the group
+  // before, F': the first row of the next group), its first row F + a XL + c L = d
+  double* gr = c.grp + (c.gk & 1) * grp_doubles(NR);
+  double* gf = gr + (2 + NR) * kGroups;
+  c.gk++;
+  const int grp = c.t >> 4;
+  {
+    const double a14 = move0<kUp + 1>(ra), c14 = move0<kUp + 1>(rc);
+    double d14[NR];
 #pragma unroll
-    for (int q = 0; q < NR; ++q) rd[q][0] = (D0n[q] - c0n * D[q][1]) * inv;
+    for (int q = 0; q < NR; ++q) d14[q] = move0<kUp + 1>(rd[q]);
+    if (tail) {
+      const double inv = recip<NW>(__builtin_fma(-A, c14, 1.0));
+      gr[grp] = -A * a14 * inv;
+      gr[kGroups + grp] = Cl * inv;
+#pragma unroll
+      for (int q = 0; q < NR; ++q)
+        gr[(2 + q) * kGroups + grp] = __builtin_fma(-A, d14[q], D[q][M - 1]) * inv;
+    }
+    if ((c.lane & 15) == 0) {
+      gf[grp] = __builtin_fma(-c0, ra, a0);
+      gf[kGroups + grp] = -c0 * rc;
+#pragma unroll
+      for (int q = 0; q < NR; ++q)
+        gf[(2 + q) * kGroups + grp] = __builtin_fma(-c0, rd[q], d0s[q]);
+    }
+  }
+  __syncthreads();
+  // all groups' last unknowns, one per lane of every wave
+  const int G = c.T >> 4, q0 = c.lane;
+  double ga = 0.0, gc = 0.0, gd[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) gd[q] = 0.0;
+  if (q0 < G) {
+    const bool nx = q0 + 1 < G;
+    const double af = nx ? gf[q0 + 1] : 0.0, cf = nx ? gf[kGroups + q0 + 1] : 0.0;
+    const double cl = gr[kGroups + q0];
+    const double inv = recip<NW>(__builtin_fma(-cl, af, 1.0));
+    ga = gr[q0] * inv;
+    gc = -cl * cf * inv;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const double df = nx ? gf[(2 + q) * kGroups + q0 + 1] : 0.0;
+      gd[q] = __builtin_fma(-cl, df, gr[(2 + q) * kGroups + q0]) * inv;
+    }
+  }
+  reduce_row<NR, NW>(ga, gc, gd);
+  double X[NR];                                  // group q0's last unknown
+  if (G <= 16) {
+#pragma unroll
+    for (int q = 0; q < NR; ++q) X[q] = gd[q];
   } else {
-    ra[0] = a0n;
-    rc[0] = c0n;
+    // the rows of 16 groups in order: F_r = y - z F_{r+1} and L_r = al - be F_{r+1} for their first
+    // and last unknowns
+    double be = 0.0, y[NR][4], z[4], al[NR][4], bl[4];
 #pragma unroll
-    for (int q = 0; q < NR; ++q) rd[q][0] = D0n[q];
-  }
-  ra[1] = A[M - 1];
-  rc[1] = C[M - 1];
+    for (int s = 0; s < 4; ++s) {
+      const double aF = lane_value(ga, 16 * s), cF = lane_value(gc, 16 * s);
+      const double aL = lane_value(ga, 16 * s + 15), cL = lane_value(gc, 16 * s + 15);
+      const double inv = recip<NW>(__builtin_fma(-aF, be, 1.0));
+      z[s] = cF * inv;
+      bl[s] = __builtin_fma(aL * be, z[s], cL);
 #pragma unroll
-  for (int q = 0; q < NR; ++q) rd[q][1] = D[q][M - 1];
-  // parallel cyclic reduction of the 2T reduced rows (normalised: unit diagonal)
-  const int T2 = 2 * c.T;
-  for (int s = 1; s < T2; s <<= 1) {
-    double* pa = c.pcr + (c.pk & 1) * c.pstride;
-    double* pc = pa + T2;
-    double* pd = pc + T2;
-    c.pk++;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int q = 2 * c.t + h;
-      pa[q] = ra[h];
-      pc[q] = rc[h];
-#pragma unroll
-      for (int k = 0; k < NR; ++k) pd[k * T2 + q] = rd[k][h];
+      for (int q = 0; q < NR; ++q) {
+        const double ap = s > 0 ? al[q][s - 1] : 0.0;
+        y[q][s] = __builtin_fma(-aF, ap, lane_value(gd[q], 16 * s)) * inv;
+        al[q][s] = __builtin_fma(aL * be, y[q][s],
+                                 __builtin_fma(-aL, ap, lane_value(gd[q], 16 * s + 15)));
+      }
+      be = bl[s];
     }
-    __syncthreads();
+    const int row = c.lane >> 4;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int q = 2 * c.t + h;
-      double am = 0.0, cm = 0.0, ap = 0.0, cp = 0.0, dm[NR], dp[NR];
+    for (int q = 0; q < NR; ++q) {
+      double F = 0.0, before = 0.0, after = 0.0;
 #pragma unroll
-      for (int k = 0; k < NR; ++k) dm[k] = dp[k] = 0.0;
-      if (q - s >= 0) {
-        am = pa[q - s];
-        cm = pc[q - s];
-#pragma unroll
-        for (int k = 0; k < NR; ++k) dm[k] = pd[k * T2 + q - s];
+      for (int s = 3; s >= 0; --s) {
+        const double L = __builtin_fma(-bl[s], F, al[q][s]);
+        if (row == s) after = F;
+        if (row == s + 1) before = L;
+        F = __builtin_fma(-z[s], F, y[q][s]);
       }
-      if (q + s < T2) {
-        ap = pa[q + s];
-        cp = pc[q + s];
-#pragma unroll
-        for (int k = 0; k < NR; ++k) dp[k] = pd[k * T2 + q + s];
-      }
-      const double inv = 1.0 / (1.0 - ra[h] * cm - rc[h] * ap);
-      const double a = ra[h], cc = rc[h];
-      ra[h] = -a * am * inv;
-      rc[h] = -cc * cp * inv;
-#pragma unroll
-      for (int k = 0; k < NR; ++k) rd[k][h] = (rd[k][h] - a * dm[k] - cc * dp[k]) * inv;
+      X[q] = __builtin_fma(-ga, before, __builtin_fma(-gc, after, gd[q]));
     }
   }
-  // back substitution, in place
+  // back: the last unknowns of this group and of the one before, of this block and of the one
+  // before, then the rows
+  const int w4 = __builtin_amdgcn_readfirstlane(c.wave) * 4, row = c.lane >> 4;
 #pragma unroll
   for (int q = 0; q < NR; ++q) {
+    const double l0 = lane_value(X[q], w4), l1 = lane_value(X[q], w4 + 1);
+    const double l2 = lane_value(X[q], w4 + 2), l3 = lane_value(X[q], w4 + 3);
+    const double lb = w4 > 0 ? lane_value(X[q], w4 - 1) : 0.0;
+    const double L = row == 0 ? l0 : (row == 1 ? l1 : (row == 2 ? l2 : l3));
+    const double XL = row == 0 ? lb : (row == 1 ? l0 : (row == 2 ? l1 : l2));
+    const double xl = __builtin_fma(-ra, XL, __builtin_fma(-rc, L, rd[q]));
+    const double xp = move<kUp + 1>(xl, XL);
+    double p = A0 * xp;
 #pragma unroll
-    for (int i = 1; i < M - 1; ++i) D[q][i] = D[q][i] - A[i] * rd[q][0] - C[i] * rd[q][1];
-    D[q][0] = rd[q][0];
-    D[q][M - 1] = rd[q][1];
+    for (int i = 0; i < M - 1; ++i) {
+      D[q][i] -= p;
+      p *= E[i + 1];
+    }
+    D[q][M - 1] = xl;
+#pragma unroll
+    for (int i = M - 2; i >= 0; --i) D[q][i] = __builtin_fma(E[i], D[q][i + 1], D[q][i]);
   }
-  if (PER) {
+  if constexpr (PER) {
     // x = y - z (v.y) / (1 + v.z),  v = (1, 0, .., 0, r/d0)
     double xl[NR], xr[NR], w0[NR], wn[NR];
-    exchange<M, NR>(c, D, xl, xr, w0, wn);
+    exchange<M, NR, true>(c, D, xl, xr, w0, wn);
     const double v1 = r / d0;
     const double f = (w0[0] + v1 * wn[0]) / (1.0 + w0[NR - 1] + v1 * wn[NR - 1]);
 #pragma unroll
@@ -362,81 +490,95 @@ struct Edges {
 };
 
 template <int M, bool PER>
-__device__ __forceinline__ Edges<M> edges(Ctx& c, const double (&x)[M]) {
-  double xx[1][M];
+__device__ __forceinline__ Edges<M> edges(Ctx& c, const double (&x)[M], double* mx = nullptr) {
+  constexpr int NR = PER ? 2 : 1;       // the edge buffers have this layout
+  double xx[NR][M];
 #pragma unroll
-  for (int i = 0; i < M; ++i) xx[0][i] = x[i];
-  double xl[1], xr[1], w0[1], wn[1];
-  exchange<M, 1>(c, xx, xl, xr, w0, wn);
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int i = 0; i < M; ++i) xx[r][i] = x[i];
+  double xl[NR], xr[NR], w0[NR], wn[NR];
+  exchange<M, NR, PER>(c, xx, xl, xr, w0, wn, mx);
   return Edges<M>{xl[0], xr[0], w0[0], wn[0]};
 }
 
-// Solve y - tau f^S(y) = rhs for this thread's rows (guess in y on entry).  Linear f^S: one
-// solve and one step of iterative refinement with the FP64 residual, so that each stage is the
-// exact solution of its linear system to rounding (section II).  Otherwise Newton's method
-// with the stopping rule: the largest update is below 1e-15 max(1, max|y|), or below
-// 1e-11 max(1, max|y|) and above half the previous one (rounding noise); after maxit iterates
-// without stopping, y becomes NaN.  MEM: the right-hand side is read from rhs_mem (rows g0..)
-// instead of registers, which keeps the largest blocks (16 rows per thread) out of scratch.
-template <int M, bool PER, bool MEM>
-__device__ __forceinline__ void stage_solve(Ctx& c, double tau, int maxit, const double (&rhs)[M],
-                                            const double* __restrict__ rhs_mem, double (&y)[M]) {
+// Rows g0-1 .. g0+M of a register block as its stencils see them (a periodic grid wraps rows 0 and
+// n-1: the block's row before row 0 is row n-1; a row after row n-1 is row 0).
+template <int M, bool PER>
+__device__ __forceinline__ void with_halo(const Ctx& c, const double (&x)[M], const Edges<M>& e,
+                                          double (&out)[M + 2]) {
+  out[0] = PER && c.g0 == 0 ? e.wn : e.l;
+#pragma unroll
+  for (int i = 0; i < M; ++i) out[i + 1] = PER && c.g0 + i == c.n ? e.w0 : x[i];
+  out[M + 1] = PER && c.g0 + M == c.n ? e.w0 : e.r;
+}
+
+// Solve y - tau f^S(y) = rhs for this thread's rows (guess in y on entry, its neighbours in e) and
+// leave the solution's neighbours in e.  Linear f^S: y += solve(FP64 residual of the guess).
+// Otherwise Newton's method with the stopping rule: the largest update is below 1e-15 max(1,
+// max|y|), or below 1e-11 max(1, max|y|) and above half the previous one (rounding noise); after
+// maxit iterates without stopping, y becomes NaN.  rhs_at(i): the right-hand side of local row i.
+template <int M, bool PER, typename Rhs>
+__device__ __forceinline__ void stage_solve(Ctx& c, double tau, int maxit, Rhs rhs_at,
+                                            double (&y)[M], Edges<M>& e) {
   const double r = tau * c.nu_h2;
   const double b0 = 1.0 + 2.0 * r;
-  auto rhs_at = [&](int i) { return MEM ? rhs_mem[c.g0 + i] : rhs[i]; };
+  e = edges<M, PER>(c, y);
   if (c.fs == RIDC_FS_DIFFUSION) {
-    tri_solve<M, PER>(c, r, b0, [&](int i, double& b, double& d) { b = b0; d = rhs_at(i); }, y);
-    const Edges<M> e = edges<M, PER>(c, y);
-    double delta[M];
-    tri_solve<M, PER>(
+    double delta[M], yh[M + 2];
+    with_halo<M, PER>(c, y, e, yh);
+    tri_solve<M, PER, false>(
         c, r, b0,
-        [&](int i, double& b, double& d) {
-          double um, up;
-          nbrs<M, PER>(c, y, i, e.l, e.r, e.w0, e.wn, um, up);
-          d = rhs_at(i) - (y[i] - tau * c.nu_h2 * (up - 2.0 * y[i] + um));
+        [&](int i, double& b, double& d) __attribute__((always_inline)) {
+          d = rhs_at(i) - (y[i] - tau * c.nu_h2 * (yh[i + 2] - 2.0 * y[i] + yh[i]));
           b = b0;
         },
         delta);
 #pragma unroll
     for (int i = 0; i < M; ++i) y[i] += delta[i];
+    e = edges<M, PER>(c, y);
     return;
   }
   double last = __builtin_inf();
   bool done = false;
   for (int it = 0; it < maxit && !done; ++it) {
-    const Edges<M> e = edges<M, PER>(c, y);
-    double delta[M];
-    tri_solve<M, PER>(
+    double delta[M], yh[M + 2];
+    with_halo<M, PER>(c, y, e, yh);
+    tri_solve<M, PER, true>(
         c, r, b0,
-        [&](int i, double& b, double& d) {
-          double um, up;
-          nbrs<M, PER>(c, y, i, e.l, e.r, e.w0, e.wn, um, up);
-          d = rhs_at(i) - (y[i] - tau * fstiff(c, um, y[i], up));
+        [&](int i, double& b, double& d) __attribute__((always_inline)) {
+          d = rhs_at(i) - (y[i] - tau * fstiff(c, yh[i], y[i], yh[i + 2]));
           b = b0 - tau * c.kappa * react_prime(c.fs, y[i]);
         },
         delta);
-    double dmax = 0.0, ymax = 0.0;
+    double mx[2] = {0.0, 0.0};          // largest update, largest value
 #pragma unroll
     for (int i = 0; i < M; ++i) {
       y[i] += delta[i];
-      if (c.g0 + i < c.n) {
-        dmax = fmax(dmax, fabs(delta[i]));
-        ymax = fmax(ymax, fabs(y[i]));
-      }
+      const bool real = c.g0 + i < c.n;
+      mx[0] = real ? fmax(mx[0], fabs(delta[i])) : mx[0];
+      mx[1] = real ? fmax(mx[1], fabs(y[i])) : mx[1];
     }
-    wg_max2(c, dmax, ymax);
-    const double scale = fmax(1.0, ymax);
-    done = dmax <= 1e-15 * scale || (dmax <= 1e-11 * scale && dmax > 0.5 * last);
-    last = dmax;
+    e = edges<M, PER>(c, y, mx);
+    const double scale = fmax(1.0, mx[1]);
+    done = mx[0] <= 1e-15 * scale || (mx[0] <= 1e-11 * scale && mx[0] > 0.5 * last);
+    last = mx[0];
   }
   if (!done) {
 #pragma unroll
     for (int i = 0; i < M; ++i) y[i] = __builtin_nan("");
+    e = edges<M, PER>(c, y);
   }
 }
 
+// m mod R (a step's index fits 32 bits in all but the longest runs)
+__device__ __forceinline__ int ring_slot(int64_t m, int R) {
+  const int s = (uint64_t)m >> 32 == 0 ? (int)((uint32_t)m % (uint32_t)R) : (int)(m % R);
+  return __builtin_amdgcn_readfirstlane(s);    // uniform: addresses built from it stay scalar
+}
+
 template <int M, bool PER>
-__device__ void imex_step(const ImexLvl& L, int64_t sigma, bool init, double* lds) {
+__device__ __forceinline__ void imex_step(const ImexLvl& L, int64_t sigma, bool init, double* lds) {
   constexpr int NR = PER ? 2 : 1;
   Ctx c;
   c.n = L.n;
@@ -448,23 +590,23 @@ __device__ void imex_step(const ImexLvl& L, int64_t sigma, bool init, double* ld
   c.ce = L.ce;
   c.nu_h2 = L.nu_h2;
   c.kappa = L.kappa;
-  c.pstride = 2 * c.T * (2 + NR);
-  c.xstride = NR * (2 * c.T + 2);
-  c.pcr = lds;
-  c.ex = lds + 2 * c.pstride;
-  c.red = c.ex + 2 * c.xstride;
-  c.pk = c.xk = c.rk = 0;
-  const int n = c.n;
+  c.lane = c.t & 63;
+  c.wave = c.t >> 6;
+  c.grp = lds;
+  c.ex = lds + 2 * grp_doubles(NR);
+  c.rhs = c.ex + 2 * ex_doubles(NR);
+  c.gk = c.xk = 0;
+  const int64_t V = (int64_t)M * c.T;    // doubles per vector
   if (init) {
     // f of the initial value (slot 0), read by the next level's window at node t_0
     if (!L.ownF) return;
     double u[M + 2];
-    load_halo<M, PER>(c, L.own, u);
+    load_halo<M, PER>(c, gp(L.own), u);
     double f[M];
+    fe_rows<M>(c.fe, c.ce, u, f);
 #pragma unroll
-    for (int i = 0; i < M; ++i)
-      f[i] = fstiff(c, u[i], u[i + 1], u[i + 2]) + fe_eval(c.fe, c.ce, u[i], u[i + 1], u[i + 2]);
-    store_rows<M>(c, L.ownF, f);
+    for (int i = 0; i < M; ++i) f[i] += fstiff(c, u[i], u[i + 1], u[i + 2]);
+    store_real<M>(c, gp(L.ownF), f);
     return;
   }
   const int64_t m = sigma - L.sigma0 - L.delay;   // this step computes t_m from t_{m-1}
@@ -473,128 +615,161 @@ __device__ void imex_step(const ImexLvl& L, int64_t sigma, bool init, double* ld
   const double dt = L.dt;
   const int s = L.s, S = L.S;
   const bool corr = L.prev != nullptr;
-  const double* yn_p = L.own + (tn % L.R_own) * (int64_t)n;
+  const gdbl* yn_p = gp(L.own) + ring_slot(tn, L.R_own) * V;
   // corrector window: S nodes t_start .. t_{start+S-1}; t_n sits at position rpos
   int64_t start = 0;
-  int rpos = 0;
+  int rpos = 0, slot0 = 0;
   if (corr) {
     start = tn >= S - 2 ? tn + 2 - S : 0;
     rpos = (int)(tn - start);
+    slot0 = ring_slot(start, L.R_prev);
+  }
+  gdbl* const ks = gp(L.ks);
+  gdbl* const ss_p = ks + 2 * (s - 1) * V;     // f^S(eta(t_n + c_i dt)) during a solve
+  gdbl* const sn_p = ss_p + V;                 // f^N(eta(t_n + c_i dt)) during a solve
+  // does a later stage take K^S_i, K^N_i ?
+  auto taken = [&](int i, bool* S_i, bool* N_i) {
+    *S_i = *N_i = false;
+    for (int l = i + 1; l < s; ++l) {
+      *S_i = *S_i || L.AS[l][i] != 0.0;
+      *N_i = *N_i || L.AN[l][i] != 0.0;
+    }
+  };
+  bool useS, useN;
+  {
+    // stage 0: explicit, c = 0, so Y_0 = y_n and eta is the node at t_n
+    taken(0, &useS, &useN);
+    double y[M + 2], v[M + 2], k[M], f[M];
+    load_halo<M, PER>(c, yn_p, y);
+    if (corr) load_halo<M, PER>(c, gp(L.prev) + ring_slot(tn, L.R_prev) * V, v);
+    if (useS) {
+#pragma unroll
+      for (int x = 0; x < M; ++x) {
+        k[x] = fstiff(c, y[x], y[x + 1], y[x + 2]);
+        if (corr) k[x] -= fstiff(c, v[x], v[x + 1], v[x + 2]);
+      }
+      store_rows<M>(c, ks, k);
+    }
+    if (useN) {
+      fe_rows<M>(c.fe, c.ce, y, k);
+      if (corr) {
+        fe_rows<M>(c.fe, c.ce, v, f);
+#pragma unroll
+        for (int x = 0; x < M; ++x) k[x] -= f[x];
+      }
+      store_rows<M>(c, ks + V, k);
+    }
   }
   double Y[M], rhs[M];
-  for (int i = 0; i < s; ++i) {
-    double* ss_p = L.ks + (int64_t)(2 * (s - 1)) * n;     // f^S(eta(t_n + c_i dt)), scratch
-    double* sn_p = ss_p + n;                              // f^N(eta(t_n + c_i dt)), scratch
-    // rhs = y_n + I_i + dt sum_{l<i} (AS K^S_l + AN K^N_l)
+  Edges<M> edge;     // neighbours of this thread's block of Y_i
+  for (int i = 1; i < s; ++i) {
+    const double tau = dt * L.AS[i][i];
+    // rhs = y_n + I_i - tau f^S(eta) + dt sum_{l<i} (AS K^S_l + AN K^N_l)
     load_rows<M>(c, yn_p, rhs);
-    double guess[M];
     if (corr) {
-      const double* w = L.wt + ((int64_t)rpos * s + i) * 2 * S;
-      double e[M + 2], q[M];
+      const gdbl* w = gp(L.wt) + ((int64_t)rpos * s + i) * 2 * S;
+      {
+        // eta; nodes of weight zero are not read (a stage at a node takes that node alone)
+        double e[M + 2], f[M];
 #pragma unroll
-      for (int k = 0; k < M + 2; ++k) e[k] = 0.0;
+        for (int k = 0; k < M + 2; ++k) e[k] = 0.0;
+        int at = slot0;
+        for (int k = 0; k < S; ++k) {
+          const double lk = w[k];
+          if (lk != 0.0) {
+            double v[M + 2];
+            load_halo<M, PER>(c, gp(L.prev) + at * V, v);
 #pragma unroll
-      for (int k = 0; k < M; ++k) q[k] = 0.0;
-      for (int k = 0; k < S; ++k) {
-        const int64_t slot = ((start + k) % L.R_prev) * (int64_t)n;
-        const double lk = w[k], qk = w[S + k];
-        double v[M + 2];
-        load_halo<M, PER>(c, L.prev + slot, v);
-#pragma unroll
-        for (int x = 0; x < M + 2; ++x) e[x] += lk * v[x];
-        double fv[M];
-        load_rows<M>(c, L.prevF + slot, fv);
-#pragma unroll
-        for (int x = 0; x < M; ++x) q[x] += qk * fv[x];
-      }
-      double ssv[M], snv[M];
-#pragma unroll
-      for (int x = 0; x < M; ++x) {
-        ssv[x] = fstiff(c, e[x], e[x + 1], e[x + 2]);
-        snv[x] = fe_eval(c.fe, c.ce, e[x], e[x + 1], e[x + 2]);
-        rhs[x] = rhs[x] + dt * q[x];
-        guess[x] = e[x + 1];
-      }
-      store_rows<M>(c, ss_p, ssv);
-      store_rows<M>(c, sn_p, snv);
-    } else {
-#pragma unroll
-      for (int x = 0; x < M; ++x) guess[x] = rhs[x];
-    }
-    for (int l = 0; l < i; ++l) {
-      const double as = dt * L.AS[i][l], an = dt * L.AN[i][l];
-      if (as == 0.0 && an == 0.0) continue;
-      double kS[M], kN[M];
-      load_rows<M>(c, L.ks + (int64_t)(2 * l) * n, kS);
-      load_rows<M>(c, L.ks + (int64_t)(2 * l + 1) * n, kN);
-#pragma unroll
-      for (int x = 0; x < M; ++x) rhs[x] = rhs[x] + (as * kS[x] + an * kN[x]);
-    }
-    const double a = L.AS[i][i];
-    double kS[M];   // f^S(Y_i), then K^S_i
-    Edges<M> e;     // neighbours of this thread's block of Y_i
-    if (a == 0.0) {
-      // stage 0 (c_0 = 0): Y_0 = y_n
-#pragma unroll
-      for (int x = 0; x < M; ++x) Y[x] = rhs[x];
-      e = edges<M, PER>(c, Y);
-#pragma unroll
-      for (int x = 0; x < M; ++x) {
-        double um, up;
-        nbrs<M, PER>(c, Y, x, e.l, e.r, e.w0, e.wn, um, up);
-        kS[x] = fstiff(c, um, Y[x], up);
-      }
-    } else {
-      const double tau = dt * a;
-      if (corr) {
-        double ssv[M];
-        load_rows<M>(c, ss_p, ssv);
-#pragma unroll
-        for (int x = 0; x < M; ++x) rhs[x] = rhs[x] - tau * ssv[x];
-      }
-#pragma unroll
-      for (int x = 0; x < M; ++x) Y[x] = guess[x];
-      constexpr bool kMem = M >= 16;
-      double* rhs_p = sn_p + n;                             // third scratch vector
-      if (kMem) store_rows<M>(c, rhs_p, rhs);
-      stage_solve<M, PER, kMem>(c, tau, L.maxit, rhs, rhs_p, Y);
-      if (kMem) load_rows<M>(c, rhs_p, rhs);
-      e = edges<M, PER>(c, Y);
-#pragma unroll
-      for (int x = 0; x < M; ++x) kS[x] = (Y[x] - rhs[x]) / tau;
-    }
-    if (i < s - 1) {
-      double kN[M], ssv[M], snv[M];
-      if (corr) {
-        load_rows<M>(c, ss_p, ssv);
-        load_rows<M>(c, sn_p, snv);
-      } else {
-#pragma unroll
-        for (int x = 0; x < M; ++x) ssv[x] = snv[x] = 0.0;
-      }
-#pragma unroll
-      for (int x = 0; x < M; ++x) {
-        double um, up;
-        nbrs<M, PER>(c, Y, x, e.l, e.r, e.w0, e.wn, um, up);
-        kS[x] = kS[x] - ssv[x];
-        kN[x] = fe_eval(c.fe, c.ce, um, Y[x], up) - snv[x];
-      }
-      store_rows<M>(c, L.ks + (int64_t)(2 * i) * n, kS);
-      store_rows<M>(c, L.ks + (int64_t)(2 * i + 1) * n, kN);
-    } else {
-      const int64_t slot = (m % L.R_own) * (int64_t)n;
-      store_rows<M>(c, L.own + slot, Y);
-      if (L.ownF) {
-        double f[M];
+            for (int x = 0; x < M + 2; ++x) e[x] += lk * v[x];
+          }
+          at = at + 1 == L.R_prev ? 0 : at + 1;
+        }
+        if (i < s - 1) {
+          fe_rows<M>(c.fe, c.ce, e, f);
+          store_rows<M>(c, sn_p, f);
+        }
 #pragma unroll
         for (int x = 0; x < M; ++x) {
-          double um, up;
-          nbrs<M, PER>(c, Y, x, e.l, e.r, e.w0, e.wn, um, up);
-          f[x] = fstiff(c, um, Y[x], up) + fe_eval(c.fe, c.ce, um, Y[x], up);
+          f[x] = fstiff(c, e[x], e[x + 1], e[x + 2]);
+          rhs[x] -= tau * f[x];
+          Y[x] = e[x + 1];
         }
-        store_rows<M>(c, L.ownF + slot, f);
+        if (i < s - 1) store_rows<M>(c, ss_p, f);
+      }
+      double q[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) q[k] = 0.0;
+      int at = slot0;
+      for (int k = 0; k < S; ++k) {
+        const double qk = w[S + k];
+        double fv[M];
+        load_rows<M>(c, gp(L.prevF) + at * V, fv);
+#pragma unroll
+        for (int x = 0; x < M; ++x) q[x] += qk * fv[x];
+        at = at + 1 == L.R_prev ? 0 : at + 1;
+      }
+#pragma unroll
+      for (int x = 0; x < M; ++x) rhs[x] = rhs[x] + dt * q[x];
+    } else {
+#pragma unroll
+      for (int x = 0; x < M; ++x) Y[x] = rhs[x];
+    }
+    for (int l = 0; l < 2 * i; ++l) {
+      const double al = dt * (l & 1 ? L.AN[i][l >> 1] : L.AS[i][l >> 1]);
+      if (al == 0.0) continue;
+      double k[M];
+      load_rows<M>(c, ks + l * V, k);
+#pragma unroll
+      for (int x = 0; x < M; ++x) rhs[x] += al * k[x];
+    }
+    // the largest blocks keep the right-hand side in LDS during the solve
+    constexpr bool kMem = M >= 16;
+    if constexpr (kMem) {
+#pragma unroll
+      for (int x = 0; x < M; ++x) c.rhs[x * c.T + c.t] = rhs[x];
+      stage_solve<M, PER>(c, tau, L.maxit, [&](int x) __attribute__((always_inline)) { return c.rhs[x * c.T + c.t]; }, Y, edge);
+    } else {
+      stage_solve<M, PER>(c, tau, L.maxit, [&](int x) __attribute__((always_inline)) { return rhs[x]; }, Y, edge);
+    }
+    if (i < s - 1) {
+      // K^S_i = (Y_i - rhs) / tau - f^S(eta), K^N_i = f^N(Y_i) - f^N(eta), where taken
+      taken(i, &useS, &useN);
+      if (useS) {
+        double k[M];
+#pragma unroll
+        for (int x = 0; x < M; ++x)
+          k[x] = (Y[x] - (kMem ? c.rhs[x * c.T + c.t] : rhs[x])) / tau;
+        if (corr) {
+          double v[M];
+          load_rows<M>(c, ss_p, v);
+#pragma unroll
+          for (int x = 0; x < M; ++x) k[x] -= v[x];
+        }
+        store_rows<M>(c, ks + 2 * i * V, k);
+      }
+      if (useN) {
+        double k[M], yh[M + 2];
+        with_halo<M, PER>(c, Y, edge, yh);
+        fe_rows<M>(c.fe, c.ce, yh, k);
+        if (corr) {
+          double v[M];
+          load_rows<M>(c, sn_p, v);
+#pragma unroll
+          for (int x = 0; x < M; ++x) k[x] -= v[x];
+        }
+        store_rows<M>(c, ks + (2 * i + 1) * V, k);
       }
     }
+  }
+  const int64_t slot = ring_slot(m, L.R_own) * V;
+  store_real<M>(c, gp(L.own) + slot, Y);
+  if (L.ownF) {
+    double f[M], yh[M + 2];
+    with_halo<M, PER>(c, Y, edge, yh);
+    fe_rows<M>(c.fe, c.ce, yh, f);
+#pragma unroll
+    for (int x = 0; x < M; ++x) f[x] += fstiff(c, yh[x], yh[x + 1], yh[x + 2]);
+    store_real<M>(c, gp(L.ownF) + slot, f);
   }
 }
 
@@ -605,10 +780,31 @@ __global__ __launch_bounds__(kImexMaxThreads) void k_imex1d(const ImexLvl* __res
   imex_step<M, PER>(items[blockIdx.x], sigma, init != 0, lds);
 }
 
+// Slot 0 of every level's ring from the initial data (block order, zero padding).
+__global__ void k_imex_load(const double* __restrict__ u0, ImexRings rings, int n, int M, int T) {
+  double* __restrict__ dst = rings.ring[blockIdx.y];
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < M * T; e += gridDim.x * blockDim.x) {
+    const int g = (e % T) * M + e / T;
+    dst[e] = g < n ? u0[g] : 0.0;
+  }
+}
+
+// A vector in block order to grid order; *flag set to 1 when a value is not finite.
+__global__ void k_imex_read(const double* __restrict__ src, double* __restrict__ dst, int n, int M,
+                            int T, int* flag) {
+  int bad = 0;
+  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < n; g += gridDim.x * blockDim.x) {
+    const double v = src[(g % M) * T + g / M];
+    dst[g] = v;
+    if (!(v - v == 0.0)) bad = 1;      // NaN or Inf
+  }
+  if (flag && __any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+}
+
 template <int M, bool PER>
 hipError_t launch_t(const ImexLvl* items, int count, int threads, int64_t sigma, bool init,
                     hipStream_t stream) {
-  const size_t lds = sizeof(double) * lds_doubles(PER ? 2 : 1, threads);
+  const size_t lds = sizeof(double) * lds_doubles(PER ? 2 : 1, M, threads);
   static size_t allowed = 65536;
   if (lds > allowed) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_imex1d<M, PER>),
@@ -636,14 +832,30 @@ hipError_t launch_m(int M, const ImexLvl* items, int count, int threads, int64_t
 }  // namespace
 
 void imex_shape(int64_t n, int* M, int* threads) {
-  // the fewest rows per thread that keep the workgroup within 512 threads (measured: longer
-  // per-thread blocks with fewer waves are slower at every size, the elimination chain and the
-  // register pressure outweighing the PCR stages saved)
+  // The fewest rows per thread that keep the workgroup within one wave per SIMD (256 threads), 8
+  // rows at most up to n = 4096.  Steps of RIDC4 with the cubic reaction, us, at 2 / 4 / 8 / 16 rows:
+  // n = 500 22.0 / 23.1 / 27.0 / 54.0, 999 35.9 / 25.5 / 29.0 / 54.0, 2000 - / 41.1 / 32.3 / 56.1, 4000
+  // - / - / 53.5 / 62.2 (two waves on a SIMD take turns; a longer block is a longer chain).
   int m = 2;
+  while (m < 8 && (n + m - 1) / m > 256) m *= 2;
   while (m < kImexMaxRows && (n + m - 1) / m > kImexMaxThreads) m *= 2;
   const int64_t t = (n + m - 1) / m;
   *M = m;
   *threads = (int)((t + 63) / 64 * 64);
+}
+
+hipError_t launch_imex_load(const double* u0, const ImexRings& rings, int P, int n, int M, int T,
+                            hipStream_t stream) {
+  hipLaunchKernelGGL(k_imex_load, dim3((M * T + 255) / 256, P), dim3(256), 0, stream, u0, rings, n,
+                     M, T);
+  return hipGetLastError();
+}
+
+hipError_t launch_imex_read(const double* src, double* dst, int n, int M, int T, int* flag,
+                            hipStream_t stream) {
+  hipLaunchKernelGGL(k_imex_read, dim3((n + 255) / 256), dim3(256), 0, stream, src, dst, n, M, T,
+                     flag);
+  return hipGetLastError();
 }
 
 hipError_t launch_imex1d(const ImexLvl* d_items, int count, int M, int threads, bool periodic,

@@ -181,7 +181,7 @@ constexpr int kImexMaxRows = 16;       // rows per thread at most: n <= 8192
 // One (instance, level) work item.  The level computes t_m, m = sigma - sigma0 - delay, at
 // launch step sigma (1 <= m <= nt).
 struct ImexLvl {
-  double* own;            // level values: R_own slots of n
+  double* own;            // level values: R_own slots of M * T (block order)
   double* ownF;           // f^S + f^N of the level values, same slots; null for the top level
   const double* prev;     // previous level's values (R_prev slots); null for the predictor
   const double* prevF;    // previous level's f
@@ -199,6 +199,17 @@ struct ImexLvl {
 // Rows per thread (2, 4, 8 or 16) and threads per workgroup (a multiple of 64, at most 512)
 // of the IMEX level step for n unknowns.
 void imex_shape(int64_t n, int* M, int* threads);
+
+// Ring vectors of an IMEX handle hold M * T doubles in block order (row i of thread t's block, grid
+// row t M + i, at i T + t; padding rows zero).  Slot 0 of P rings from u0, and a ring vector back
+// to grid order (flag, nullable: set to 1 when a value is not finite).
+struct ImexRings {
+  double* ring[kMaxOrder];
+};
+hipError_t launch_imex_load(const double* u0, const ImexRings& rings, int P, int n, int M, int T,
+                            hipStream_t stream);
+hipError_t launch_imex_read(const double* src, double* dst, int n, int M, int T, int* flag,
+                            hipStream_t stream);
 
 // One launch over d_items[0..count) (all of the shape M, threads and of one boundary kind) at
 // launch step sigma; init: instead, write f of every level's initial value (slot 0).

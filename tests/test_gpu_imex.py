@@ -186,3 +186,24 @@ def test_full_length_workloads(env, which):
     else:
         prob, u0 = workloads.config_stiff_1d()
     check(env, prob, u0, prob["nt"])
+
+
+# the level step's shapes: 2, 4, 8 or 16 rows per thread (n up to 512, 1024, 4096, 8192), groups of
+# 16 threads (one, a part of one, up to 16, more than 16), rows of 16 groups, padding rows in the
+# last block, whole blocks, and a last row that ends a block, a wave or the workgroup
+@pytest.mark.parametrize("n", [2, 3, 32, 33, 128, 511, 512, 513, 1024, 1025, 2048, 2049, 4096, 4099,
+                               8191])
+@pytest.mark.parametrize("kind", ["dirichlet", "periodic", "newton"])
+def test_level_step_shapes(env, kind, n):
+    if kind == "newton":
+        prob, u0 = workloads.config_stiff_1d(n=n, nt=400, order=2, kappa=500.0,
+                                             pairs=("ark3", "fbe"))
+    elif kind == "periodic":
+        prob, _ = workloads.config_advdiff_1d(n=n, nt=400, order=2)
+        u0 = workloads.fourier_modes_1d(n, np.random.default_rng(n))
+        prob["pairs"] = ["fbe", "ark3"]
+    else:
+        prob, u0 = workloads.config_reacdiff_1d(n=n, nt=400, order=2)
+        prob["pairs"] = ["fbe", "ark4"]
+        u0 = u0 + 0.1
+    check(env, prob, u0, 6)
