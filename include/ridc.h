@@ -263,7 +263,7 @@ int ridc_autotune(ridc_handle* h, int32_t* threads_out, int32_t* rows_out, int32
  * shorter than the system); flags bit 0 = write level values with nontemporal stores; flags
  * bit 1 = one workgroup of `threads` (512 or 1024, rows 0) runs every level and many pipeline
  * steps in one launch (needs the levels' cycles to fit one CU's LDS; order <= 6 with 512
- * threads, order <= 4 with 1024).
+ * threads, order <= 4 with 1024; up to 256 rows the rings are held there too).
  * Errors: RIDC_E_INVAL if the tiling does not fit.                                            */
 int ridc_set_tile(ridc_handle* h, int32_t threads, int32_t rows, int32_t flags);
 
@@ -273,7 +273,8 @@ int ridc_set_tile(ridc_handle* h, int32_t threads, int32_t rows, int32_t flags);
  * level's whole cycle in one workgroup whenever it fits; rows >= 256 cuts longer cycles into
  * chunks whose rows plus PCR halos stay within `rows` (systems whose halo is too long for that
  * keep whole cycles).  Like every tiling it does not change results (section III-E's pipeline
- * and the solves are computed the same way).  Default: 256 threads, rows 0.
+ * and the solves are computed the same way).  Until one is set or measured, each grouped launch
+ * takes a tiling by the rows it covers.
  * Errors: RIDC_E_INVAL for other values.                                                      */
 int ridc_set_batch_tile(int32_t threads, int32_t rows);
 

@@ -68,6 +68,11 @@ struct ridc_handle {
   size_t fused_lds = 0;
   Fused1D fused_item{};
   Fused1D* d_fused = nullptr;
+  // small systems run whole ranges of steps in one workgroup with the rings in LDS (k_small1d):
+  // possible, and in use for an untuned handle that no larger one is grouped with (with the
+  // whole-range workgroup set, always)
+  bool small_ok = false, small = false;
+  size_t small_lds = 0;
   size_t blocks_cap = 0;
   size_t lds = 0;
 
@@ -164,6 +169,7 @@ std::mutex g_tune_mu;
 struct BatchTile {
   int threads = 256;
   int rows = 0;
+  bool automatic = true;   // nothing set or measured: stage_batch_1d picks one for each group
 };
 BatchTile g_batch_tile;
 bool g_batch_tile_set = false;
@@ -172,7 +178,7 @@ BatchTile current_batch_tile() {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   if (!g_batch_tile_set) {
     int t = 0, r = 0;
-    if (tune_get_batch(&t, &r)) g_batch_tile = BatchTile{t, r};
+    if (tune_get_batch(&t, &r)) g_batch_tile = BatchTile{t, r, false};
     g_batch_tile_set = true;
   }
   return g_batch_tile;
@@ -249,25 +255,28 @@ int choose_tile_1d(const ridc_problem* p, const PcrPlan& pcr, Tile1D* out,
     return RIDC_OK;
   }
   const int64_t H = halo_rows(pcr);
-  // default for long systems with a short PCR halo: chunks, as many as give about 256
-  // workgroups per step over the levels (one per CU: a single system's step is bound by
-  // latency, not bytes), at least 128 rows each, 1024 threads where the order allows
-  // (measured at n = 8192, order 4: 128-row chunks of 1024 threads run a step in 5.3 us,
-  // 1024-row chunks of 256 threads in 10.8).  The whole-range workgroup is left to
-  // measurement: ridc_autotune, ridc_set_tile.
-  if (p->n >= 2048 && H <= 512) {
+  const int64_t ms = p->bc == RIDC_BC_PERIODIC ? p->n : p->n + 2;
+  // Default: chunks, as many as give about 256 workgroups per step over the levels (one per CU: a
+  // single system's step is bound by latency, not bytes), at least 128 rows each, 1024 threads
+  // where the order allows (512 above), while a chunk with its halos is no longer than twice the
+  // system.  Step times, us, of 128-row chunks against the whole cycle in 256 threads, order 4: n =
+  // 300 3.6 / 5.9, 999 4.2 / 11.6, 1500 4.2 / 15.4, 2000 4.5 / 20.9; order 8, n = 1024: 4.5 / 10.9.  Against
+  // 1024-row chunks of 256 threads at n = 8192: 5.3 / 10.8.  Whole-range workgroups are chosen in
+  // ridc_create (small systems), by ridc_autotune or by ridc_set_tile.
+  {
     const int64_t per_level = std::max<int64_t>(1, 256 / p->order);
     int64_t B = (p->n / per_level) / 64 * 64;
     B = std::min<int64_t>(1024, std::max<int64_t>(128, B));
-    const int threads = p->order <= kMaxJ1024 + 1 ? 1024 : 256;
-    Tile1D chunk{0, (int)B, threads};
-    if (tile_fits(p, pcr, chunk)) {
+    const Tile1D chunk{0, (int)B, p->order <= kMaxJ1024 + 1 ? 1024 : 512};
+    if (B + 2 * H <= 2 * ms && tile_fits(p, pcr, chunk)) {
       *out = chunk;
       return RIDC_OK;
     }
   }
   Tile1D chunk{0, 1024, 256};
-  Tile1D wrap{1, 0, 256};
+  // whole cycles: more threads for longer ones
+  const int big = p->order <= kMaxJ1024 + 1 ? 1024 : 512;
+  Tile1D wrap{1, 0, ms <= 256 ? 256 : (ms <= 512 ? 512 : big)};
   if (tile_fits(p, pcr, wrap)) {
     *out = wrap;
     return RIDC_OK;
@@ -577,13 +586,23 @@ int launch_fused_steps(ridc_handle* h, int64_t first, int64_t last) {
   F.sigma0 = 0;
   F.sigma_first = first - 1;
   F.sigma_last = last;
-  RIDC_HIP_TRY(launch_fused_1d(nullptr, &F, 1, h->P, h->fused_threads, h->fused_lds, h->stream));
+  if (!h->small_ok) {
+    RIDC_HIP_TRY(launch_fused_1d(nullptr, &F, 1, h->P, h->fused_threads, h->fused_lds, h->stream));
+    return RIDC_OK;
+  }
+  // at most 2^16 steps (0.2 s) a launch: the default for small systems holds the stream's other work
+  // up no longer
+  for (int64_t f = first - 1; f < last; f += 1 << 16) {
+    F.sigma_first = f;
+    F.sigma_last = std::min<int64_t>(last, f + (1 << 16));
+    RIDC_HIP_TRY(launch_small_1d(nullptr, &F, 1, h->P, h->small_lds, h->stream));
+  }
   return RIDC_OK;
 }
 
 int run_solo_steps(ridc_handle* h, int64_t first, int64_t last) {
   if (h->imex) return launch_imex_steps(h, first, last);
-  if (h->p.dim == 1 && h->fused) return launch_fused_steps(h, first, last);
+  if (h->p.dim == 1 && (h->fused || h->small)) return launch_fused_steps(h, first, last);
   if (h->p.dim == 1) return launch_solo_steps_1d(h, first, last);
   Plan2D* pl = h->p2;
   const int64_t before = first - 1;
@@ -602,6 +621,7 @@ int check_handles(ridc_handle* const* hs, int32_t count) {
 
 int apply_tile_1d(ridc_handle* h, const Tile1D& t) {
   if (!tile_fits(&h->p, h->pcr, t)) return fail(RIDC_E_INVAL, "tile does not fit this system");
+  h->small = false;                    // a tiling was asked for
   if (t.fused) {
     const FusedPlan fp = plan_fused(&h->p, t.fused);
     h->fused = true;
@@ -700,6 +720,18 @@ Tile1D batch_tile_for(const ridc_handle* h, const BatchTile& bt, int threads) {
   return Tile1D{-1, 0, threads};
 }
 
+// The grouped tiling of a launch over `level_rows` rows of all levels when none was set or measured:
+// the fewer rows there are to fill the chip with, the finer the cut.  Step times, us, of (threads,
+// rows) choices: 1.6e6 rows (256 instances, n 256..4096, order 4) (256, 1536) 20.2, (512, 768) 23, whole
+// cycles in 256 threads 34.9; 4e5 rows (512, 768) 9.7, (256, 1536) 12, whole 30.6; 1e5 rows (512, 512)
+// 6.6, (512, 1536) 8.9, whole 29.2; 2.5e4 rows (512, 384) 5.7, (512, 1536) 8.0, whole 27.1.
+BatchTile default_batch_tile(int64_t level_rows) {
+  if (level_rows >= 800000) return BatchTile{256, 1536, false};
+  if (level_rows >= 200000) return BatchTile{512, 768, false};
+  if (level_rows >= 50000) return BatchTile{512, 512, false};
+  return BatchTile{512, 384, false};
+}
+
 struct BatchStage {
   int nblocks = 0, threads = 256, maxP = 1;
   size_t lds = 0;
@@ -708,10 +740,15 @@ struct BatchStage {
 // Fill and upload the item and block tables of one grouped launch over the 1D handles hs.
 // Normal use: each handle's own step = launch step + its current sigma.  timing: every level
 // active from its start-up step on and never finishing (the rings are scratch).
-int stage_batch_1d(const std::vector<ridc_handle*>& hs, const BatchTile& bt, bool timing,
+int stage_batch_1d(const std::vector<ridc_handle*>& hs, const BatchTile& asked, bool timing,
                    hipStream_t stream, BatchStage* out) {
   BatchStage st;
-  for (auto* h : hs) st.maxP = std::max(st.maxP, h->P);
+  int64_t level_rows = 0;
+  for (auto* h : hs) {
+    st.maxP = std::max(st.maxP, h->P);
+    level_rows += h->P * h->p.n;
+  }
+  const BatchTile bt = asked.automatic ? default_batch_tile(level_rows) : asked;
   st.threads = bt.threads;
   if (st.threads == 1024 && st.maxP > kMaxJ1024 + 1) st.threads = 512;
   std::vector<Tile1D> tiles(hs.size());
@@ -1177,6 +1214,18 @@ int ridc_create(const ridc_problem* p, void* hip_stream, ridc_handle** out) {
       F.nu_h2 = h->solo.nu_h2;
       F.inv_divisor = 1.0 / h->pcr.divisor;
     }
+    {
+      Tile1D tuned;
+      int slots = 0;
+      for (int j = 0; j < h->P; ++j) slots += h->R[j];
+      if (p->n <= kSmallRows && h->P <= kMaxJ1024 + 1) {
+        h->small_lds = lds_bytes_small_1d((int)p->n, slots, h->P);
+        const int max_lds = device_max_lds();
+        h->small_ok = h->small_lds <= (size_t)max_lds &&
+                      prepare_small_1d(h->fused_item, max_lds) == hipSuccess;
+      }
+      h->small = h->small_ok && !tuned_tile(p->n, p->bc, h->pcr.stages, &tuned);
+    }
     if (hipMemcpy(h->d_blocks, h->blocks.data(), sizeof(Blk1D) * h->blocks.size(),
                   hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(h->d_items, h->proto.data(), sizeof(Lvl1D) * h->proto.size(),
@@ -1401,23 +1450,29 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
   }
   // fused-eligible 1D handles: one workgroup each, every requested step in one launch
   {
-    std::vector<ridc_handle*> hf, hs;
+    std::vector<ridc_handle*> hf, hm, hs;
     // batches keep the GPU busy with one launch per step (measured faster than whole-range
-    // workgroups); a handle tuned to the whole-range workgroup keeps it
-    for (auto* h : h1) (h->fused ? hf : hs).push_back(h);
+    // workgroups); a handle tuned to the whole-range workgroup keeps it, and small systems among
+    // themselves take it (a workgroup each: a step costs no more than it does alone)
+    bool all_small = true;
+    for (auto* h : h1) all_small = all_small && h->small;
+    for (auto* h : h1) (h->fused || all_small ? (h->small_ok ? hm : hf) : hs).push_back(h);
     h1.swap(hs);
-    if (!hf.empty()) {
+    for (auto* list : {&hf, &hm}) {
+      const std::vector<ridc_handle*>& hw = *list;
+      if (hw.empty()) continue;
+      const bool small = list == &hm;
       rc = arena_reserve(1, 1, stream);
       if (rc != RIDC_OK) return rc;
-      rc = arena_reserve_fused(hf.size());
+      rc = arena_reserve_fused(hw.size());
       if (rc != RIDC_OK) return rc;
       int maxP = 1;
       size_t lds = 0;
-      for (size_t i = 0; i < hf.size(); ++i) {
-        ridc_handle* h = hf[i];
+      for (size_t i = 0; i < hw.size(); ++i) {
+        ridc_handle* h = hw[i];
         maxP = std::max(maxP, h->P);
         const FusedPlan fp = plan_fused(&h->p, 512);
-        lds = std::max(lds, fp.lds);
+        lds = std::max(lds, small ? h->small_lds : fp.lds);
         Fused1D F = h->fused_item;
         F.group = fp.group;
         F.nt = h->nt;
@@ -1426,15 +1481,18 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
         F.sigma_last = std::min(h->total, h->sigma + max_steps);
         g_arena.h_fused[i] = F;
       }
-      RIDC_HIP_TRY(hipMemcpyAsync(g_arena.d_fused, g_arena.h_fused, sizeof(Fused1D) * hf.size(),
+      RIDC_HIP_TRY(hipMemcpyAsync(g_arena.d_fused, g_arena.h_fused, sizeof(Fused1D) * hw.size(),
                                   hipMemcpyHostToDevice, stream));
       RIDC_HIP_TRY(hipEventRecord(g_arena.done, stream));
       g_arena.pending = true;
-      RIDC_HIP_TRY(launch_fused_1d(g_arena.d_fused, nullptr, (int)hf.size(), maxP, 512, lds,
-                                   stream));
+      if (small)
+        RIDC_HIP_TRY(launch_small_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, lds, stream));
+      else
+        RIDC_HIP_TRY(launch_fused_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, 512, lds,
+                                     stream));
       rc = arena_release(stream);
       if (rc != RIDC_OK) return rc;
-      for (auto* h : hf) h->sigma = std::min(h->total, h->sigma + max_steps);
+      for (auto* h : hw) h->sigma = std::min(h->total, h->sigma + max_steps);
     }
   }
   if (!h1.empty()) {
@@ -1792,7 +1850,7 @@ int ridc_set_batch_tile(int32_t threads, int32_t rows) {
     return fail(RIDC_E_INVAL, "batch threads must be 256, 512 or 1024");
   if (rows < 0 || (rows > 0 && rows < 256)) return fail(RIDC_E_INVAL, "batch rows: 0 or >= 256");
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_batch_tile = BatchTile{threads, rows};
+  g_batch_tile = BatchTile{threads, rows, false};
   g_batch_tile_set = true;
   return RIDC_OK;
 }
@@ -1810,7 +1868,7 @@ int ridc_autotune_batch(ridc_handle* const* hs, int32_t count, int32_t* threads_
     int t = 0, r = 0;
     if (tune_get_batch(&t, &r)) {
       std::lock_guard<std::mutex> lk(g_tune_mu);
-      g_batch_tile = BatchTile{t, r};
+      g_batch_tile = BatchTile{t, r, false};
       g_batch_tile_set = true;
       if (threads_out) *threads_out = t;
       if (rows_out) *rows_out = r;
@@ -1838,7 +1896,7 @@ int ridc_autotune_batch(ridc_handle* const* hs, int32_t count, int32_t* threads_
     constexpr int kReps = 20;
     for (int T : {256, 512, 1024})
       for (int rows : {0, 512, 768, 1024, 1536, 2048, 4096}) {
-        const BatchTile bt{T, rows};
+        const BatchTile bt{T, rows, false};
         BatchStage st;
         rc = stage_batch_1d(h1, bt, true, stream, &st);
         if (rc != RIDC_OK) break;
@@ -1862,7 +1920,7 @@ int ridc_autotune_batch(ridc_handle* const* hs, int32_t count, int32_t* threads_
         }
         if (ms < best_ms) {
           best_ms = ms;
-          best = BatchTile{st.threads, rows};
+          best = BatchTile{st.threads, rows, false};
         }
       }
     (void)hipEventDestroy(a);

@@ -23,6 +23,8 @@
 // and carries a halo of 2^K - 1 rows on each side, recomputing the halo's right-hand side; the
 // valid region shrinks by 2^k per stage.  Both modes perform the same operations on the same
 // values for every output row, so results do not depend on the tiling.
+#include <type_traits>
+
 #include "ridc_internal.h"
 
 namespace ridc {
@@ -49,13 +51,32 @@ __device__ __forceinline__ double pcr_upd(double c, double a, double b, double g
   return __builtin_fma(-g, a + b, c);
 }
 
+// The arithmetic of a right-hand-side row.  Every kernel that computes one uses these functions, with
+// the products and sums fused as written here and nowhere else, so that their bits agree.
 // f_E at one point from its neighbours; ce is explicit_coeff(fe, a, h).
 __device__ __forceinline__ double fe_eval(int fe, double ce, double um, double u0, double up) {
+#pragma clang fp contract(off)
   if (fe == RIDC_FE_ADVECT_C2) return -ce * (up - um);
   if (fe == RIDC_FE_LOGISTIC) return u0 * (1.0 - u0);
   if (fe == RIDC_FE_ADVECT_UPWIND) return ce >= 0.0 ? -ce * (u0 - um) : -ce * (up - u0);
   if (fe == RIDC_FE_BURGERS) return -ce * (up * up - um * um);
   return 0.0;
+}
+// u + dt f_E(u)
+__device__ __forceinline__ double row_start(int fe, double ce, double dt, double um, double u0,
+                                            double up) {
+  return __builtin_fma(dt, fe_eval(fe, ce, um, u0, up), u0);
+}
+// acc + cf f_E(v) + cl L v for one window value (f: f_E(v))
+__device__ __forceinline__ double row_sum(double acc, double nu_h2, double cf, double cl, double vm,
+                                          double v0, double vp, double f) {
+#pragma clang fp contract(off)
+  const double li = nu_h2 * ((vm + vp) - 2.0 * v0);
+  return __builtin_fma(cf, f, __builtin_fma(cl, li, acc));
+}
+__device__ __forceinline__ double row_add(double acc, int fe, double ce, double nu_h2, double cf,
+                                          double cl, double vm, double v0, double vp) {
+  return row_sum(acc, nu_h2, cf, cl, vm, v0, vp, fe_eval(fe, ce, vm, v0, vp));
 }
 
 // Per-workgroup view of one level step of level J: where the level's value and the previous
@@ -134,7 +155,7 @@ __device__ __forceinline__ void rhs_rows_bc(const Geo& G, const Step<J>& S, int 
       um = up;
       up = t;
     }
-    double acc = u0 + G.dt * fe_eval(G.fe, G.ce, um, u0, up);
+    double acc = row_start(G.fe, G.ce, G.dt, um, u0, up);
 #pragma unroll
     for (int i = 0; i < (J > 0 ? J + 1 : 0); ++i) {
       double vm = from_lane_below(v0[i]), vp = from_lane_above(v0[i]);
@@ -143,8 +164,7 @@ __device__ __forceinline__ void rhs_rows_bc(const Geo& G, const Step<J>& S, int 
         vm = vp;
         vp = t;
       }
-      const double li = G.nu_h2 * ((vm + vp) - 2.0 * v0[i]);
-      acc += S.cf[i] * fe_eval(G.fe, G.ce, vm, v0[i], vp) + S.cl[i] * li;
+      acc = row_add(acc, G.fe, G.ce, G.nu_h2, S.cf[i], S.cl[i], vm, v0[i], vp);
     }
     if (lane >= 1 && lane <= 62 && l < count) d[l] = ghost ? 0.0 : (mir ? -acc : acc);
   }
@@ -179,6 +199,13 @@ __device__ __forceinline__ void store_row(gdbl* p, double v, bool nt) {
     *p = v;
 }
 
+// m mod R.  A step's index fits 32 bits in all but the longest runs, and a 64-bit remainder is some
+// hundred dependent instructions at the head of every step (4.29 -> 4.16 us at n = 999, order 4).
+__device__ __forceinline__ int ring_slot(int64_t m, int R) {
+  if ((uint64_t)m >> 32 == 0) return (int)((uint32_t)m % (uint32_t)R);
+  return (int)(m % R);
+}
+
 // Geometry and this step's window of a level (shared by the per-step and the fused kernels).
 template <int J>
 __device__ __forceinline__ void make_step(const View& L, int64_t m, Geo& G, Step<J>& S) {
@@ -191,13 +218,15 @@ __device__ __forceinline__ void make_step(const View& L, int64_t m, Geo& G, Step
   G.nu_h2 = L.nu_h2;
   const int n = G.n;
   const int64_t nidx = m - 1;
-  S.u = L.own + (nidx % L.R_own) * (int64_t)n;
-  S.out = L.own + (m % L.R_own) * (int64_t)n;
+  int su = ring_slot(nidx, L.R_own);
+  S.u = L.own + su * (int64_t)n;
+  su = su + 1 == L.R_own ? 0 : su + 1;
+  S.out = L.own + su * (int64_t)n;
   if constexpr (J > 0) {
     const int64_t s = m - J > 0 ? m - J : 0;          // window t_s..t_{s+J}
     const gdbl* w = L.W + (nidx - s) * (J + 1);       // row r = n - s
     const int R = L.R_prev;
-    int slot = (int)(s % R);
+    int slot = ring_slot(s, R);
 #pragma unroll
     for (int i = 0; i <= J; ++i) {
       S.v[i] = L.prev + (int64_t)slot * n;
@@ -470,7 +499,7 @@ __device__ __forceinline__ void fused_body(const Fused1D& F) {
       d1 = t;
     }
     if (act) {
-      gdbl* out = gp(F.ring[j]) + (m % F.R[j]) * (int64_t)n;
+      gdbl* out = gp(F.ring[j]) + ring_slot(m, F.R[j]) * (int64_t)n;
       for (int l = l0 + lt; l < l1; l += G) out[per ? l : l - 1] = d0[l] * F.inv_divisor;
     }
     __syncthreads();                         // this step's values before the next step reads
@@ -488,6 +517,249 @@ __global__ __launch_bounds__(FT) void k_fused1d_one(const Fused1D F) {
   fused_body<MJ>(F);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Small systems: one workgroup, one wave per level, runs a range of pipeline steps with the level
+// rings in LDS.  Lane `lane` of level j's wave owns the rows r 64 + lane, r < R.  A ring slot holds n
+// + 2 values, grid row i at i + 1; its ends are the ghost rows (Dirichlet: zero; periodic: copies of
+// rows n-1 and 0).  A wave's LDS accesses execute in order, so the PCR stages of a level need no
+// barrier and one buffer: every row's partners are read before any row is written.  One workgroup
+// barrier per pipeline step.  The rings are loaded before the first step and stored after the last,
+// so that steps by other kernels may come before and after.  The arithmetic of every row is that of
+// level_step.
+// Bound: latency (LDS round trips, seven stages at n = 128).  Per step, us, against one launch per
+// step of 128-row chunks or whole cycles (3.4-4.5 whatever the size, the launch itself 1.6) at order
+// 4: n = 64 0.87, 128 1.30, 256 2.2 (orders 1 and 6: 1.55 and 3.1).  With eight rows a lane (n up to 512)
+// the rows' registers spill and a step takes 2.5-3.1 at order 1 but 3.9-5.2 at order 4, against 3.2 and
+// 3.9-4.5 of the chunks, so those sizes stay with them.
+// ---------------------------------------------------------------------------------------------
+// LDS accesses of one wave before and after this point stay in this order.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+struct SmallLvl {
+  double* own;          // ring of the level in LDS
+  const double* prev;   // ring of the level below
+  double* buf;          // solve buffer: cycle rows (n + 2 values)
+  const double* W;      // weights of the level
+  int su, sw, sp;       // slots of t_{m-1}, t_m, and of the window's first node in prev
+  int R_prev;
+};
+
+// f_E at K points at once (the kind is branched on once)
+template <int K>
+__device__ __forceinline__ void fe_points(int fe, double ce, const double (&m)[K],
+                                          const double (&u)[K], const double (&p)[K],
+                                          double (&out)[K]) {
+  auto all = [&](auto kind) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) out[i] = fe_eval(decltype(kind)::value, ce, m[i], u[i], p[i]);
+  };
+  if (fe == RIDC_FE_ADVECT_C2) all(std::integral_constant<int, RIDC_FE_ADVECT_C2>{});
+  else if (fe == RIDC_FE_LOGISTIC) all(std::integral_constant<int, RIDC_FE_LOGISTIC>{});
+  else if (fe == RIDC_FE_ADVECT_UPWIND) all(std::integral_constant<int, RIDC_FE_ADVECT_UPWIND>{});
+  else if (fe == RIDC_FE_BURGERS) all(std::integral_constant<int, RIDC_FE_BURGERS>{});
+  else all(std::integral_constant<int, RIDC_FE_NONE>{});
+}
+
+// Every step of level J in sigma_first+1 .. sigma_last: one barrier per step, whether the level is
+// active or not.
+template <int J, int R, bool PER>
+__device__ __forceinline__ void small_run(const Fused1D& F, SmallLvl L, int lane, double gam,
+                                          int shift) {
+  const int n = F.n, M = F.M, st = n + 2, stages = F.stages;
+  constexpr int g0 = PER ? 0 : 1;    // cycle row of grid row 0
+  constexpr int K = J > 0 ? (J + 2) * R : R;
+  const int Ro = F.R[J];
+  int row[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) row[r] = r * 64 + lane < n ? r * 64 + lane : n - 1;
+  double cf[J + 1], cl[J + 1];
+  int64_t m = F.sigma_first + 1 - F.sigma0 - (int64_t)J * (J + 1) / 2;
+  bool fresh = true;
+  for (int64_t sigma = F.sigma_first + 1; sigma <= F.sigma_last; ++sigma, ++m) {
+    if (m >= 1 && m <= F.nt) {
+      L.sw = L.su + 1 == Ro ? 0 : L.su + 1;
+      if (J > 0 && (fresh || m <= J + 1)) {
+        // the window's coefficients: those of the start-up rows, then the steady ones
+        const int64_t nidx = m - 1, s = m - J > 0 ? m - J : 0;
+        const double* w = L.W + (int)(nidx - s) * (J + 1);
+#pragma unroll
+        for (int i = 0; i <= J; ++i) {
+          const double wi = w[i];
+          cf[i] = F.dt * (wi - (s + i == nidx ? 1.0 : 0.0));
+          cl[i] = F.dt * (wi - (s + i == nidx + 1 ? 1.0 : 0.0));
+        }
+        fresh = false;
+      }
+      // points: the R rows of the own value, then of each window value
+      double a[K], b[K], c[K], f[K];
+      const double* u = L.own + L.su * st;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        a[r] = u[row[r]];
+        b[r] = u[row[r] + 1];
+        c[r] = u[row[r] + 2];
+      }
+      if constexpr (J > 0) {
+        int slot = L.sp;
+#pragma unroll
+        for (int i = 0; i <= J; ++i) {
+          const double* v = L.prev + slot * st;
+          slot = slot + 1 == L.R_prev ? 0 : slot + 1;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            a[(i + 1) * R + r] = v[row[r]];
+            b[(i + 1) * R + r] = v[row[r] + 1];
+            c[(i + 1) * R + r] = v[row[r] + 2];
+          }
+        }
+      }
+      fe_points<K>(F.fe, F.ce, a, b, c, f);
+      double x[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        x[r] = __builtin_fma(F.dt, f[r], b[r]);
+        if constexpr (J > 0) {
+#pragma unroll
+          for (int i = 0; i <= J; ++i) {
+            const int k = (i + 1) * R + r;
+            x[r] = row_sum(x[r], F.nu_h2, cf[i], cl[i], a[k], b[k], c[k], f[k]);
+          }
+        }
+      }
+      // PCR over the cycle: periodic rows g = i of n; Dirichlet rows g = i + 1 of the odd extension,
+      // rows 0 and n + 1 zero
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (r * 64 + lane < n) L.buf[r * 64 + lane + g0] = x[r];
+      for (int k = 0; k < stages; ++k) {
+        const int sh = __builtin_amdgcn_readlane(shift, k);
+        const double g = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(gam), k),
+                                          __builtin_amdgcn_readlane(__double2loint(gam), k));
+        wave_order();
+        double p[R], q[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          int ia = row[r] + g0 - sh, ib = row[r] + g0 + sh;
+          if (ia < 0) ia += M;
+          if (ib >= M) ib -= M;
+          if constexpr (PER) {
+            p[r] = L.buf[ia];
+            q[r] = L.buf[ib];
+          } else {
+            const bool fa = ia > n + 1, fb = ib > n + 1;
+            p[r] = L.buf[fa ? M - ia : ia];
+            q[r] = L.buf[fb ? M - ib : ib];
+            p[r] = fa ? -p[r] : p[r];
+            q[r] = fb ? -q[r] : q[r];
+          }
+        }
+        wave_order();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          x[r] = pcr_upd(x[r], p[r], q[r], g);
+          if (r * 64 + lane < n) L.buf[r * 64 + lane + g0] = x[r];
+        }
+      }
+      double* out = L.own + L.sw * st;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = r * 64 + lane;
+        const double y = x[r] * F.inv_divisor;
+        if (i < n) {
+          out[i + 1] = y;
+          if (PER && i == 0) out[n + 1] = y;
+          if (PER && i == n - 1) out[0] = y;
+        }
+      }
+      L.su = L.sw;
+      if (m >= J) L.sp = L.sp + 1 == L.R_prev ? 0 : L.sp + 1;
+    }
+    __syncthreads();                         // this step's values before the next step reads
+  }
+}
+
+template <int MJ, int R, bool PER>
+__device__ __forceinline__ void small_rows(const Fused1D& F) {
+  extern __shared__ double lds[];
+  const int lane = threadIdx.x & 63;
+  const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // this wave's level
+  if (j >= F.P) {                            // a grouped launch's deeper items: barriers only
+    __syncthreads();
+    for (int64_t sigma = F.sigma_first + 1; sigma <= F.sigma_last; ++sigma) __syncthreads();
+    return;
+  }
+  const int n = F.n, st = n + 2;
+  int slots = 0, before = 0, below = 0, woff = 0;
+  for (int q = 0; q < F.P; ++q) {
+    if (q < j) {
+      below = slots;
+      woff += q * (q + 1);
+    }
+    if (q == j) before = slots;
+    slots += F.R[q];
+  }
+  const int Ro = F.R[j];
+  SmallLvl L;
+  L.own = lds + before * st;
+  L.prev = lds + below * st;
+  L.buf = lds + (slots + j) * st;
+  double* wl = lds + (slots + F.P) * st + woff;
+  L.W = wl;
+  L.R_prev = j > 0 ? F.R[j - 1] : 1;
+  for (int q = 0; q < Ro; ++q)
+    for (int i = lane; i < st; i += 64) {
+      const int g = i == 0 ? (PER ? n - 1 : -1) : (i == n + 1 ? (PER ? 0 : -1) : i - 1);
+      L.own[q * st + i] = g >= 0 ? gp(F.ring[j])[(int64_t)q * n + g] : 0.0;
+    }
+  for (int i = lane; i < st; i += 64) L.buf[i] = 0.0;
+  if (lane < j * (j + 1)) wl[lane] = gp(F.W[j])[lane];
+  // the stages' coefficients and shifts, one per lane
+  const int sl = lane < F.stages ? lane : 0;
+  const double gam = gp(F.gamma)[sl];
+  const int shift = gp(F.shift)[sl];
+  int64_t m = F.sigma_first + 1 - F.sigma0 - (int64_t)j * (j + 1) / 2;
+  const int64_t m0 = m > 1 ? m : 1;          // first step this level takes here
+  L.su = ring_slot(m0 - 1, Ro);
+  L.sp = j > 0 ? ring_slot(m0 > j ? m0 - j : 0, L.R_prev) : 0;
+  __syncthreads();
+  switch (j) {
+    case 0: small_run<0, R, PER>(F, L, lane, gam, shift); break;
+    case 1: if constexpr (MJ >= 1) small_run<1, R, PER>(F, L, lane, gam, shift); break;
+    case 2: if constexpr (MJ >= 2) small_run<2, R, PER>(F, L, lane, gam, shift); break;
+    case 3: if constexpr (MJ >= 3) small_run<3, R, PER>(F, L, lane, gam, shift); break;
+    case 4: if constexpr (MJ >= 4) small_run<4, R, PER>(F, L, lane, gam, shift); break;
+    default: if constexpr (MJ >= 5) small_run<5, R, PER>(F, L, lane, gam, shift); break;
+  }
+  for (int q = 0; q < Ro; ++q)
+    for (int i = lane; i < n; i += 64) gp(F.ring[j])[(int64_t)q * n + i] = L.own[q * st + i + 1];
+}
+
+template <int MJ>
+__device__ __forceinline__ void small_body(const Fused1D& F) {
+  if (F.bc == RIDC_BC_PERIODIC) {
+    if (F.n <= 64) small_rows<MJ, 1, true>(F);
+    else if (F.n <= 128) small_rows<MJ, 2, true>(F);
+    else small_rows<MJ, 4, true>(F);
+  } else {
+    if (F.n <= 64) small_rows<MJ, 1, false>(F);
+    else if (F.n <= 128) small_rows<MJ, 2, false>(F);
+    else small_rows<MJ, 4, false>(F);
+  }
+}
+
+template <int MJ>
+__global__ __launch_bounds__(64 * (MJ + 1)) void k_small1d(const Fused1D* __restrict__ items) {
+  small_body<MJ>(items[blockIdx.x]);
+}
+
+// One instance, descriptor in the kernel arguments.
+template <int MJ, int R, bool PER>
+__global__ __launch_bounds__(64 * (MJ + 1)) void k_small1d_one(const Fused1D F) {
+  small_rows<MJ, R, PER>(F);
+}
 
 __global__ void k_nonfinite(const double* __restrict__ x, int64_t count, int* flag) {
   int bad = 0;
@@ -680,6 +952,57 @@ hipError_t launch_fused_1d(const Fused1D* d_items, const Fused1D* one, int count
     if (max_order <= 4) return fused_launch<3, 1024>(d_items, one, count, lds_bytes, stream);
   }
   return hipErrorInvalidValue;
+}
+
+size_t lds_bytes_small_1d(int n, int slots, int order) {
+  size_t w = 0;
+  for (int j = 1; j < order; ++j) w += (size_t)j * (j + 1);
+  return sizeof(double) * ((size_t)(slots + order) * (n + 2) + w);
+}
+
+namespace {
+template <int MJ>
+const void* small_kernel(int n, bool per) {
+  if (n <= 64)
+    return per ? reinterpret_cast<const void*>(&k_small1d_one<MJ, 1, true>)
+               : reinterpret_cast<const void*>(&k_small1d_one<MJ, 1, false>);
+  if (n <= 128)
+    return per ? reinterpret_cast<const void*>(&k_small1d_one<MJ, 2, true>)
+               : reinterpret_cast<const void*>(&k_small1d_one<MJ, 2, false>);
+  return per ? reinterpret_cast<const void*>(&k_small1d_one<MJ, 4, true>)
+             : reinterpret_cast<const void*>(&k_small1d_one<MJ, 4, false>);
+}
+const void* small_kernel(int order, int n, int bc) {
+  const bool per = bc == RIDC_BC_PERIODIC;
+  return order <= 4 ? small_kernel<3>(n, per) : small_kernel<kMaxJ1024>(n, per);
+}
+const void* small_items_kernel(int order) {
+  return order <= 4 ? reinterpret_cast<const void*>(&k_small1d<3>)
+                    : reinterpret_cast<const void*>(&k_small1d<kMaxJ1024>);
+}
+}  // namespace
+
+hipError_t prepare_small_1d(const Fused1D& F, int lds_bytes) {
+  hipError_t e = hipSuccess;
+  // (a batch's highest order, and with it the kernel, may be another instance's)
+  for (const void* k : {small_kernel(F.P, F.n, F.bc), small_items_kernel(1),
+                        small_items_kernel(kMaxJ1024 + 1)})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  return e;
+}
+
+hipError_t launch_small_1d(const Fused1D* d_items, const Fused1D* one, int count, int max_order,
+                           size_t lds_bytes, hipStream_t stream) {
+  if (max_order > kMaxJ1024 + 1) return hipErrorInvalidValue;
+  if (one) {
+    void* args[] = {const_cast<Fused1D*>(one)};
+    return hipLaunchKernel(small_kernel(one->P, one->n, one->bc), dim3(1), dim3(64 * one->P), args,
+                           lds_bytes, stream);
+  }
+  void* args[] = {&d_items};
+  return hipLaunchKernel(small_items_kernel(max_order), dim3(count), dim3(64 * max_order), args,
+                         lds_bytes, stream);
 }
 
 hipError_t launch_nonfinite_check(const double* x, int64_t count, int* flag, hipStream_t stream) {

@@ -430,3 +430,80 @@ def test_stencil_time_is_2d_only(env):
         s.stencil_time(5)
     assert ei.value.code == ridc.RIDC_E_UNSUPPORTED
     s.close()
+
+
+@pytest.mark.parametrize("order", [1, 2, 4, 5, 6])
+@pytest.mark.parametrize("bc,fe", [("periodic", "advect"), ("periodic", "upwind"),
+                                   ("dirichlet", "burgers"), ("dirichlet", "logistic"),
+                                   ("dirichlet", "none")])
+def test_small_systems_in_one_workgroup(env, order, bc, fe):
+    """Up to 256 rows a handle of its own, or a batch of such handles, runs whole ranges of steps in
+    one workgroup with a wave a level.  Sizes around one, two and four rows a lane; the bits are those
+    of a launch per step whatever the range is cut into, alone and in a batch, and the oracle agrees."""
+    torch, ridc = env
+    nt = 18
+    solvers, u0s, nts, want = [], [], [], []
+    for n in (2, 3, 7, 63, 64, 65, 127, 128, 129, 192, 255, 256):
+        _say(f"case: small {bc} {fe} n={n} P={order}")
+        length = 2 * math.pi if bc == "periodic" else 1.0
+        x = workloads.grid_points(bc, n, length)
+        u0 = np.sin(x) + 0.25 * np.cos(5 * x) if bc == "periodic" else x * (length - x) * 4
+        prob = dict(dim=1, bc=bc, n=n, length=length, fe=fe, a=0.6, nu=2e-3, T=0.05, nt=nt,
+                    order=order)
+        small, lv = run_gpu(env, prob, u0)
+        step, lv_s = run_gpu(env, prob, u0, tile=(256, 0, 0))
+        np.testing.assert_array_equal(small, step)
+        np.testing.assert_array_equal(lv, lv_s)
+        p = Problem(dim=1, bc=bc, n=n, length=length, fe=fe, a=0.6, nu=2e-3, dt=0.05 / nt)
+        ref = ridc_pipelined(p, u0, nt, order)
+        for j in range(order):
+            assert rel_l2(lv[j], ref[j]) <= TOL
+        s = ridc.Ridc(prob)
+        x0 = torch.tensor(u0, dtype=torch.float64, device="cuda")
+        out = torch.empty_like(x0)
+        s.begin(x0, nt)
+        chunk = 1
+        while s.remaining() > 0:
+            ridc.advance([s], chunk)
+            chunk = chunk % 5 + 2
+            if chunk == 4:                       # the rings pass to the other kernel and back
+                s.set_tile(256, 0, 0)
+            elif chunk == 5 and order <= 6:
+                s.set_tile(512, 0, 2)
+        s.read(out)
+        s.sync()
+        np.testing.assert_array_equal(out.cpu().numpy(), step)
+        s.close()
+        s = ridc.Ridc(prob)
+        solvers.append(s)
+        u0s.append(x0)
+        nts.append(nt - (n % 3))
+        want.append(run_gpu(env, dict(prob), u0, nt=nts[-1], tile=(256, 0, 0))[0])
+    uTs = [torch.empty_like(x0) for x0 in u0s]
+    ridc.integrate_batch(solvers, u0s, nts, uTs)
+    torch.cuda.synchronize()
+    for uT, w in zip(uTs, want):
+        np.testing.assert_array_equal(uT.cpu().numpy(), w)
+    for s in solvers:
+        s.close()
+
+
+@pytest.mark.parametrize("bc,n,order", [("periodic", 257, 4), ("dirichlet", 300, 1),
+                                        ("dirichlet", 129, 8), ("periodic", 200, 7),
+                                        ("periodic", 999, 6), ("dirichlet", 2047, 4),
+                                        ("periodic", 1500, 8), ("periodic", 9500, 2)])
+@pytest.mark.parametrize("nu", [2e-5, 2e-3, 2e-1])
+def test_default_tilings_equal_whole_cycles(env, bc, n, order, nu):
+    """Chunks (their number depends on the halo, so on nu) or a whole cycle, as a new handle takes
+    them, give the bits of one 256-thread workgroup a level."""
+    length = 2 * math.pi if bc == "periodic" else 1.0
+    x = workloads.grid_points(bc, n, length)
+    u0 = np.sin(x) + 0.25 * np.cos(5 * x) if bc == "periodic" else x * (length - x) * 4
+    nt = 12
+    prob = dict(dim=1, bc=bc, n=n, length=length, fe="advect" if bc == "periodic" else "logistic",
+                a=0.6, nu=nu, T=0.004, nt=nt, order=order)
+    _say(f"case: default tile {bc} n={n} P={order} nu={nu}")
+    got, lv = run_gpu(env, prob, u0)
+    want, lv_w = run_gpu(env, prob, u0, tile=(256, 0, 0))
+    np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(lv, lv_w)
