@@ -23,7 +23,8 @@
 // batched over every active level of every instance in one launch; the final update is fused
 // into the epilogue of the second pass.  Sides that are multiples of 64 fold Q by its reflection
 // symmetry, Q_{n-1-k, j} = (-1)^j Q_{k, j}, which halves the contraction (k_pass2d): a pass folds
-// (and splits) its operand while staging it.
+// its operand while staging it; the operand of a folded split-BF16 pass arrives folded and split
+// (store_split).
 //
 // Reduced precision (FP32 or split BF16) adds one FP64 residual refinement:
 //   x1 = S~(b),  rho = b - (x1 - dt nu Lap_h x1)  (FP64 5-point),  x = x1 + S~(rho);
@@ -59,6 +60,8 @@ struct Lvl2D {
   double* x64;          // FP64 sine coefficients, or (refined paths) the FP32 first solve
   float* lo0;           // reduced precision: the right-hand side or residual the solve takes
   float* lo1;           // reduced precision: its sine coefficients
+                        // (split-BF16 folded systems: both as split operands, store_split, lo1
+                        // between its pass and the line solves in paired column order)
   const double* col;    // line-solve constants of every column: lambda, g, kappa (n each)
   int64_t nt, sigma0;
   int32_t n, j, R_own, R_prev, fe, prec;
@@ -72,6 +75,7 @@ struct Pass2D {
   void* C;              // output (unless final)
   const float* add;     // final epilogue: extra term (x1 of the refinement, FP32), nullable
   const void* Q;        // transform matrix in the input precision (BF16: hi, lo at +n*n)
+  int64_t paired;       // C takes its columns in paired order (paired_col)
 };
 
 struct Plan2D {
@@ -128,10 +132,41 @@ __device__ __forceinline__ void gst(void* p, V v) {
   *(__attribute__((address_space(1))) V*)p = v;
 }
 
-// The FP32 copy of a right-hand side or residual that the first pass of a reduced-precision
-// solve reads (row-major; that pass folds it, and the split-BF16 pass splits it, while staging).
+// The FP32 copy of a right-hand side or residual that the first pass of an FP32 solve (or of a
+// split-BF16 one that does not fold) reads: row-major; that pass folds or splits it while staging.
 __device__ __forceinline__ void store_lo(float* base, int64_t idx, double v) {
   gst<float>(base + idx, (float)v);
+}
+
+// FP32 -> BF16 hi (round to nearest) in the low half, BF16 lo (of the remainder) in the high half
+__device__ __forceinline__ unsigned split_bf16(float v) {
+  const __bf16 b = (__bf16)v;
+  return (unsigned)__builtin_bit_cast(unsigned short, b) |
+         ((unsigned)__builtin_bit_cast(unsigned short, (__bf16)(v - (float)b)) << 16);
+}
+
+// The operand of a folded split-BF16 pass, 4 n bytes a row like the FP32 values it stands for: for
+// every 8 k < n/2 the BF16 hi and lo of the sums a_k + a_{n-1-k}, then of the differences a_k -
+// a_{n-1-k}, 16 bytes each.  Folding and splitting where the values are made costs each of them once;
+// in the pass every column tile did it again, 0.7 us of vector work for the 0.6 us of matrix work of a
+// slice (24.3 us a pass at 1024^2, four levels).
+// A lane holds x = a_k and y = a_{n-1-k} (low) or the two exchanged and writes two k of one plane:
+// lanes l and l ^ 1 hold neighbouring k and exchange halves.
+__device__ __forceinline__ void store_split(void* row, int k, bool low, float x, float y) {
+  const unsigned own = split_bf16(low ? x + y : y - x);
+  const unsigned oth = (unsigned)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xF, 0xF, false);
+  const unsigned a = k & 1 ? oth : own, b = k & 1 ? own : oth;      // of the even k, of the odd one
+  const bool hi = (threadIdx.x & 1) == 0;
+  const unsigned w = hi ? (a & 0xffffu) | (b << 16) : (a >> 16) | (b & 0xffff0000u);
+  gst<unsigned>((char*)row + (k >> 3) * 64 + (low ? 0 : 32) + (hi ? 0 : 16) + (k & 6) * 2, w);
+}
+
+// Paired column order: position p of a row holds, sixteen at a time, 8 columns and the 8 that
+// mirror them, so that a block of the line solves owns both halves of the sums and differences it
+// writes (n a multiple of 64).
+__device__ __forceinline__ int paired_col(int p, int n) {
+  const int g = p >> 4, o = p & 15;
+  return o < 8 ? 8 * g + o : n - 16 - 8 * g + o;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -140,7 +175,9 @@ __device__ __forceinline__ void store_lo(float* base, int64_t idx, double v) {
 // neighbours come from the adjacent lanes (DPP wave shifts); the columns just outside the wave's
 // 64, which lanes 0 and 63 take, come from one load per half-wave at one address.  Columns at or
 // beyond n hold zero, which is also the Dirichlet ghost value, so a wave that straddles the last
-// column needs no special case.
+// column needs no special case.  SPLIT (operands for a folded split-BF16 pass): the wave owns 32
+// columns and the 32 that mirror them, lane l and lane 63 - l mirrored, and has four outside columns,
+// a quarter-wave each.
 // ---------------------------------------------------------------------------------------------
 constexpr int ST_WAVES = 4;  // waves per block, stacked in rows
 
@@ -185,6 +222,30 @@ __device__ __forceinline__ bool stencil_tile(int n, const StBlock& b, int* iy0, 
   return *ix0 < n && *iy0 < n;
 }
 
+// The column of this lane in the strip at ix0, and the column just outside that lanes 0 (west) and 63
+// (east), or with SPLIT also 32 (west) and 31 (east), take from `outside`.
+template <bool SPLIT>
+__device__ __forceinline__ int strip_col(int lane, int ix0, int n) {
+  return SPLIT && lane >= 32 ? n - ix0 / 2 - 64 + lane : (SPLIT ? ix0 / 2 : ix0) + lane;
+}
+template <bool SPLIT>
+__device__ __forceinline__ int strip_outside(int lane, int ix0, int n) {
+  if constexpr (SPLIT) {
+    const int k0 = ix0 / 2;
+    return lane < 32 ? (lane < 16 ? k0 - 1 : k0 + 32) : (lane < 48 ? n - k0 - 33 : n - k0);
+  } else {
+    return lane < 32 ? ix0 - 1 : ix0 + 64;
+  }
+}
+template <bool SPLIT>
+__device__ __forceinline__ bool strip_west(int lane) {
+  return lane == 0 || (SPLIT && lane == 32);
+}
+template <bool SPLIT>
+__device__ __forceinline__ bool strip_east(int lane) {
+  return lane == 63 || (SPLIT && lane == 31);
+}
+
 // ---------------------------------------------------------------------------------------------
 // right-hand side (increment form), FP64; also writes the low-precision copy.  The quadrature
 // of f along level j-1 is taken as sum_i w_i f_E(v_i) + nu Lap_h (sum_i w_i v_i): the stencil
@@ -203,12 +264,12 @@ struct RhsRow {
 // predictor), or -1: any j, up to the largest order.  This kernel uses no LDS, and its plain
 // (flat) loads measured faster than global ones (31.2 against 33.2 us per launch at 1024^2,
 // FP64).
-template <int JT, int RY>
+template <int JT, int RY, bool SPLIT>
 __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, int ix0) {
   constexpr int JN = JT < 0 ? RIDC_MAX_ORDER : (JT == 0 ? 1 : JT);
   const int n = L.n;
-  const int ix = ix0 + (threadIdx.x & 63);
-  const bool col = ix < n;
+  const int ix = strip_col<SPLIT>(threadIdx.x & 63, ix0, n);
+  const bool col = SPLIT || ix < n;
   const int64_t nn = (int64_t)n * n;
   const int64_t nidx = m - 1;
   const double* __restrict__ u = L.own + ring_slot(nidx, L.R_own) * nn;
@@ -276,7 +337,7 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
   // the column just outside the strip that lane 0 (west) or lane 63 (east) takes: every lane
   // of a half reads that one address (zero outside the grid, the Dirichlet ghost value)
   const int lane = threadIdx.x & 63;
-  const int xo = lane < 32 ? ix0 - 1 : ix0 + 64;
+  const int xo = strip_outside<SPLIT>(lane, ix0, n);
   const bool xok = xo >= 0 && xo < n;
   const int xoc = xok ? xo : ixc;
   const double dt = L.dt;
@@ -292,8 +353,8 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
       const RhsRow dn = load(iy + 1);
       const double ev = window_sum((int64_t)iy * n + xoc);
       double vw = lane_below(mid.V), ve = lane_above(mid.V);
-      vw = lane == 0 ? (xok ? ev : 0.0) : vw;
-      ve = lane == 63 ? (xok ? ev : 0.0) : ve;
+      vw = strip_west<SPLIT>(lane) ? (xok ? ev : 0.0) : vw;
+      ve = strip_east<SPLIT>(lane) ? (xok ? ev : 0.0) : ve;
       const double lap = ((vw + ve) + (up + dn.V)) - 4.0 * mid.V;
       const double quad = mid.fq + L.nu_h2 * lap;
       bs[r] = JT == 0 ? dt * quad
@@ -306,13 +367,19 @@ __device__ __forceinline__ void rhs_level(const Lvl2D& L, int64_t m, int iy0, in
       for (int r = 0; r < RG; ++r) {
         const int64_t c = (int64_t)(iy0 + q + r) * n + ix;
         L.b64[c] = bs[r];
-        if (L.prec != PREC_F64) store_lo(L.lo0, c, bs[r]);
+        if constexpr (SPLIT) {
+          const float x = (float)bs[r];
+          store_split(L.lo0 + (int64_t)(iy0 + q + r) * n, lane < 32 ? ix : n - 1 - ix, lane < 32, x,
+                      __shfl_xor(x, 63));
+        } else if (L.prec != PREC_F64) {
+          store_lo(L.lo0, c, bs[r]);
+        }
       }
     }
   }
 }
 
-template <int RY>
+template <int RY, bool SPLIT>
 __global__ __launch_bounds__(256) void k_rhs2d(const Lvl2D* __restrict__ levels, int64_t sigma) {
   const StBlock blk = stencil_block();
   const Lvl2D& L = levels[blk.z];
@@ -321,11 +388,11 @@ __global__ __launch_bounds__(256) void k_rhs2d(const Lvl2D* __restrict__ levels,
   int iy0, ix0;
   if (!stencil_tile<RY>(L.n, blk, &iy0, &ix0)) return;
   switch (L.j) {
-    case 0: rhs_level<0, RY>(L, m, iy0, ix0); break;
-    case 1: rhs_level<2, RY>(L, m, iy0, ix0); break;
-    case 2: rhs_level<3, RY>(L, m, iy0, ix0); break;
-    case 3: rhs_level<4, RY>(L, m, iy0, ix0); break;
-    default: rhs_level<-1, RY>(L, m, iy0, ix0); break;
+    case 0: rhs_level<0, RY, SPLIT>(L, m, iy0, ix0); break;
+    case 1: rhs_level<2, RY, SPLIT>(L, m, iy0, ix0); break;
+    case 2: rhs_level<3, RY, SPLIT>(L, m, iy0, ix0); break;
+    case 3: rhs_level<4, RY, SPLIT>(L, m, iy0, ix0); break;
+    default: rhs_level<-1, RY, SPLIT>(L, m, iy0, ix0); break;
   }
 }
 
@@ -333,7 +400,7 @@ __global__ __launch_bounds__(256) void k_rhs2d(const Lvl2D* __restrict__ levels,
 // FP32 (in the x64 buffer; it leaves an FP32 accumulator, so nothing is lost).  Every row of the
 // wave's column strip is loaded before any is used, so all of a wave's loads are in flight at
 // once.
-template <int RY>
+template <int RY, bool SPLIT>
 __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ levels, int64_t sigma) {
   const StBlock blk = stencil_block();
   const Lvl2D& L = levels[blk.z];
@@ -343,15 +410,15 @@ __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ level
   int iy0, ix0;
   if (!stencil_tile<RY>(n, blk, &iy0, &ix0)) return;
   const int lane = threadIdx.x & 63;
-  const int ix = ix0 + lane;
-  const bool col = ix < n;
+  const int ix = strip_col<SPLIT>(lane, ix0, n);
+  const bool col = SPLIT || ix < n;
   const float* __restrict__ x1 = (const float*)L.x64;
   // No load sits behind a branch, so that all of them issue back to back: lanes past n and the
   // rows beyond the grid read a clamped in-range address and take zero instead, and the column
   // just outside the strip, which lane 0 (west) or 63 (east) takes, is read by every lane of
   // its half at that one address.  Every wave has RY rows (n is a multiple of 32).
   const int ixc = col ? ix : n - 1;
-  const int xo = lane < 32 ? ix0 - 1 : ix0 + 64;
+  const int xo = strip_outside<SPLIT>(lane, ix0, n);
   const bool xok = xo >= 0 && xo < n;
   const int xoc = xok ? xo : ixc;
   float xr[RY + 2], xe[RY];
@@ -375,15 +442,23 @@ __global__ __launch_bounds__(256) void k_resid2d(const Lvl2D* __restrict__ level
 #pragma unroll
   for (int r = 0; r < RY; ++r) {
     double xw = (double)lane_below(xr[r + 1]), xa = (double)lane_above(xr[r + 1]);
-    xw = lane == 0 ? (double)xe[r] : xw;
-    xa = lane == 63 ? (double)xe[r] : xa;
+    xw = strip_west<SPLIT>(lane) ? (double)xe[r] : xw;
+    xa = strip_east<SPLIT>(lane) ? (double)xe[r] : xa;
     const double x = (double)xr[r + 1];
     const double lap = ((xw + xa) + ((double)xr[r] + (double)xr[r + 2])) - 4.0 * x;
     res[r] = br[r] - (x - L.dt * L.nu_h2 * lap);
   }
   if (col) {
 #pragma unroll
-    for (int r = 0; r < RY; ++r) store_lo(L.lo0, (int64_t)(iy0 + r) * n + ix, res[r]);
+    for (int r = 0; r < RY; ++r) {
+      if constexpr (SPLIT) {
+        const float v = (float)res[r];
+        store_split(L.lo0 + (int64_t)(iy0 + r) * n, lane < 32 ? ix : n - 1 - ix, lane < 32, v,
+                    __shfl_xor(v, 63));
+      } else {
+        store_lo(L.lo0, (int64_t)(iy0 + r) * n + ix, res[r]);
+      }
+    }
   }
 }
 
@@ -398,20 +473,30 @@ static dim3 stencil_grid(int cnt, int64_t nmax) {
 static bool short_strips(int cnt, int64_t nmax) {
   return (nmax + 63) / 64 * (nmax / 16) * cnt < 2048;
 }
-static void launch_rhs(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, hipStream_t st) {
+// split: the systems' passes take split operands (split_operands)
+static void launch_rhs(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, bool split,
+                       hipStream_t st) {
+  auto go = [&](auto kern, dim3 grid) {
+    hipLaunchKernelGGL(kern, grid, dim3(64 * ST_WAVES), 0, st, lv, sigma);
+  };
   if (short_strips(cnt, nmax))
-    hipLaunchKernelGGL(k_rhs2d<4>, stencil_grid<4>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv, sigma);
+    split ? go(k_rhs2d<4, true>, stencil_grid<4>(cnt, nmax))
+          : go(k_rhs2d<4, false>, stencil_grid<4>(cnt, nmax));
   else
-    hipLaunchKernelGGL(k_rhs2d<16>, stencil_grid<16>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv,
-                       sigma);
+    split ? go(k_rhs2d<16, true>, stencil_grid<16>(cnt, nmax))
+          : go(k_rhs2d<16, false>, stencil_grid<16>(cnt, nmax));
 }
-static void launch_resid(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, hipStream_t st) {
+static void launch_resid(const Lvl2D* lv, int cnt, int64_t nmax, int64_t sigma, bool split,
+                         hipStream_t st) {
+  auto go = [&](auto kern, dim3 grid) {
+    hipLaunchKernelGGL(kern, grid, dim3(64 * ST_WAVES), 0, st, lv, sigma);
+  };
   if (short_strips(cnt, nmax))
-    hipLaunchKernelGGL(k_resid2d<4>, stencil_grid<4>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv,
-                       sigma);
+    split ? go(k_resid2d<4, true>, stencil_grid<4>(cnt, nmax))
+          : go(k_resid2d<4, false>, stencil_grid<4>(cnt, nmax));
   else
-    hipLaunchKernelGGL(k_resid2d<16>, stencil_grid<16>(cnt, nmax), dim3(64 * ST_WAVES), 0, st, lv,
-                       sigma);
+    split ? go(k_resid2d<16, true>, stencil_grid<16>(cnt, nmax))
+          : go(k_resid2d<16, false>, stencil_grid<16>(cnt, nmax));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -456,10 +541,12 @@ __device__ __forceinline__ void line_down(double lam, double (&v)[M], double* t,
   *h = up;
 }
 
-// Add the true downward carry c and come back up from the true upward carry z, storing g z_k.
-template <typename T, int M>
+// Add the true downward carry c and come back up from the true upward carry z, storing g z_k (SPLIT:
+// as the split operand, 64 bytes per row where the block's 16 columns, in paired order, stood).
+template <typename T, int M, bool SPLIT>
 __device__ __forceinline__ void line_up(double lam, double g, double (&v)[M], double c, double z,
                                         T* __restrict__ col, int n) {
+  const int cl = threadIdx.x % LS_COLS;
 #pragma unroll
   for (int k = 0; k < M; ++k) {
     c *= lam;
@@ -468,7 +555,14 @@ __device__ __forceinline__ void line_up(double lam, double g, double (&v)[M], do
 #pragma unroll
   for (int k = M - 1; k >= 0; --k) {
     z = __builtin_fma(lam, z, v[k]);
-    gst<T>(col + (int64_t)k * n, (T)(g * z));
+    if constexpr (SPLIT) {
+      const float x = (float)(g * z);
+      const float y = __int_as_float(
+          __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x140, 0xF, 0xF, false));
+      store_split(col - cl + (int64_t)k * n, cl < 8 ? cl : 15 - cl, cl < 8, x, y);
+    } else {
+      gst<T>(col + (int64_t)k * n, (T)(g * z));
+    }
   }
 }
 
@@ -552,7 +646,7 @@ __device__ __forceinline__ void line_chain(int lane, double P, double G, double 
 }
 
 // ns = blockDim.x / 16 segments of M rows: n = ns M.
-template <typename T, int M>
+template <typename T, int M, bool SPLIT>
 __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d(const Lvl2D* __restrict__ levels,
                                                                int64_t sigma) {
   __shared__ double ex[2][LS_SEGS * LS_STRIDE], pw[3][LS_COLS];
@@ -561,10 +655,10 @@ __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d(const Lvl2D* __re
   int64_t m;
   if (!level_active(L, sigma, &m)) return;
   const int n = L.n, cl = threadIdx.x % LS_COLS;
-  const int j = (int)(q % gridDim.x) * LS_COLS + cl;
+  const int at = (int)(q % gridDim.x) * LS_COLS + cl, j = SPLIT ? paired_col(at, n) : at;
   const int seg = threadIdx.x / LS_COLS, ns = blockDim.x / LS_COLS;
   T* __restrict__ col =
-      (sizeof(T) == 8 ? (T*)L.x64 : (T*)L.lo1) + (int64_t)seg * M * n + j;
+      (sizeof(T) == 8 ? (T*)L.x64 : (T*)L.lo1) + (int64_t)seg * M * n + at;
   double v[M];
 #pragma unroll
   for (int k = 0; k < M; ++k) v[k] = (double)gld<T>(col + (int64_t)k * n);
@@ -611,14 +705,14 @@ __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d(const Lvl2D* __re
     }
   }
   __syncthreads();
-  line_up<T, M>(lam, g, v, ex[0][seg * LS_STRIDE + cl], ex[1][seg * LS_STRIDE + cl], col, n);
+  line_up<T, M, SPLIT>(lam, g, v, ex[0][seg * LS_STRIDE + cl], ex[1][seg * LS_STRIDE + cl], col, n);
 }
 
 // Columns of more than 64 segments of 32 rows (n > 2048): the block walks its columns 2048 rows
 // at a time, twice (the second walk reads the rows again instead of keeping them); t and h of
 // all n / 32 segments stay in LDS (at most 128 KB), where one thread per column turns them into
 // the segments' carries.
-template <typename T>
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d_long(const Lvl2D* __restrict__ levels,
                                                                     int64_t sigma) {
   constexpr int M = 32;
@@ -628,8 +722,8 @@ __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d_long(const Lvl2D*
   int64_t m;
   if (!level_active(L, sigma, &m)) return;
   const int n = L.n, cl = threadIdx.x % LS_COLS, ns = n / M;
-  const int j = (int)(q % gridDim.x) * LS_COLS + cl;
-  T* __restrict__ col0 = (sizeof(T) == 8 ? (T*)L.x64 : (T*)L.lo1) + j;
+  const int at = (int)(q % gridDim.x) * LS_COLS + cl, j = SPLIT ? paired_col(at, n) : at;
+  T* __restrict__ col0 = (sizeof(T) == 8 ? (T*)L.x64 : (T*)L.lo1) + at;
   double* tt = exl;
   double* hh = exl + ns * LS_COLS;
   const double lam = gld<double>(L.col + j), g = gld<double>(L.col + n + j);
@@ -671,24 +765,24 @@ __global__ __launch_bounds__(LS_COLS * LS_SEGS) void k_lines2d_long(const Lvl2D*
     for (int k = 0; k < M; ++k) v[k] = (double)gld<T>(col + (int64_t)k * n);
     double t, h;
     line_down<M>(lam, v, &t, &h);
-    line_up<T, M>(lam, g, v, tt[seg * LS_COLS + cl], hh[seg * LS_COLS + cl], col, n);
+    line_up<T, M, SPLIT>(lam, g, v, tt[seg * LS_COLS + cl], hh[seg * LS_COLS + cl], col, n);
   }
 }
 
 // Rows per segment: the fewest (8, 16 or 32) that keep a column within 64 segments; n is a
 // multiple of 32.
-template <typename T>
+template <typename T, bool SPLIT>
 static void launch_lines(const Lvl2D* lv, int cnt, int64_t n, int64_t sigma, hipStream_t st) {
   const dim3 grid((unsigned)(n / LS_COLS), (unsigned)cnt);
   const unsigned t8 = (unsigned)(n / 8 * LS_COLS);
   if (n <= 8 * LS_SEGS)
-    hipLaunchKernelGGL((k_lines2d<T, 8>), grid, dim3(t8), 0, st, lv, sigma);
+    hipLaunchKernelGGL((k_lines2d<T, 8, SPLIT>), grid, dim3(t8), 0, st, lv, sigma);
   else if (n <= 16 * LS_SEGS)
-    hipLaunchKernelGGL((k_lines2d<T, 16>), grid, dim3(t8 / 2), 0, st, lv, sigma);
+    hipLaunchKernelGGL((k_lines2d<T, 16, SPLIT>), grid, dim3(t8 / 2), 0, st, lv, sigma);
   else if (n <= 32 * LS_SEGS)
-    hipLaunchKernelGGL((k_lines2d<T, 32>), grid, dim3(t8 / 4), 0, st, lv, sigma);
+    hipLaunchKernelGGL((k_lines2d<T, 32, SPLIT>), grid, dim3(t8 / 4), 0, st, lv, sigma);
   else
-    hipLaunchKernelGGL((k_lines2d_long<T>), grid, dim3(LS_COLS * LS_SEGS),
+    hipLaunchKernelGGL((k_lines2d_long<T, SPLIT>), grid, dim3(LS_COLS * LS_SEGS),
                        2 * (size_t)(n / 32) * LS_COLS * sizeof(double), st, lv, sigma);
 }
 
@@ -751,17 +845,13 @@ __device__ __forceinline__ void fold_f32(u32x4 a, u32x4 m, u32x4* sum, u32x4* di
   *sum = __builtin_bit_cast(u32x4, flt4{x[0] + y[3], x[1] + y[2], x[2] + y[1], x[3] + y[0]});
   *dif = __builtin_bit_cast(u32x4, flt4{x[0] - y[3], x[1] - y[2], x[2] - y[1], x[3] - y[0]});
 }
-// 4 FP32 values -> BF16 hi (round to nearest) and BF16 lo (of the remainder), 8 bytes each
+// 4 FP32 values -> BF16 hi and lo, 8 bytes each
 __device__ __forceinline__ void split4_bf16(flt4 v, uint2* hi, uint2* lo) {
-  unsigned short h[4], l[4];
+  unsigned w[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const __bf16 b = (__bf16)v[e];
-    h[e] = __builtin_bit_cast(unsigned short, b);
-    l[e] = __builtin_bit_cast(unsigned short, (__bf16)(v[e] - (float)b));
-  }
-  *hi = uint2{(unsigned)h[0] | ((unsigned)h[1] << 16), (unsigned)h[2] | ((unsigned)h[3] << 16)};
-  *lo = uint2{(unsigned)l[0] | ((unsigned)l[1] << 16), (unsigned)l[2] | ((unsigned)l[3] << 16)};
+  for (int e = 0; e < 4; ++e) w[e] = split_bf16(v[e]);
+  *hi = uint2{(w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16)};
+  *lo = uint2{(w[0] >> 16) | (w[1] & 0xffff0000u), (w[2] >> 16) | (w[3] & 0xffff0000u)};
 }
 
 // Instruction order of one pipelined k-slice step (a single basic block): NR LDS reads, then
@@ -788,6 +878,9 @@ __device__ __forceinline__ void interleave_step() {
 // for j' < n/2 and 2(j' - n/2) + 1 above.  A block takes BT consecutive output columns, its
 // first BT/2 local columns the even ones (against the sums), the others the odd ones (against
 // the differences); a wave's columns are all of one parity.
+// A folded split-BF16 pass takes a split operand (store_split): its 16-byte chunks go to LDS as they
+// are, four planes (sums hi, lo, differences hi, lo) whose LDS starts are 32 bytes apart modulo the 128
+// of all banks, so that the four chunks of 8 k and the next four meet no bank twice.
 // KX = 2 doubles the k-slice (split BF16: one slice in flight instead of two).  A k-slice has
 // two LDS stages (the next slice is stored while the current one feeds the matrix cores, one
 // barrier per slice), except the wide split-BF16 slices, whose operands fill one stage's worth of
@@ -797,16 +890,25 @@ template <int PREC, int KX>
 constexpr int lds_stages() {
   return PREC == PREC_BF16 && KX == 2 ? 1 : 2;
 }
+// Bytes between the LDS rows of an operand: a slice's row is a multiple of 64 bytes, and rows at a
+// stride of 32 modulo 64 are what 16 lanes reading 16 bytes each of 16 rows need to meet all 64 banks
+// once (4 cycles a fragment; 8 at a padding of 16, and a write at either takes 8).
+constexpr int ROW_PAD = 32;
+template <int PREC, int FOLD>
+constexpr bool split_a() {
+  return PREC == PREC_BF16 && FOLD;
+}
 template <int PREC, int KX, int BT>
 constexpr size_t pass_lds_bytes(int fold) {
   typedef typename Tr<PREC>::T T;
   typedef typename std::conditional<PREC == PREC_F64, double, float>::type ST;
   constexpr int BK = Tr<PREC>::BK * KX;
-  constexpr int LDE = (BK * (int)sizeof(T) + 16) / (int)sizeof(T);
+  constexpr int LDE = (BK * (int)sizeof(T) + ROW_PAD) / (int)sizeof(T);
   constexpr int NSPLIT = PREC == PREC_BF16 ? 2 : 1;
-  const size_t k = (size_t)lds_stages<PREC, KX>() * ((fold ? 2 : 1) * NSPLIT + NSPLIT) * BT * LDE *
-                   sizeof(T);
-  const size_t ep = (size_t)(BT / wave_rows<BT>()) * 16 * (BT * sizeof(ST) + 16);
+  const size_t pad = PREC == PREC_BF16 && fold ? 4 * 32 : 0;
+  const size_t k = (size_t)lds_stages<PREC, KX>() *
+                   (((fold ? 2 : 1) * NSPLIT + NSPLIT) * BT * LDE * sizeof(T) + pad);
+  const size_t ep = (size_t)(PREC == PREC_F64 && BT == 128 ? 32 : BT) * (BT * sizeof(ST) + 16);
   return k > ep ? k : ep;
 }
 
@@ -820,7 +922,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   typedef typename TR::T T;
   typedef typename TR::Acc Acc;
   constexpr int BK = TR::BK * KX;
-  constexpr int ROWB = BK * (int)sizeof(T) + 16;     // LDS row stride in bytes (16-aligned)
+  constexpr int ROWB = BK * (int)sizeof(T) + ROW_PAD;   // LDS row stride in bytes
   constexpr int LDE = ROWB / (int)sizeof(T);          // ... in elements
   constexpr int CH = BK * (int)sizeof(T) / 16;        // 16-byte chunks per row
   constexpr int NSPLIT = PREC == PREC_BF16 ? 2 : 1;
@@ -829,10 +931,12 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   static_assert(BT * CH % NTHR == 0, "whole chunks per thread");
   extern __shared__ __attribute__((aligned(16))) unsigned char pass_smem[];
   // LDS stage b of a k-slice: the A operands, then Q
-  constexpr size_t A_BYTES = (size_t)NA * NSPLIT * BT * LDE * sizeof(T);
+  constexpr bool SPLITA = split_a<PREC, FOLD>();
+  constexpr int APL = BT * LDE + (SPLITA ? 16 : 0);   // elements of an A plane
+  constexpr size_t A_BYTES = (size_t)NA * NSPLIT * APL * sizeof(T);
   constexpr size_t STAGE_BYTES = A_BYTES + (size_t)NSPLIT * BT * LDE * sizeof(T);
   auto stage_a = [&](int b) {
-    return reinterpret_cast<T (*)[NSPLIT][BT * LDE]>(pass_smem + b * STAGE_BYTES);
+    return reinterpret_cast<T (*)[NSPLIT][APL]>(pass_smem + b * STAGE_BYTES);
   };
   auto stage_b = [&](int b) {
     return reinterpret_cast<T (*)[BT * LDE]>(pass_smem + b * STAGE_BYTES + A_BYTES);
@@ -861,7 +965,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   // A arrives row-major in FP64 or FP32 (the split-BF16 pass splits it while staging); Q in T
   typedef typename std::conditional<PREC == PREC_BF16, float, T>::type TA;
   constexpr int EA = 16 / (int)sizeof(TA);          // A elements per 16-byte chunk
-  constexpr int CHA = BK * (int)sizeof(TA) / 16;    // A chunks per row
+  constexpr int CHA = BK * (int)sizeof(TA) * (SPLITA ? 2 : 1) / 16;   // A chunks per row
   constexpr int NAC = BT * CHA / NTHR;              // A chunks per thread
   static_assert(BT * CHA % NTHR == 0, "whole A chunks per thread");
   const TA* A = (const TA*)E.A;
@@ -872,6 +976,11 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   // row of Q of local column c (rows past n read a row in range; their columns are never stored)
   auto q_row = [&](int c) {
     if constexpr (FOLD) {
+      if (SPLITA && E.paired) {
+        const int p = col0 + (c < BT / 2 ? 2 * c : 2 * (c - BT / 2) + 1);
+        const int j = paired_col(p < n ? p : n - 1, n);
+        return (j & 1 ? half : 0) + (j >> 1);
+      }
       const int e = (col0 >> 1) + (c < BT / 2 ? c : c - BT / 2);
       return (c < BT / 2 ? 0 : half) + (e < half ? e : half - 1);
     } else {
@@ -902,8 +1011,14 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   // slice's loads are issued one MFMA phase before they are stored into LDS.  Rows past n (a
   // partial block tile) read row n-1 instead: they only reach output rows past n, which the
   // epilogue never stores, and no select on the loaded values makes a step wait for its loads.
+  // row of Q chunk id: in order, but the 8 lanes of a write that hold two rows of 64 bytes hold rows r
+  // and r + 2, which are 64 bytes apart modulo the 128 that a cycle writes
+  auto q_chunk_row = [](int id) {
+    const int r = id / CH;
+    return CH == 4 ? (r & ~3) | ((r & 1) << 1) | ((r >> 1) & 1) : r;
+  };
   struct Slice {
-    u32x4 ra[NAC], rm[FOLD ? NAC : 1], rb[NSPLIT][CPT];
+    u32x4 ra[NAC], rm[FOLD && !SPLITA ? NAC : 1], rb[NSPLIT][CPT];
   };
   auto gload = [&](Slice& S, int k0) {
 #pragma unroll
@@ -913,34 +1028,42 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
       const int ga = row0 + r;
       const int64_t ko = k0 + q * EA;
       const TA* arow = A + (int64_t)(ga < n ? ga : n - 1) * n;
+      if constexpr (SPLITA) {
+        S.ra[c] = gld<u32x4>(arow + 2 * k0 + q * EA);
+        continue;
+      }
       S.ra[c] = gld<u32x4>(arow + ko);
-      if constexpr (FOLD) S.rm[c] = gld<u32x4>(arow + (n - ko - EA));
+      if constexpr (FOLD && !SPLITA) S.rm[c] = gld<u32x4>(arow + (n - ko - EA));
     }
 #pragma unroll
     for (int s = 0; s < NSPLIT; ++s)
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         const int id = tid + c * NTHR;
-        const int r = id / CH, q = id % CH;
+        const int r = q_chunk_row(id), q = id % CH;
         const int64_t ko = k0 + q * E16;
         S.rb[s][c] = gld<u32x4>(Q + s * qsplit + (int64_t)q_row(r) * K + ko);
       }
   };
-  // Rows keep a slice's k in order.  A lane of an FP32/FP64 fragment takes KQ consecutive k of its
-  // row, from KQ (l / 16), so that MFMA i of the slice multiplies k = i, KQ + i, 2 KQ + i, 3 KQ + i
-  // (the same for every shape) and rows are written and read 16 bytes at a time.
+  // Rows keep a slice's k in order.  A lane of an FP32/FP64 fragment takes every fourth 16-byte chunk
+  // of its row, from chunk l / 16, so that MFMA (v, e) of the slice multiplies k = EV (4v + l / 16) + e
+  // (the same for every shape), EV elements a chunk.
   constexpr int KQ = BK / 4;
   auto put = [&](T* row_base, int q, u32x4 v) { *(u32x4*)((char*)row_base + q * 16) = v; };
   auto sstore = [&](const Slice& S, int stage) {
-    T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
+    T (*As)[NSPLIT][APL] = stage_a(stage);
     T (*Bs)[BT * LDE] = stage_b(stage);
 #pragma unroll
     for (int c = 0; c < NAC; ++c) {
       const int id = tid + c * NTHR;
       const int r = id / CHA, q = id % CHA;
       const int ro = r * LDE;                        // row start, in elements
+      if constexpr (SPLITA) {
+        put(As[(q >> 1) & 1][q & 1] + ro, q >> 2, S.ra[c]);
+        continue;
+      }
       u32x4 su = S.ra[c], di = S.ra[c];
-      if constexpr (FOLD) {
+      if constexpr (FOLD && !SPLITA) {
         if constexpr (PREC == PREC_F64)
           fold_f64(S.ra[c], S.rm[c], &su, &di);
         else
@@ -955,7 +1078,6 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
           *(uint2*)(As[a][1] + ro + q * 4) = lo;
         };
         put4(0, su);
-        if constexpr (FOLD) put4(1, di);
       } else {
         put(As[0][0] + ro, q, su);
         if constexpr (FOLD) put(As[1][0] + ro, q, di);
@@ -966,7 +1088,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         const int id = tid + c * NTHR;
-        const int r = id / CH, q = id % CH;
+        const int r = q_chunk_row(id), q = id % CH;
         put(Bs[s] + r * LDE, q, S.rb[s][c]);
       }
   };
@@ -986,7 +1108,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
     const int k4 = lane >> 4;
 #pragma unroll
     for (int v = 0; v < KQ / EV; ++v) {
-      const u32x4 w = *(const u32x4*)(row + k4 * KQ + v * EV);
+      const u32x4 w = *(const u32x4*)(row + (v * 4 + k4) * EV);
       struct Ev {
         T x[EV];
       };
@@ -998,7 +1120,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   };
   // this wave's fragments of the slice in LDS stage `stage`: MT tiles of A rows, NB of Q rows
   auto read_frags = [&](int stage, Frag (&fa)[MT], Frag (&fb)[NB]) {
-    T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
+    T (*As)[NSPLIT][APL] = stage_a(stage);
     T (*Bs)[BT * LDE] = stage_b(stage);
 #pragma unroll
     for (int t = 0; t < MT; ++t) fa[t] = frag(As[pa0][0] + (wm + t * 16 + r16) * LDE);
@@ -1030,7 +1152,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
     bf16x8 ahi[MT], alo[MT], bhi[NB], blo[NB];
   };
   auto read_frags_bf = [&](int stage, int ks, FragB& f) {
-    T (*As)[NSPLIT][BT * LDE] = stage_a(stage);
+    T (*As)[NSPLIT][APL] = stage_a(stage);
     T (*Bs)[BT * LDE] = stage_b(stage);
     const int kb = (lane >> 4) * 16 + ks * 64;
 #pragma unroll
@@ -1065,14 +1187,21 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.ahi[a], f.bhi[b], acc[a][b], 0, 0, 0);
     }
   };
-  // the epilogue's geometry: round a takes tile row a of every wave, 16 rows per wave row
+  // the epilogue's geometry: the block tile goes through LDS at once, the large FP64 one in rounds of
+  // a tile row of every wave (at 1024^2, four levels, a pass takes 78.0 us in rounds, 79.0 at once;
+  // split BF16 20.7 and 20.6)
+  constexpr int ROUNDS = PREC == PREC_F64 && BT == 128 ? MT : 1;
+  constexpr int AG = MT / ROUNDS;                             // tile rows of a wave per round
+  constexpr int RW = 16 * AG;                                 // ... in rows
   typedef typename std::conditional<PREC == PREC_F64, double, float>::type ST;
-  constexpr int RW = BT / WM * 16;                            // output rows per round
   constexpr int SS = BT + 16 / (int)sizeof(ST);               // LDS row stride, 16-byte rows
   constexpr int EC = OUT == OUT_F32 ? 4 : 2;                  // elements per chunk
   constexpr int CPR = BT / EC;                                // chunks per row
-  constexpr int NC = RW * CPR / NTHR;                         // chunks per thread and round
-  static_assert(RW * CPR % NTHR == 0, "whole chunks per thread");
+  constexpr int NC = BT * CPR / NTHR;                         // chunks per thread
+  constexpr int GC = BT < 128 ? NC : (NC + 3) / 4;            // ... per group (below)
+  constexpr int NG = NC / GC, GR = NG / ROUNDS;               // groups, and groups per round
+  static_assert(NC % GC == 0 && NG % ROUNDS == 0, "whole groups");
+  static_assert(BT * CPR % NTHR == 0, "whole chunks per thread");
   ST* stg = reinterpret_cast<ST*>(pass_smem);
   double* out64 = nullptr;
   const double* base = nullptr;
@@ -1084,35 +1213,33 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   // rows (l/16) + 4r (measured lane layouts of the two instructions)
   const int i_base = PREC == PREC_F64 ? (lane >> 4) : 4 * (lane >> 4);
   constexpr int i_step = PREC == PREC_F64 ? 4 : 1;
-  auto chunk_at = [&](int a, int c, int* lr, int* lc, int64_t* o) {
-    const int id = tid + c * NTHR;
-    *lr = id / CPR;
+  auto chunk_at = [&](int g, int c, int* lr, int* lc, int64_t* o) {   // chunk c of group g
+    const int id = tid + (g % GR * GC + c) * NTHR;
+    *lr = id / CPR;                                  // LDS row: the round's rows of every wave row
     *lc = (id % CPR) * EC;
-    const int row = row0 + (*lr / 16) * WM + 16 * a + *lr % 16;
+    const int row = row0 + *lr / RW * WM + g / GR * RW + *lr % RW;
     *o = (int64_t)row * n + col0 + *lc;
     return row < n && col0 + *lc < n;                // n is a multiple of 32: whole chunks
   };
-  // the final update's FP64 operands (base, add) of this thread's chunks: one round ahead, or, in
-  // the small tiles, all of them before the k-loop, under which they arrive
-  constexpr int NF = BT < 128 ? MT : 2;
-  dbl2 bq[NF][NC];
-  flt2 aq[NF][NC];
-  auto fetch = [&](int a, int slot) {
+  // the final update's FP64 operands (base, add) of this thread's chunks, in groups of GC: all of them
+  // before the k-loop of the small tiles, under which they arrive; in the large ones a group ahead,
+  // the first under the last slices
+  constexpr int SLOTS = OUT == OUT_FINAL ? (NG > 1 ? 2 : 1) : 1;
+  dbl2 bq[SLOTS][GC];
+  flt2 aq[SLOTS][GC];
+  auto fetch = [&](int g) {
     if constexpr (OUT == OUT_FINAL) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
+      for (int c = 0; c < GC; ++c) {
         int lr, lc;
         int64_t o;
-        if (!chunk_at(a, c, &lr, &lc, &o)) continue;
-        bq[slot][c] = gld<dbl2>(base + o);
-        aq[slot][c] = PREC != PREC_F64 && E.add ? gld<flt2>(E.add + o) : flt2{0.0f, 0.0f};
+        if (!chunk_at(g, c, &lr, &lc, &o)) continue;
+        bq[g % SLOTS][c] = gld<dbl2>(base + o);
+        aq[g % SLOTS][c] = PREC != PREC_F64 && E.add ? gld<flt2>(E.add + o) : flt2{0.0f, 0.0f};
       }
     }
   };
-  if constexpr (BT < 128) {
-#pragma unroll
-    for (int a = 0; a < MT; ++a) fetch(a, a);
-  }
+  if constexpr (BT < 128) fetch(0);
   auto kslice = [&](int k) { return (k < KT ? k : KT - 1) * BK; };
   if constexpr (PREC == PREC_BF16 && lds_stages<PREC, KX>() == 1) {
     // wide slices: one in flight, its loads cover a whole MFMA phase of twice the length
@@ -1123,6 +1250,7 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
       sstore(sl, 0);
       __syncthreads();
       if (kt + 1 < KT) gload(sl, (kt + 1) * BK);
+      else fetch(0);
 #pragma unroll
       for (int ks = 0; ks < KX; ++ks) {
         FragB f;
@@ -1157,34 +1285,60 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
       if (kt + 1 < KT) step(kt + 1, s1, s0);
     }
   } else {
-    // Two LDS stages and two register sets of fragments.  Step kt issues the MFMAs of slice kt
-    // from registers while the fragments of slice kt+1 are read from LDS, slice kt+2 is stored
-    // into the stage slice kt came from (read into registers before the previous barrier) and
-    // slice kt+3 is loading from global memory: one barrier per slice.  A step is one basic
-    // block (the slices past the end re-read the last one and are never used), so that its LDS
-    // and global memory instructions can be issued one between each pair of MFMAs
+    // Two LDS stages and two register sets of fragments.  Step kt issues the MFMAs of slice kt from
+    // registers while the fragments of slice kt+1 are read from LDS, slice kt+2 is stored into the
+    // stage slice kt came from (read into registers before the previous barrier) and slice kt+3
+    // (TWO: and kt+4, where the registers hold two slices) is loading: one barrier per slice.  A step
+    // is one basic block (loads past the end re-read the last slice and are never used), so that
+    // its LDS and global memory instructions can be issued one between each pair of MFMAs
     // (interleave_step): the memory work runs under the matrix cores instead of between them.
-    Slice sl;
+    // The last two slices have nothing left to load, and a final update's first operands come in
+    // under them (not in FP64, whose registers are full).
     auto run = [&](auto read, auto mfma, auto& f0, auto& f1, auto interleave) {
-      gload(sl, 0);
-      sstore(sl, 0);
-      gload(sl, kslice(1));
+      constexpr bool TWO = PREC == PREC_BF16 && OUT != OUT_FINAL;
+      Slice s0, s1;
+      gload(s0, 0);
+      gload(s1, kslice(1));
+      sstore(s0, 0);
+      gload(s0, kslice(2));
       __syncthreads();
       read(0, f0);
-      sstore(sl, 1);
-      gload(sl, kslice(2));
+      sstore(s1, 1);
+      if constexpr (TWO) gload(s1, kslice(3));
       __syncthreads();
-      auto step = [&](int kt, const auto& cur, auto& next) {
+      auto step = [&](int kt, Slice& sl, const auto& cur, auto& next) {
         read((kt + 1) & 1, next);
         sstore(sl, kt & 1);
-        gload(sl, kslice(kt + 3));
+        gload(sl, kslice(kt + (TWO ? 4 : 3)));
         mfma(cur);
         interleave();
         __syncthreads();
       };
-      for (int kt = 0; kt < KT; kt += 2) {
-        step(kt, f0, f1);
-        if (kt + 1 < KT) step(kt + 1, f1, f0);
+      Slice& odd = TWO ? s1 : s0;
+      if constexpr (PREC == PREC_F64) {
+        for (int kt = 0; kt < KT; kt += 2) {
+          step(kt, s0, f0, f1);
+          if (kt + 1 < KT) step(kt + 1, s0, f1, f0);
+        }
+        fetch(0);
+        return;
+      }
+      int kt = 0;
+      for (; kt + 3 < KT; kt += 2) {
+        step(kt, s0, f0, f1);
+        step(kt + 1, odd, f1, f0);
+      }
+      if (kt + 3 == KT) {
+        step(kt, s0, f0, f1);
+        fetch(0);
+        read((kt + 2) & 1, f0);
+        mfma(f1);
+        mfma(f0);
+      } else {
+        fetch(0);
+        if (kt + 2 == KT) read((kt + 1) & 1, f1);
+        mfma(f0);
+        if (kt + 2 == KT) mfma(f1);
       }
     };
     if constexpr (PREC == PREC_BF16) {
@@ -1204,40 +1358,42 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
   }
 
   // epilogue: acc[a][b] holds the 16 x 16 tile at local rows wm + 16a, local columns wn + 16b
-  // (column l%16 of lane l).  Round a takes tile row a of every wave through LDS, 16 rows per
-  // wave row, the columns put back in their natural order; each thread then finishes and writes
-  // 16-byte chunks, consecutive threads consecutive chunks of a row.
-  if constexpr (BT == 128) fetch(0, 0);
+  // (column l%16 of lane l).  A round goes through LDS, the columns put back in their natural
+  // order; each thread then finishes and writes 16-byte chunks, consecutive threads consecutive
+  // chunks of a row.
 #pragma unroll
-  for (int a = 0; a < MT; ++a) {
-    __syncthreads();                                  // the buffer is free
+  for (int g = 0; g < NG; ++g) {
+    if (g % GR == 0) {
+      __syncthreads();                                // the buffer is free
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int c = wn + 16 * b + r16;
-      const int nat = FOLD ? (c < BT / 2 ? 2 * c : 2 * (c - BT / 2) + 1) : c;
-      ST* dst = stg + (wm / WM * 16 + i_base) * SS + nat;
+      for (int ar = 0; ar < AG; ++ar)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dst[i_step * r * SS] = acc[a][b][r];
+        for (int b = 0; b < NB; ++b) {
+          const int c = wn + 16 * b + r16;
+          const int nat = FOLD ? (c < BT / 2 ? 2 * c : 2 * (c - BT / 2) + 1) : c;
+          ST* dst = stg + (wm / WM * RW + 16 * ar + i_base) * SS + nat;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dst[i_step * r * SS] = acc[g / GR * AG + ar][b][r];
+        }
+      __syncthreads();
     }
-    __syncthreads();
-    if constexpr (BT == 128)
-      if (a + 1 < MT) fetch(a + 1, (a + 1) % NF);
+    if (g + 1 < NG) fetch(g + 1);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
+    for (int c = 0; c < GC; ++c) {
       int lr, lc;
       int64_t o;
-      if (!chunk_at(a, c, &lr, &lc, &o)) continue;
+      if (!chunk_at(g, c, &lr, &lc, &o)) continue;
       const ST* src = stg + lr * SS + lc;
       if constexpr (OUT == OUT_F64) {
         gst<dbl2>((double*)E.C + o, *(const dbl2*)src);
       } else if constexpr (OUT == OUT_F32) {
         gst<flt4>((float*)E.C + o, *(const flt4*)src);
       } else {
-        const dbl2 bs = bq[a % NF][c];
+        const dbl2 bs = bq[g % SLOTS][c];
         if constexpr (PREC == PREC_F64) {
           gst<dbl2>(out64 + o, dbl2{bs[0] + src[0], bs[1] + src[1]});
         } else {
-          const flt2 ad = aq[a % NF][c];
+          const flt2 ad = aq[g % SLOTS][c];
           gst<dbl2>(out64 + o, dbl2{bs[0] + ((double)ad[0] + (double)src[0]),
                                     bs[1] + ((double)ad[1] + (double)src[1])});
         }
@@ -1334,6 +1490,9 @@ size_t level_ws_bytes(int64_t n, int prec) {
   return 2 * nn * sizeof(double) + 2 * nn * sizeof(float);          // b64, x64, lo0, lo1
 }
 
+// Whether the passes of a system take split operands (store_split).
+bool split_operands(int prec, int64_t n) { return prec == PREC_BF16 && folded(n); }
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Wide k-slices for the split-BF16 pass when the folded contraction is a multiple of twice the
@@ -1428,9 +1587,14 @@ hipError_t allow_lds() {
 template <int PREC>
 hipError_t allow_pass() {
   typedef typename std::conditional<PREC == PREC_F64, double, float>::type T;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lines2d_long<T>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lines2d_long<T, false>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      2 * (16384 / 32) * LS_COLS * (int)sizeof(double));
+  if constexpr (PREC == PREC_BF16)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lines2d_long<T, true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                              2 * (16384 / 32) * LS_COLS * (int)sizeof(double));
   if (e == hipSuccess) e = allow_lds<PREC, PREC == PREC_F64 ? OUT_F64 : OUT_F32>();
   if (e == hipSuccess) e = allow_lds<PREC, OUT_FINAL>();
   return e;
@@ -1561,6 +1725,7 @@ int plan2d_create(const ridc_problem* p, double h, double* const* ring, const in
         E.Q = pl->prec == PREC_F32 ? (const void*)pl->Q32 : (const void*)pl->Qbf;
         E.A = k % 2 == 0 ? L.lo0 : L.lo1;
         E.C = k % 2 == 0 ? (void*)L.lo1 : k == 1 ? (void*)L.x64 : nullptr;
+        E.paired = k % 2 == 0 && split_operands(pl->prec, n);
         if (k == 3) E.add = (const float*)L.x64;   // x = x1 + S~(rho)
       }
     }
@@ -1618,7 +1783,11 @@ void run_solve(const Lvl2D* lv, const Pass2D* d, int cnt, int64_t n, int64_t s, 
   constexpr int OWN = PREC == PREC_F64 ? OUT_F64 : OUT_F32;
   typedef typename std::conditional<PREC == PREC_F64, double, float>::type T;
   launch_pass<PREC, OWN>(d, lv, cnt, n, s, tile, st);
-  launch_lines<T>(lv, cnt, n, s, st);
+  if constexpr (PREC == PREC_BF16)
+    split_operands(PREC, n) ? launch_lines<T, true>(lv, cnt, n, s, st)
+                            : launch_lines<T, false>(lv, cnt, n, s, st);
+  else
+    launch_lines<T, false>(lv, cnt, n, s, st);
   launch_pass<PREC, LAST>(d + cnt, lv, cnt, n, s, tile, st);
 }
 
@@ -1627,16 +1796,16 @@ void run_solve(const Lvl2D* lv, const Pass2D* d, int cnt, int64_t n, int64_t s, 
 // passes is pass-major: passes[k * cnt + e].
 void run_stages(int prec, const Lvl2D* lv, const Pass2D* d, int cnt, int64_t n, int64_t s,
                 int tile, hipStream_t st) {
-  launch_rhs(lv, cnt, n, s, st);
+  launch_rhs(lv, cnt, n, s, split_operands(prec, n), st);
   if (prec == PREC_F64) {
     run_solve<PREC_F64, OUT_FINAL>(lv, d, cnt, n, s, tile, st);
   } else if (prec == PREC_F32) {
     run_solve<PREC_F32, OUT_F32>(lv, d, cnt, n, s, tile, st);
-    launch_resid(lv, cnt, n, s, st);
+    launch_resid(lv, cnt, n, s, false, st);
     run_solve<PREC_F32, OUT_FINAL>(lv, d + 2 * cnt, cnt, n, s, tile, st);
   } else {
     run_solve<PREC_BF16, OUT_F32>(lv, d, cnt, n, s, tile, st);
-    launch_resid(lv, cnt, n, s, st);
+    launch_resid(lv, cnt, n, s, split_operands(prec, n), st);
     run_solve<PREC_BF16, OUT_FINAL>(lv, d + 2 * cnt, cnt, n, s, tile, st);
   }
 }
@@ -1789,7 +1958,7 @@ int plan2d_time_pass(Plan2D* pl, int64_t sigma, int reps, hipStream_t stream, do
   const int tile = pl->tile;
   // the right-hand side of this step, then `reps` back-to-back launches of its first pass, which
   // rewrite the sine coefficients only
-  launch_rhs(pl->d_levels, P, n, sigma, stream);
+  launch_rhs(pl->d_levels, P, n, sigma, split_operands(pl->prec, n), stream);
   auto pass = [&] {
     if (pl->prec == PREC_F64)
       launch_pass<PREC_F64, OUT_F64>(pl->d_passes, pl->d_levels, P, n, sigma, tile, stream);
@@ -1820,13 +1989,13 @@ int plan2d_time_rhs(Plan2D* pl, int64_t sigma, int reps, hipStream_t stream, dou
   const int P = pl->P;
   const int64_t n = pl->n;
   // the right-hand side of this step, launched repeatedly (it rewrites the same values)
-  launch_rhs(pl->d_levels, P, n, sigma, stream);
+  launch_rhs(pl->d_levels, P, n, sigma, split_operands(pl->prec, n), stream);
   hipEvent_t a, b;
   RIDC_HIP_TRY(hipEventCreate(&a));
   RIDC_HIP_TRY(hipEventCreate(&b));
   (void)hipEventRecord(a, stream);
   for (int r = 0; r < reps; ++r)
-    launch_rhs(pl->d_levels, P, n, sigma, stream);
+    launch_rhs(pl->d_levels, P, n, sigma, split_operands(pl->prec, n), stream);
   (void)hipEventRecord(b, stream);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipEventSynchronize(b);

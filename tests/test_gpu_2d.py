@@ -136,6 +136,32 @@ def test_block_tiles_are_bitwise_equal(env, prec):
             s.close()
 
 
+# folded split-BF16 passes take operands folded and split by the kernels that make them: one, two and
+# three slices of the contraction in the 32-tiles and, in a group, the 128-tiles (partial ones at n =
+# 192 and 320), and the line solves of 32 rows a thread and of two walks.  Bars: TOL (nu <= 1e-3); a
+# group's bits are those of a handle alone.
+@pytest.mark.parametrize("n,count", [(64, 128), (128, 64), (192, 32), (320, 15), (1088, 1), (2112, 1)])
+def test_split_operands(env, n, count):
+    torch, ridc = env
+    prob, u0 = workloads.config_reacdiff_2d(n=n, nt=3, order=2 if count == 1 else 1, T=6e-3, nu=1e-3)
+    _say(f"case: 2D bf16x3 split operands n={n} count={count}")
+    ref = oracle2d(prob, u0)
+    top, lvs = run2d(env, prob, u0, prec="bf16x3")
+    for j in range(prob["order"]):
+        err, emax = errs(lvs[j], ref[j])
+        assert err <= tol_of("bf16x3", j) and emax <= tol_of("bf16x3", j), (j, err, emax)
+    if count > 1:
+        x0 = torch.tensor(u0.reshape(-1), dtype=torch.float64, device="cuda")
+        solvers = [ridc.Ridc(prob, prec="bf16x3") for _ in range(count)]
+        uTs = [torch.empty_like(x0) for _ in range(count)]
+        ridc.integrate_batch(solvers, [x0] * count, [prob["nt"]] * count, uTs)
+        torch.cuda.synchronize()
+        for u in uTs:
+            np.testing.assert_array_equal(u.cpu().numpy().reshape(-1), np.asarray(top).reshape(-1))
+        for s in solvers:
+            s.close()
+
+
 @pytest.mark.parametrize("prec", ["fp64", "bf16x3"])
 def test_kernel_time_leaves_the_integration_unchanged(env, prec):
     """ridc_kernel_time runs the next step's stages again and again around its timed pass; the
