@@ -62,12 +62,8 @@ __device__ __forceinline__ double fe_eval(int fe, double ce, double um, double u
   if (fe == RIDC_FE_BURGERS) return -ce * (up * up - um * um);
   return 0.0;
 }
-// u + dt f_E(u)
-__device__ __forceinline__ double row_start(int fe, double ce, double dt, double um, double u0,
-                                            double up) {
-  return __builtin_fma(dt, fe_eval(fe, ce, um, u0, up), u0);
-}
-// acc + cf f_E(v) + cl L v for one window value (f: f_E(v))
+// acc + cf f_E(v) + cl L v for one window value (f: f_E(v)).  A row sums its small terms first, from dt
+// f_E(u), and adds the value u last: one rounding of the size of u.
 __device__ __forceinline__ double row_sum(double acc, double nu_h2, double cf, double cl, double vm,
                                           double v0, double vp, double f) {
 #pragma clang fp contract(off)
@@ -155,7 +151,8 @@ __device__ __forceinline__ void rhs_rows_bc(const Geo& G, const Step<J>& S, int 
       um = up;
       up = t;
     }
-    double acc = row_start(G.fe, G.ce, G.dt, um, u0, up);
+    const double f0 = fe_eval(G.fe, G.ce, um, u0, up);
+    double acc = J > 0 ? G.dt * f0 : __builtin_fma(G.dt, f0, u0);
 #pragma unroll
     for (int i = 0; i < (J > 0 ? J + 1 : 0); ++i) {
       double vm = from_lane_below(v0[i]), vp = from_lane_above(v0[i]);
@@ -166,6 +163,7 @@ __device__ __forceinline__ void rhs_rows_bc(const Geo& G, const Step<J>& S, int 
       }
       acc = row_add(acc, G.fe, G.ce, G.nu_h2, S.cf[i], S.cl[i], vm, v0[i], vp);
     }
+    if (J > 0) acc = u0 + acc;
     if (lane >= 1 && lane <= 62 && l < count) d[l] = ghost ? 0.0 : (mir ? -acc : acc);
   }
 }
@@ -620,13 +618,14 @@ __device__ __forceinline__ void small_run(const Fused1D& F, SmallLvl L, int lane
       double x[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        x[r] = __builtin_fma(F.dt, f[r], b[r]);
+        x[r] = J > 0 ? F.dt * f[r] : __builtin_fma(F.dt, f[r], b[r]);
         if constexpr (J > 0) {
 #pragma unroll
           for (int i = 0; i <= J; ++i) {
             const int k = (i + 1) * R + r;
             x[r] = row_sum(x[r], F.nu_h2, cf[i], cl[i], a[k], b[k], c[k], f[k]);
           }
+          x[r] = b[r] + x[r];
         }
       }
       // PCR over the cycle: periodic rows g = i of n; Dirichlet rows g = i + 1 of the odd extension,
