@@ -33,6 +33,7 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <map>
 #include <mutex>
@@ -1600,10 +1601,19 @@ hipError_t allow_pass() {
   return e;
 }
 
+// Once per device and precision (the attributes stay; setting them costs 50 us a plan).
 hipError_t prepare_pass_kernels(int prec) {
-  return prec == PREC_BF16  ? allow_pass<PREC_BF16>()
-         : prec == PREC_F32 ? allow_pass<PREC_F32>()
-                            : allow_pass<PREC_F64>();
+  static std::atomic<unsigned> done[64];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool known = dev >= 0 && dev < 64;
+  if (known && (done[dev].load(std::memory_order_acquire) >> prec & 1u)) return hipSuccess;
+  e = prec == PREC_BF16  ? allow_pass<PREC_BF16>()
+      : prec == PREC_F32 ? allow_pass<PREC_F32>()
+                         : allow_pass<PREC_F64>();
+  if (e == hipSuccess && known) done[dev].fetch_or(1u << prec, std::memory_order_release);
+  return e;
 }
 
 // transform passes of one step: two per solve, two solves on the refined paths
@@ -1873,12 +1883,58 @@ int arena2d_reserve(size_t nlv, size_t nps, hipStream_t stream) {
   return RIDC_OK;
 }
 
+// Side streams that run groups beside the caller's stream: three of the calling thread's own for the
+// device it used last, given back when the thread ends.  The caller's stream waits for them before a
+// call returns, so to the caller everything stays in its stream's order.
+struct SideStreams {
+  static constexpr int N = 3;
+  int device = -1;
+  hipStream_t s[N] = {};
+  hipEvent_t fork = nullptr, join[N] = {};
+  void release() {
+    for (auto& x : s)
+      if (x) (void)hipStreamDestroy(x);
+    for (auto& x : join)
+      if (x) (void)hipEventDestroy(x);
+    if (fork) (void)hipEventDestroy(fork);
+    *this = SideStreams{};
+  }
+  // the streams of the current device; false (and none) when they cannot be had
+  bool reserve() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    if (device == dev) return true;
+    release();
+    bool ok = hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
+    for (int i = 0; i < N && ok; ++i)
+      ok = hipStreamCreateWithFlags(&s[i], hipStreamNonBlocking) == hipSuccess &&
+           hipEventCreateWithFlags(&join[i], hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      (void)hipGetLastError();
+      release();
+      return false;
+    }
+    device = dev;
+    return true;
+  }
+};
+struct SideStreamsOwner {
+  SideStreams v;
+  ~SideStreamsOwner() {
+    if (v.device >= 0) v.release();
+  }
+};
+thread_local SideStreamsOwner g_side;
+
 }  // namespace
 
 // Advance plans by `steps` pipeline steps.  A single plan uses its own tables.  Several plans
 // are grouped by (precision, n): each group runs every stage of a step as one launch with one
 // grid z-slice per (plan, level), with the same tile shapes as a single plan, so a plan's bits
 // do not depend on its company.  Plan i's own step during launch step s is sigma_before[i] + s.
+// Groups do not depend on each other: the largest keeps the caller's stream and the others run beside
+// it (except under capture), so that the short launches of small grids, which leave most of the chip
+// idle, fill the gaps of the large ones'.
 int plan2d_advance(Plan2D* const* pls, int count, const int64_t* sigma_before, int64_t steps,
                    hipStream_t stream) {
   if (count <= 0 || steps <= 0) return RIDC_OK;
@@ -1941,11 +1997,37 @@ int plan2d_advance(Plan2D* const* pls, int count, const int64_t* sigma_before, i
   RIDC_HIP_TRY(hipMemcpyAsync(g_a2.d_ps, g_a2.h_ps, po * sizeof(Pass2D), hipMemcpyHostToDevice, stream));
   RIDC_HIP_TRY(hipEventRecord(g_a2.done, stream));
   g_a2.pending = true;
+  // lanes: 0 the caller's stream, then the side streams
+  hipStream_t lane[1 + SideStreams::N] = {stream};
+  int nl = 1;
+  if (gs.size() > 1) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(stream, &cap) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    if (known && cap == hipStreamCaptureStatusNone && g_side.v.reserve()) {
+      nl = (int)std::min<size_t>(gs.size(), 1 + SideStreams::N);
+      RIDC_HIP_TRY(hipEventRecord(g_side.v.fork, stream));
+      for (int i = 1; i < nl; ++i) {
+        lane[i] = g_side.v.s[i - 1];
+        RIDC_HIP_TRY(hipStreamWaitEvent(lane[i], g_side.v.fork, 0));
+      }
+    }
+  }
+  std::stable_sort(gs.begin(), gs.end(), [](const G& a, const G& b) {
+    return a.n * a.n * a.n * a.cnt > b.n * b.n * b.n * b.cnt;
+  });
   for (int64_t s = 1; s <= steps; ++s)
-    for (auto& g : gs)
+    for (size_t k = 0; k < gs.size(); ++k) {
+      const G& g = gs[k];
       run_stages(g.prec, g_a2.d_lv + g.lv_off, g_a2.d_ps + g.ps_off, g.cnt, g.n, s, g.tile,
-                 stream);
-  RIDC_HIP_TRY(hipGetLastError());
+                 lane[k % nl]);
+    }
+  const hipError_t launched = hipGetLastError();
+  for (int i = 1; i < nl; ++i) {
+    RIDC_HIP_TRY(hipEventRecord(g_side.v.join[i - 1], lane[i]));
+    RIDC_HIP_TRY(hipStreamWaitEvent(stream, g_side.v.join[i - 1], 0));
+  }
+  RIDC_HIP_TRY(launched);
   RIDC_HIP_TRY(hipEventRecord(g_a2.used, stream));
   g_a2.used_stream = stream;
   g_a2.in_use = true;

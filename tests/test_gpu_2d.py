@@ -162,6 +162,39 @@ def test_split_operands(env, n, count):
             s.close()
 
 
+# groups of one batch run beside each other on streams of the library's own; to the caller all of it is
+# in the order of its stream: inputs written just before, outputs read just after, buffers used again
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_groups_keep_the_order_of_the_callers_stream(env, own_stream):
+    torch, ridc = env
+    stream = torch.cuda.Stream() if own_stream else torch.cuda.current_stream()
+    shapes = [(64, "fp64"), (96, "bf16x3"), (128, "bf16x3"), (160, "fp32"), (256, "fp64"),
+              (256, "bf16x3"), (64, "fp64")]
+    probs = [workloads.config_reacdiff_2d(n=n, nt=5 + i, order=1 + i % 3, T=1e-2, nu=1e-3)
+             for i, (n, _) in enumerate(shapes)]
+    with torch.cuda.stream(stream):
+        solvers = [ridc.Ridc(p, prec=prec) for (p, _), (_, prec) in zip(probs, shapes)]
+        x = [torch.tensor(u.reshape(-1), dtype=torch.float64, device="cuda") for _, u in probs]
+        nts = [p["nt"] for p, _ in probs]
+        want = [[s.integrate(c * a, nt).clone() for s, a, nt in zip(solvers, x, nts)]
+                for c in (1.0, 0.5, 0.25)]
+        bufs, outs = [torch.zeros_like(a) for a in x], [torch.empty_like(a) for a in x]
+        got = []
+        for c in (1.0, 0.5, 0.25):
+            for b, a in zip(bufs, x):
+                torch.mul(a, c, out=b)
+            ridc.integrate_batch(solvers, bufs, nts, outs)
+            got.append([o.clone() for o in outs])
+            for b in bufs:
+                b.fill_(float("nan"))
+    torch.cuda.synchronize()
+    for w, g in zip(want, got):
+        for a, b in zip(w, g):
+            np.testing.assert_array_equal(b.cpu().numpy(), a.cpu().numpy())
+    for s in solvers:
+        s.close()
+
+
 @pytest.mark.parametrize("prec", ["fp64", "bf16x3"])
 def test_kernel_time_leaves_the_integration_unchanged(env, prec):
     """ridc_kernel_time runs the next step's stages again and again around its timed pass; the
