@@ -261,7 +261,7 @@ int choose_tile_1d(const ridc_problem* p, const PcrPlan& pcr, Tile1D* out,
   // where the order allows (512 above), while a chunk with its halos is no longer than twice the
   // system.  Step times, us, of 128-row chunks against the whole cycle in 256 threads, order 4: n =
   // 300 3.6 / 5.9, 999 4.2 / 11.6, 1500 4.2 / 15.4, 2000 4.5 / 20.9; order 8, n = 1024: 4.5 / 10.9.  Against
-  // 1024-row chunks of 256 threads at n = 8192: 5.3 / 10.8.  Whole-range workgroups are chosen in
+  // 1024-row chunks of 256 threads at n = 8192: 5.2 / 10.8.  Whole-range workgroups are chosen in
   // ridc_create (small systems), by ridc_autotune or by ridc_set_tile.
   {
     const int64_t per_level = std::max<int64_t>(1, 256 / p->order);
@@ -722,9 +722,9 @@ Tile1D batch_tile_for(const ridc_handle* h, const BatchTile& bt, int threads) {
 
 // The grouped tiling of a launch over `level_rows` rows of all levels when none was set or measured:
 // the fewer rows there are to fill the chip with, the finer the cut.  Step times, us, of (threads,
-// rows) choices: 1.6e6 rows (256 instances, n 256..4096, order 4) (256, 1536) 20.2, (512, 768) 23, whole
-// cycles in 256 threads 34.9; 4e5 rows (512, 768) 9.7, (256, 1536) 12, whole 30.6; 1e5 rows (512, 512)
-// 6.6, (512, 1536) 8.9, whole 29.2; 2.5e4 rows (512, 384) 5.7, (512, 1536) 8.0, whole 27.1.
+// rows) choices: 1.6e6 rows (256 instances, n 256..4096, order 4) (256, 1536) 18.9, (512, 1536) 21.0,
+// whole cycles in 256 threads 35.0; 4e5 rows (512, 768) 9.1, (512, 1536) 9.8, whole 30.6; 1e5 rows (512,
+// 512) 6.3, (512, 1536) 8.1, whole 29.4; 2.5e4 rows (512, 384) 5.2, (512, 1536) 7.6, whole 27.4.
 BatchTile default_batch_tile(int64_t level_rows) {
   if (level_rows >= 800000) return BatchTile{256, 1536, false};
   if (level_rows >= 200000) return BatchTile{512, 768, false};
