@@ -44,22 +44,19 @@ KERNEL_SOURCE = {
     "2d": os.path.join(ROOT, "paper_1209_4297_amd", "csrc", "kernels_2d.hip"),
 }
 MEASURED_TRAFFIC = {
-    ("reacdiff1d", (1024, 128, 1)): ("1d", "7487c6781845e08d", 4530176),
-    ("reacdiff1d", (1024, 128, 0)): ("1d", "7487c6781845e08d", 4530176),
-    ("batched1d", (256, 1536)): ("1d", "7487c6781845e08d", 72678016),
-    ("batched1d", (512, 1536)): ("1d", "7487c6781845e08d", 72604672),
-    ("reacdiff2d_rhs", "fp64"): ("2d", "1f1d915c37f8735f", 148586752),
-    ("reacdiff2d_rhs", "fp32"): ("2d", "1f1d915c37f8735f", 167388416),
-    ("reacdiff2d_rhs", "bf16x3"): ("2d", "1f1d915c37f8735f", 167307008),
-    # the timed transform pass (the second of a step) per (precision, pass-shape bits)
-    ("reacdiff2d", ("fp64", 0)): ("2d", "1f1d915c37f8735f", 100898304),
-    ("reacdiff2d", ("fp64", 4)): ("2d", "1f1d915c37f8735f", 100911360),
-    ("reacdiff2d", ("fp32", 0)): ("2d", "1f1d915c37f8735f", 50555648),
-    ("reacdiff2d", ("fp32", 4)): ("2d", "1f1d915c37f8735f", 50574080),
-    ("reacdiff2d", ("bf16x3", 0)): ("2d", "1f1d915c37f8735f", 50544384),
-    # bit 2 reshapes only the first pass of each solve: the timed pass is the same kernel
-    ("reacdiff2d", ("bf16x3", 2)): ("2d", "1f1d915c37f8735f", 50544384),
-    ("reacdiff2d", ("bf16x3", 4)): ("2d", "1f1d915c37f8735f", 50552576),
+    ("reacdiff1d", (1024, 128, 1)): ("1d", "287b99411e110a71", 4599808),
+    ("reacdiff1d", (1024, 128, 0)): ("1d", "287b99411e110a71", 4599808),
+    ("batched1d", (256, 1536)): ("1d", "287b99411e110a71", 66931072),
+    ("batched1d", (512, 1536)): ("1d", "287b99411e110a71", 66859008),
+    ("reacdiff2d_rhs", "fp64"): ("2d", "21b32c3af8e635ac", 148313600),
+    ("reacdiff2d_rhs", "fp32"): ("2d", "21b32c3af8e635ac", 167660032),
+    ("reacdiff2d_rhs", "bf16x3"): ("2d", "21b32c3af8e635ac", 166891008),
+    # the timed transform pass (the first of a step) per (precision, pass-shape bits)
+    ("reacdiff2d", ("fp64", 0)): ("2d", "21b32c3af8e635ac", 100765696),
+    ("reacdiff2d", ("fp32", 0)): ("2d", "21b32c3af8e635ac", 50474752),
+    ("reacdiff2d", ("fp32", 1)): ("2d", "21b32c3af8e635ac", 50555648),
+    ("reacdiff2d", ("bf16x3", 0)): ("2d", "21b32c3af8e635ac", 50441216),
+    ("reacdiff2d", ("bf16x3", 2)): ("2d", "21b32c3af8e635ac", 50480128),
 }
 
 
@@ -445,7 +442,8 @@ def shape_name(shape):
     bits = shape[2]
     return {"bits": bits, "threads": shape[0], "wave_columns": 64 if bits & 1 else 32,
             "k_slice": "32 (two LDS stages)" if bits & 2 else "default",
-            "intermediates": "row-major, folded while staging"}
+            "intermediates": "row-major, folded while staging; split BF16: folded and split where "
+                             "they are made"}
 
 
 def stencil_roofline(ridc, s, x0, nt, reps):

@@ -1240,8 +1240,8 @@ int ridc_create(const ridc_problem* p, void* hip_stream, ridc_handle** out) {
       ridc_destroy(h);
       return rc;
     }
-    // untuned split-BF16 plans take the 32-wide k-slices for the first pass of a solve where
-    // they are a choice (whole steps at n = 1024: 229-232 against 233-239 us)
+    // untuned split-BF16 plans take the 32-wide k-slices where
+    // they are a choice (whole steps at n = 1024: 144 against 156 us)
     int tuned = 0;
     if (p->prec == RIDC_PREC_BF16X3_REFINE && !tune_get_2d(p->n, p->prec, &tuned)) {
       std::vector<int> c;

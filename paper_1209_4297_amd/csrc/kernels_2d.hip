@@ -17,7 +17,7 @@
 // column j of T, (1 + dt nu mu_j) x - dt nu D2 x = T_j, and X is the solutions times Q.
 // Diagonalising the columns as well would take two more products by Q, the cost of a pass each
 // (75 us at 1024^2 over four levels in FP64); the line solves read and write each vector once
-// (k_lines2d, 14 us there, which took the step from 305 to 200 us).
+// (k_lines2d, 14 us there; the step went from 305 to 180 us).
 // Each product by Q is one pass C = A Q, a GEMM on the matrix cores (v_mfma_f64_16x16x4f64,
 // v_mfma_f32_16x16x4_f32, or three v_mfma_f32_16x16x32_bf16 products of hi/lo BF16 splits),
 // batched over every active level of every instance in one launch; the final update is fused
@@ -149,8 +149,9 @@ __device__ __forceinline__ unsigned split_bf16(float v) {
 // The operand of a folded split-BF16 pass, 4 n bytes a row like the FP32 values it stands for: for
 // every 8 k < n/2 the BF16 hi and lo of the sums a_k + a_{n-1-k}, then of the differences a_k -
 // a_{n-1-k}, 16 bytes each.  Folding and splitting where the values are made costs each of them once;
-// in the pass every column tile did it again, 0.7 us of vector work for the 0.6 us of matrix work of a
-// slice (24.3 us a pass at 1024^2, four levels).
+// in the pass every column tile did it again.  At 1024^2, four levels: a pass 24.3 -> 22.4 us (20.6 with
+// the LDS rows of ROW_PAD and a second slice on its way), the right-hand side 24.3 -> 26.2, the line
+// solves 9.5 -> 11.3; a whole step 153.7 -> 144.
 // A lane holds x = a_k and y = a_{n-1-k} (low) or the two exchanged and writes two k of one plane:
 // lanes l and l ^ 1 hold neighbouring k and exchange halves.
 __device__ __forceinline__ void store_split(void* row, int k, bool low, float x, float y) {
@@ -1496,8 +1497,9 @@ bool split_operands(int prec, int64_t n) { return prec == PREC_BF16 && folded(n)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Wide k-slices for the split-BF16 pass when the folded contraction is a multiple of twice the
-// slice (measured: 31.9 -> 29.2 us per pass at 1024^2; the FP32 and FP64 passes gain nothing).
+// Wide k-slices for the split-BF16 pass are possible when the folded contraction is a multiple of twice
+// the slice.  An untuned handle takes narrow ones: whole steps, us, wide / narrow, order 4: 1024^2 155.6 /
+// 144.2, 768^2 115.3 / 103.1, 512^2 60.2 / 60.5 (no 128-tiles).
 template <int PREC>
 bool wide_slices(int64_t n) {
   return PREC == PREC_BF16 && folded(n) && (n / 2) % (2 * Tr<PREC>::BK) == 0;
