@@ -914,7 +914,8 @@ constexpr size_t pass_lds_bytes(int fold) {
   return k > ep ? k : ep;
 }
 
-template <int PREC, int OUT, int FOLD, int KX, int BT, int WC>
+// DEEP (small tiles, a multiple of four slices): four slices' loads in flight instead of two.
+template <int PREC, int OUT, int FOLD, int KX, int BT, int WC, bool DEEP = false>
 __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
     const Pass2D* __restrict__ passes, const Lvl2D* __restrict__ levels, int64_t sigma) {
   constexpr int NTHR = pass_threads<BT, WC>();
@@ -1261,15 +1262,9 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
       }
     }
   } else if constexpr (BT < 128) {
-    // small tiles: a pass is a few slices long and bound by the latency of its loads, so two
-    // slices' loads are in flight from the start
-    Slice s0, s1;
-    gload(s0, 0);
-    if (KT > 1) gload(s1, BK);
-    sstore(s0, 0);
-    __syncthreads();
-    auto step = [&](int kt, Slice& mine, Slice& next) {
-      if (kt + 2 < KT) gload(mine, (kt + 2) * BK);
+    // small tiles: a pass is a few slices long and bound by the latency of its loads, so the
+    // loads of two slices, or of four (DEEP), are in flight from the start
+    auto multiply = [&](int kt) {
       if constexpr (PREC == PREC_BF16) {
         FragB f;
         read_frags_bf(kt & 1, 0, f);
@@ -1279,12 +1274,54 @@ __global__ __launch_bounds__((pass_threads<BT, WC>())) void k_pass2d(
         read_frags(kt & 1, fa, fb);
         mfma_frags(fa, fb);
       }
-      if (kt + 1 < KT) sstore(next, (kt + 1) & 1);
-      __syncthreads();
     };
-    for (int kt = 0; kt < KT; kt += 2) {
-      step(kt, s0, s1);
-      if (kt + 1 < KT) step(kt + 1, s1, s0);
+    Slice s0, s1;
+    if constexpr (DEEP) {
+      Slice s2, s3;
+      gload(s0, 0);
+      gload(s1, BK);
+      gload(s2, 2 * BK);
+      gload(s3, 3 * BK);
+      sstore(s0, 0);
+      __syncthreads();
+      // `mine` held slice kt, `next` holds slice kt + 1
+      auto step = [&](int kt, Slice& mine, Slice& next) {
+        gload(mine, (kt + 4) * BK);
+        multiply(kt);
+        sstore(next, (kt + 1) & 1);
+        __syncthreads();
+      };
+      auto last = [&](int kt, Slice& next) {
+        multiply(kt);
+        sstore(next, (kt + 1) & 1);
+        __syncthreads();
+      };
+      int kt = 0;
+      for (; kt + 4 < KT; kt += 4) {
+        step(kt, s0, s1);
+        step(kt + 1, s1, s2);
+        step(kt + 2, s2, s3);
+        step(kt + 3, s3, s0);
+      }
+      last(kt, s1);
+      last(kt + 1, s2);
+      last(kt + 2, s3);
+      multiply(kt + 3);
+    } else {
+      gload(s0, 0);
+      if (KT > 1) gload(s1, BK);
+      sstore(s0, 0);
+      __syncthreads();
+      auto step = [&](int kt, Slice& mine, Slice& next) {
+        if (kt + 2 < KT) gload(mine, (kt + 2) * BK);
+        multiply(kt);
+        if (kt + 1 < KT) sstore(next, (kt + 1) & 1);
+        __syncthreads();
+      };
+      for (int kt = 0; kt < KT; kt += 2) {
+        step(kt, s0, s1);
+        if (kt + 1 < KT) step(kt + 1, s1, s0);
+      }
     }
   } else {
     // Two LDS stages and two register sets of fragments.  Step kt issues the MFMAs of slice kt from
@@ -1554,12 +1591,25 @@ void launch_pass(const Pass2D* d, const Lvl2D* lv, int count, int64_t n, int64_t
     }
     if (fold) go(k_pass2d<PREC, OUT, 1, 1, 128, 32>, 128, pass_threads<128, 32>(), half);
     else go(k_pass2d<PREC, OUT, 0, 1, 128, 32>, 128, pass_threads<128, 32>(), full);
-  } else if (bt == 64) {
-    if (fold) go(k_pass2d<PREC, OUT, 1, 1, 64, 32>, 64, pass_threads<64, 32>(), pass_lds_bytes<PREC, 1, 64>(1));
-    else go(k_pass2d<PREC, OUT, 0, 1, 64, 32>, 64, pass_threads<64, 32>(), pass_lds_bytes<PREC, 1, 64>(0));
   } else {
-    if (fold) go(k_pass2d<PREC, OUT, 1, 1, 32, 16>, 32, pass_threads<32, 16>(), pass_lds_bytes<PREC, 1, 32>(1));
-    else go(k_pass2d<PREC, OUT, 0, 1, 32, 16>, 32, pass_threads<32, 16>(), pass_lds_bytes<PREC, 1, 32>(0));
+    // Whole steps, us, with two slices / four in flight: 256^2 FP64 order 4 26.1 / 24.0, 512^2 order 2 FP64
+    // 44.5 / 41.4, FP32 57.1 / 55.5 and split BF16 49.6 / 46.1, 768^2 order 2 FP32 116 / 104; split BF16
+    // in 64-tiles with one block a CU (512^2 order 4) 60.4 / 56.6, with more (768^2 order 2) 78.5 / 80.8.
+    // Slices that are not a multiple of four need a test at every load (1-2 % slower at 64^2..384^2).
+    const int64_t blocks = ((n + bt - 1) / bt) * ((n + bt - 1) / bt) * count;
+    const bool deep = fold && n / 2 / Tr<PREC>::BK % 4 == 0 &&
+                      !(PREC == PREC_BF16 && bt == 64 && blocks > 256);
+    if (bt == 64) {
+      constexpr size_t half = pass_lds_bytes<PREC, 1, 64>(1);
+      if (deep) go(k_pass2d<PREC, OUT, 1, 1, 64, 32, true>, 64, pass_threads<64, 32>(), half);
+      else if (fold) go(k_pass2d<PREC, OUT, 1, 1, 64, 32>, 64, pass_threads<64, 32>(), half);
+      else go(k_pass2d<PREC, OUT, 0, 1, 64, 32>, 64, pass_threads<64, 32>(), pass_lds_bytes<PREC, 1, 64>(0));
+    } else {
+      constexpr size_t half = pass_lds_bytes<PREC, 1, 32>(1);
+      if (deep) go(k_pass2d<PREC, OUT, 1, 1, 32, 16, true>, 32, pass_threads<32, 16>(), half);
+      else if (fold) go(k_pass2d<PREC, OUT, 1, 1, 32, 16>, 32, pass_threads<32, 16>(), half);
+      else go(k_pass2d<PREC, OUT, 0, 1, 32, 16>, 32, pass_threads<32, 16>(), pass_lds_bytes<PREC, 1, 32>(0));
+    }
   }
 }
 
@@ -1577,8 +1627,10 @@ hipError_t allow_lds() {
   add(&k_pass2d<PREC, OUT, 1, 1, 128, 32>, pass_lds_bytes<PREC, 1, 128>(1));
   add(&k_pass2d<PREC, OUT, 0, 1, 64, 32>, pass_lds_bytes<PREC, 1, 64>(0));
   add(&k_pass2d<PREC, OUT, 1, 1, 64, 32>, pass_lds_bytes<PREC, 1, 64>(1));
+  add(&k_pass2d<PREC, OUT, 1, 1, 64, 32, true>, pass_lds_bytes<PREC, 1, 64>(1));
   add(&k_pass2d<PREC, OUT, 0, 1, 32, 16>, pass_lds_bytes<PREC, 1, 32>(0));
   add(&k_pass2d<PREC, OUT, 1, 1, 32, 16>, pass_lds_bytes<PREC, 1, 32>(1));
+  add(&k_pass2d<PREC, OUT, 1, 1, 32, 16, true>, pass_lds_bytes<PREC, 1, 32>(1));
   if constexpr (PREC == PREC_BF16) {
     add(&k_pass2d<PREC, OUT, 1, 2, 128, 32>, pass_lds_bytes<PREC, 2, 128>(1));
   } else {

@@ -162,6 +162,31 @@ def test_split_operands(env, n, count):
             s.close()
 
 
+# small tiles with a multiple of four k-slices keep four slices' loads in flight: the smallest such sides of
+# each precision and the next, alone (32-tiles), in groups of 64-tiles and in a group of 128-tiles
+@pytest.mark.parametrize("n,prec", [(128, "fp64"), (256, "fp64"), (256, "fp32"), (512, "fp32"),
+                                    (256, "bf16x3"), (512, "bf16x3")])
+def test_four_slices_in_flight(env, n, prec):
+    torch, ridc = env
+    prob, u0 = workloads.config_reacdiff_2d(n=n, nt=3, order=1, T=6e-3, nu=1e-3)
+    _say(f"case: 2D {prec} four slices n={n}")
+    ref = oracle2d(prob, u0)
+    top, lvs = run2d(env, prob, u0, prec=prec)
+    err, emax = errs(lvs[0], ref[0])
+    assert err <= tol_of(prec, 0) and emax <= tol_of(prec, 0), (err, emax)
+    x0 = torch.tensor(u0.reshape(-1), dtype=torch.float64, device="cuda")
+    tiles64, tiles128 = (n // 64) ** 2, (n // 128) ** 2
+    for count in (257 // tiles64 + 1, -(-128 // tiles128)):
+        solvers = [ridc.Ridc(prob, prec=prec) for _ in range(count)]
+        uTs = [torch.empty_like(x0) for _ in range(count)]
+        ridc.integrate_batch(solvers, [x0] * count, [prob["nt"]] * count, uTs)
+        torch.cuda.synchronize()
+        for u in uTs:
+            np.testing.assert_array_equal(u.cpu().numpy().reshape(-1), np.asarray(top).reshape(-1))
+        for s in solvers:
+            s.close()
+
+
 # groups of one batch run beside each other on streams of the library's own; to the caller all of it is
 # in the order of its stream: inputs written just before, outputs read just after, buffers used again
 @pytest.mark.parametrize("own_stream", [False, True])
