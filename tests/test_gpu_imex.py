@@ -207,3 +207,19 @@ def test_level_step_shapes(env, kind, n):
         prob["pairs"] = ["fbe", "ark4"]
         u0 = u0 + 0.1
     check(env, prob, u0, 6)
+
+
+# linear stages at large r = dt nu / h^2, where the identity in I - tau nu D2 is small beside the
+# Laplacian and the rounding of one solve grows with r: r = 25 .. 1e4 at n = 1000 and 1.7e3 .. 6.7e5
+# at n = 8191
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+@pytest.mark.parametrize("pairs", [("fbe",), ("fbe", "fbe"), ("ark3",)], ids=["fbe", "fbe2", "ark3"])
+@pytest.mark.parametrize("n,nu", [(1000, 0.1), (1000, 1.0), (8191, 0.1), (8191, 1.0)])
+def test_linear_stages_at_large_r(env, n, nu, pairs, bc):
+    nt = 100
+    if bc == "dirichlet":
+        prob, u0 = workloads.config_reacdiff_1d(n=n, nt=nt, order=len(pairs))
+    else:
+        prob, _ = workloads.config_advdiff_1d(n=n, nt=nt, order=len(pairs))
+        u0 = workloads.fourier_modes_1d(n, np.random.default_rng(n))
+    check(env, dict(prob, nu=nu, a=0.01, T=1.0, pairs=list(pairs)), u0, nt)
