@@ -134,13 +134,13 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 }
 
 // 1 / b (b of moderate size) from the hardware estimate (2^-24) and two Newton steps, about an
-// ulp; NEWTON: one step, 2^-48, for solves that Newton's method repeats.  Used in the solves only,
-// whose results are corrections.
-template <bool NEWTON>
+// ulp.  Used in the solves only, whose results are corrections.  (With one step, 2^-48, in the solves
+// of a stiff reaction, the cubic one's steps took 2-3 % less and ended 1.5 times as far from the
+// exact solution: a last update of some 1e-15 is not exact enough then.)
 __device__ __forceinline__ double recip(double b) {
   double x = __builtin_amdgcn_rcp(b);
   x = __builtin_fma(__builtin_fma(-b, x, 1.0), x, x);
-  return NEWTON ? x : __builtin_fma(__builtin_fma(-b, x, 1.0), x, x);
+  return __builtin_fma(__builtin_fma(-b, x, 1.0), x, x);
 }
 
 // The largest v of the wave: of doubles (NaN passed over), or of non-negative ints.
@@ -283,7 +283,7 @@ __device__ __forceinline__ double fstiff(const Ctx& c, double um, double u0, dou
 // a x_{q-S} + x_q + c x_{q+S} = d, takes rows q -+ S.  Past the row's ends the coupling stays (to
 // the unknown before or after the row): a missing row reads as (a, c, d) = (-1, 0, 0) below and
 // (0, -1, 0) above.
-template <int S, int NR, bool NW>
+template <int S, int NR>
 __device__ __forceinline__ void reduce_stage(double& a, double& c, double (&d)[NR]) {
   const double am = move<kUp + S>(a, -1.0), cm = move0<kUp + S>(c);
   const double ap = move0<kDown + S>(a), cp = move<kDown + S>(c, -1.0);
@@ -293,19 +293,19 @@ __device__ __forceinline__ void reduce_stage(double& a, double& c, double (&d)[N
     dm[k] = move0<kUp + S>(d[k]);
     dp[k] = move0<kDown + S>(d[k]);
   }
-  const double inv = recip<NW>(__builtin_fma(-a, cm, __builtin_fma(-c, ap, 1.0)));
+  const double inv = recip(__builtin_fma(-a, cm, __builtin_fma(-c, ap, 1.0)));
 #pragma unroll
   for (int k = 0; k < NR; ++k)
     d[k] = __builtin_fma(-a, dm[k], __builtin_fma(-c, dp[k], d[k])) * inv;
   a = -a * am * inv;
   c = -c * cp * inv;
 }
-template <int NR, bool NW>
+template <int NR>
 __device__ __forceinline__ void reduce_row(double& a, double& c, double (&d)[NR]) {
-  reduce_stage<1, NR, NW>(a, c, d);
-  reduce_stage<2, NR, NW>(a, c, d);
-  reduce_stage<4, NR, NW>(a, c, d);
-  reduce_stage<8, NR, NW>(a, c, d);
+  reduce_stage<1, NR>(a, c, d);
+  reduce_stage<2, NR>(a, c, d);
+  reduce_stage<4, NR>(a, c, d);
+  reduce_stage<8, NR>(a, c, d);
 }
 
 // Solve the tridiagonal system with off-diagonals -r (zero at Dirichlet ends; periodic: cyclic
@@ -313,7 +313,7 @@ __device__ __forceinline__ void reduce_row(double& a, double& c, double (&d)[NR]
 // rows(i, b, d).  x receives this thread's rows of the solution (padding rows: 0).
 // Periodic (PER): d0 is the diagonal of row 0; the second right-hand side is the rank-one
 // correction's vector.
-template <int M, bool PER, bool NW, typename Rows>
+template <int M, bool PER, typename Rows>
 __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows,
                                           double (&x)[M]) {
   constexpr int NR = PER ? 2 : 1;
@@ -343,7 +343,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
       }
     }
     if (i > 0) b = __builtin_fma(-r, E[i - 1], b);
-    double inv = recip<NW>(b);
+    double inv = recip(b);
     inv = g < n ? inv : 0.0;
     E[i] = r * inv;
 #pragma unroll
@@ -364,7 +364,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
   double ra, rc, rd[NR];
   {
     const double an = move0<kDown + 1>(a0), cn = move0<kDown + 1>(c0);
-    const double inv = recip<NW>(__builtin_fma(-Cl, an, 1.0));
+    const double inv = recip(__builtin_fma(-Cl, an, 1.0));
     ra = tail ? 0.0 : A * inv;
     rc = tail ? -1.0 : -Cl * cn * inv;
 #pragma unroll
@@ -373,7 +373,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
       rd[q] = tail ? 0.0 : __builtin_fma(-Cl, dn, D[q][M - 1]) * inv;
     }
   }
-  reduce_row<NR, NW>(ra, rc, rd);
+  reduce_row<NR>(ra, rc, rd);
   // the group's equations: its last unknown L + a XL + c F' = d (XL: the last unknown of the group
   // before, F': the first row of the next group), its first row F + a XL + c L = d
   double* gr = c.grp + (c.gk & 1) * grp_doubles(NR);
@@ -386,7 +386,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
 #pragma unroll
     for (int q = 0; q < NR; ++q) d14[q] = move0<kUp + 1>(rd[q]);
     if (tail) {
-      const double inv = recip<NW>(__builtin_fma(-A, c14, 1.0));
+      const double inv = recip(__builtin_fma(-A, c14, 1.0));
       gr[grp] = -A * a14 * inv;
       gr[kGroups + grp] = Cl * inv;
 #pragma unroll
@@ -411,7 +411,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
     const bool nx = q0 + 1 < G;
     const double af = nx ? gf[q0 + 1] : 0.0, cf = nx ? gf[kGroups + q0 + 1] : 0.0;
     const double cl = gr[kGroups + q0];
-    const double inv = recip<NW>(__builtin_fma(-cl, af, 1.0));
+    const double inv = recip(__builtin_fma(-cl, af, 1.0));
     ga = gr[q0] * inv;
     gc = -cl * cf * inv;
 #pragma unroll
@@ -420,7 +420,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
       gd[q] = __builtin_fma(-cl, df, gr[(2 + q) * kGroups + q0]) * inv;
     }
   }
-  reduce_row<NR, NW>(ga, gc, gd);
+  reduce_row<NR>(ga, gc, gd);
   double X[NR];                                  // group q0's last unknown
   if (G <= 16) {
 #pragma unroll
@@ -433,7 +433,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
     for (int s = 0; s < 4; ++s) {
       const double aF = lane_value(ga, 16 * s), cF = lane_value(gc, 16 * s);
       const double aL = lane_value(ga, 16 * s + 15), cL = lane_value(gc, 16 * s + 15);
-      const double inv = recip<NW>(__builtin_fma(-aF, be, 1.0));
+      const double inv = recip(__builtin_fma(-aF, be, 1.0));
       z[s] = cF * inv;
       bl[s] = __builtin_fma(aL * be, z[s], cL);
 #pragma unroll
@@ -549,7 +549,7 @@ __device__ __forceinline__ void stage_solve(Ctx& c, double tau, int maxit, Rhs r
     for (int it = 0; it < kMaxCorrections; ++it) {
       double delta[M], yh[M + 2];
       with_halo<M, PER>(c, y, e, yh);
-      tri_solve<M, PER, false>(
+      tri_solve<M, PER>(
           c, r, b0,
           [&](int i, double& b, double& d) __attribute__((always_inline)) {
             d = rhs_at(i) - (y[i] - tau * c.nu_h2 * (yh[i + 2] - 2.0 * y[i] + yh[i]));
@@ -575,7 +575,7 @@ __device__ __forceinline__ void stage_solve(Ctx& c, double tau, int maxit, Rhs r
   for (int it = 0; it < maxit && !done; ++it) {
     double delta[M], yh[M + 2];
     with_halo<M, PER>(c, y, e, yh);
-    tri_solve<M, PER, true>(
+    tri_solve<M, PER>(
         c, r, b0,
         [&](int i, double& b, double& d) __attribute__((always_inline)) {
           d = rhs_at(i) - (y[i] - tau * fstiff(c, yh[i], y[i], yh[i + 2]));
