@@ -745,13 +745,27 @@ __device__ __forceinline__ void imex_step(const ImexLvl& L, int64_t sigma, bool 
 #pragma unroll
       for (int x = 0; x < M; ++x) Y[x] = rhs[x];
     }
-    for (int l = 0; l < 2 * i; ++l) {
-      const double al = dt * (l & 1 ? L.AN[i][l >> 1] : L.AS[i][l >> 1]);
-      if (al == 0.0) continue;
+    // the two terms of a stage are added up before the value, whose size sets the rounding: once a
+    // stage and not twice
+    for (int l = 0; l < i; ++l) {
+      const double as = dt * L.AS[i][l], an = dt * L.AN[i][l];
+      if (as == 0.0 && an == 0.0) continue;
       double k[M];
-      load_rows<M>(c, ks + l * V, k);
 #pragma unroll
-      for (int x = 0; x < M; ++x) rhs[x] += al * k[x];
+      for (int x = 0; x < M; ++x) k[x] = 0.0;
+      if (as != 0.0) {
+        load_rows<M>(c, ks + 2 * l * V, k);
+#pragma unroll
+        for (int x = 0; x < M; ++x) k[x] *= as;
+      }
+      if (an != 0.0) {
+        double kn[M];
+        load_rows<M>(c, ks + (2 * l + 1) * V, kn);
+#pragma unroll
+        for (int x = 0; x < M; ++x) k[x] += an * kn[x];
+      }
+#pragma unroll
+      for (int x = 0; x < M; ++x) rhs[x] += k[x];
     }
     // the largest blocks keep the right-hand side in LDS during the solve
     constexpr bool kMem = M >= 16;

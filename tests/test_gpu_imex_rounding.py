@@ -100,3 +100,14 @@ def test_newton_stage_is_as_exact_as_the_oracles(env, n):
                                          pairs=("fbe",))
     gpu, oracle = distances(env, prob, "fbe", u0, 60)
     assert gpu <= oracle
+
+
+def test_stage_sums_round_as_often_as_the_oracles(env):
+    # several stages a step: the right-hand side of a stage adds earlier stages to the value, and each
+    # addition rounds it; the oracle adds the two terms of a stage at once.  r = 17, where nothing else
+    # shows.  Half as much again for the different places of the other roundings
+    prob, _ = workloads.config_advdiff_1d(n=8191, nt=100, order=1)
+    u0 = workloads.fourier_modes_1d(8191, np.random.default_rng(8191))
+    prob = dict(prob, nu=1e-3, a=0.01, T=1.0, pairs=["ark3"])
+    gpu, oracle = distances(env, prob, "ark3", u0, 60)
+    assert gpu <= 1.5 * oracle
