@@ -32,9 +32,9 @@
 //     per thread, in the blocks' last unknowns;
 //  2. parallel cyclic reduction with DPP moves inside the rows of 16 lanes, whose last lane stays
 //     an unknown: two equations per 16 threads (its first and its last unknown) go to LDS;
-//  3. every wave reads all of them (at most 64 groups, one per lane), joins them into a
-//     tridiagonal system of the groups' last unknowns, reduces its four rows of 16 lanes the same
-//     way and eliminates the last four in order.
+//  3. every wave reads all of them (at most 32 groups, one per lane), joins them into a
+//     tridiagonal system of the groups' last unknowns, reduces its rows of 16 lanes the same way and
+//     eliminates the last unknowns of the two rows in order.
 // The unknowns come back the same way: by registers, lane moves and no further barrier.
 // Periodic grids (cyclic systems) take the Sherman-Morrison correction: the cyclic matrix is a
 // tridiagonal one plus a rank-one term, so one solve with two right-hand sides and a scalar
@@ -100,6 +100,8 @@ struct Ctx {
   int gk, xk;      // buffer toggles
 };
 constexpr int kGroups = kImexMaxThreads / 16;
+constexpr int kGroupRows = kGroups / 16;         // rows of 16 lanes that hold one group a lane
+static_assert(kGroups % 16 == 0 && kGroups <= 64, "one group per lane of a wave");
 constexpr int kWaves = kImexMaxThreads / 64;
 // values of one edge buffer: per right-hand side 2 per wave and 2 rows; then 2 maxima per wave
 __host__ __device__ constexpr int ex_doubles(int NR) { return NR * (2 * kWaves + 2) + 2 * kWaves; }
@@ -428,9 +430,9 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
   } else {
     // the rows of 16 groups in order: F_r = y - z F_{r+1} and L_r = al - be F_{r+1} for their first
     // and last unknowns
-    double be = 0.0, y[NR][4], z[4], al[NR][4], bl[4];
+    double be = 0.0, y[NR][kGroupRows], z[kGroupRows], al[NR][kGroupRows], bl[kGroupRows];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < kGroupRows; ++s) {
       const double aF = lane_value(ga, 16 * s), cF = lane_value(gc, 16 * s);
       const double aL = lane_value(ga, 16 * s + 15), cL = lane_value(gc, 16 * s + 15);
       const double inv = recip(__builtin_fma(-aF, be, 1.0));
@@ -450,7 +452,7 @@ __device__ __forceinline__ void tri_solve(Ctx& c, double r, double d0, Rows rows
     for (int q = 0; q < NR; ++q) {
       double F = 0.0, before = 0.0, after = 0.0;
 #pragma unroll
-      for (int s = 3; s >= 0; --s) {
+      for (int s = kGroupRows - 1; s >= 0; --s) {
         const double L = __builtin_fma(-bl[s], F, al[q][s]);
         if (row == s) after = F;
         if (row == s + 1) before = L;
