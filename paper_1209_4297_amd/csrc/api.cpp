@@ -600,9 +600,19 @@ int launch_fused_steps(ridc_handle* h, int64_t first, int64_t last) {
   return RIDC_OK;
 }
 
+// Whether `steps` steps of one handle are a whole-range launch.  k_small1d loads every level's ring
+// and stores it again, as much work as one to four steps.  A step, us, in ranges of 1 / 2 / 3 steps
+// against launches per step (which hide under each other): n = 64 order 4 4.9 / 2.5 / 1.9 against
+// 3.6, n = 128 order 6 6.8 / 3.9 / 3.0 against 3.9, n = 256 order 4 7.1 / 4.4 / 3.5 against 3.8 and
+// order 6 9.5 / 5.8 / 4.8 (4: 4.0, 6: 3.4) against 3.8.
+bool whole_range(const ridc_handle* h, int64_t steps) {
+  if (!h->fused && !h->small) return false;
+  return !h->small_ok || steps > std::max<int64_t>(1, h->p.n * h->P / 384);
+}
+
 int run_solo_steps(ridc_handle* h, int64_t first, int64_t last) {
   if (h->imex) return launch_imex_steps(h, first, last);
-  if (h->p.dim == 1 && (h->fused || h->small)) return launch_fused_steps(h, first, last);
+  if (h->p.dim == 1 && whole_range(h, last - first + 1)) return launch_fused_steps(h, first, last);
   if (h->p.dim == 1) return launch_solo_steps_1d(h, first, last);
   Plan2D* pl = h->p2;
   const int64_t before = first - 1;

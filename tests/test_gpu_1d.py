@@ -507,3 +507,40 @@ def test_default_tilings_equal_whole_cycles(env, bc, n, order, nu):
     want, lv_w = run_gpu(env, prob, u0, tile=(256, 0, 0))
     np.testing.assert_array_equal(got, want)
     np.testing.assert_array_equal(lv, lv_w)
+
+
+def _step_time(env, s, x0, k):
+    """Least time of a pipeline step, us, over runs of advances by k steps."""
+    import time
+    torch, ridc = env
+    s.begin(x0, 10**6)
+    ridc.advance([s], 100)
+    best = 1e30
+    for _ in range(10):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(240 // k):
+            ridc.advance([s], k)
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / (240 // k * k))
+    return best * 1e6
+
+
+@pytest.mark.parametrize("n,order", [(64, 4), (128, 6), (256, 1), (256, 4), (256, 6)])
+def test_short_ranges_of_small_systems(env, n, order):
+    """A handle advanced a step or a few at a time (serving) costs no more than launches per step: the
+    whole-range workgroup, which loads and stores all rings, takes the ranges that pay for it (it cost up
+    to 3.3 times a step).  A third above is left for the spread of the timing."""
+    torch, ridc = env
+    x = workloads.grid_points("periodic", n, 2 * math.pi)
+    x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
+    prob = dict(dim=1, bc="periodic", n=n, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3, T=0.05,
+                nt=1000, order=order)
+    s, per_step = ridc.Ridc(prob), ridc.Ridc(prob)
+    per_step.set_tile(256, 0, 0)
+    for k in (1, 2, 3):
+        a, b = _step_time(env, s, x0, k), _step_time(env, per_step, x0, k)
+        _say(f"case: n={n} P={order} ranges of {k}: {a:.2f} us a step, per-step launches {b:.2f}")
+        assert a <= 1.33 * b
+    s.close()
+    per_step.close()
