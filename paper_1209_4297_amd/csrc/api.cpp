@@ -1488,7 +1488,7 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
         F.nt = h->nt;
         F.sigma0 = 0;
         F.sigma_first = h->sigma;
-        F.sigma_last = std::min(h->total, h->sigma + max_steps);
+        F.sigma_last = h->sigma + std::min(max_steps, h->total - h->sigma);
         g_arena.h_fused[i] = F;
       }
       RIDC_HIP_TRY(hipMemcpyAsync(g_arena.d_fused, g_arena.h_fused, sizeof(Fused1D) * hw.size(),
@@ -1502,7 +1502,7 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
                                      stream));
       rc = arena_release(stream);
       if (rc != RIDC_OK) return rc;
-      for (auto* h : hw) h->sigma = std::min(h->total, h->sigma + max_steps);
+      for (auto* h : hw) h->sigma += std::min(max_steps, h->total - h->sigma);
     }
   }
   if (!h1.empty()) {

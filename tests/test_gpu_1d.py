@@ -544,3 +544,28 @@ def test_short_ranges_of_small_systems(env, n, order):
         assert a <= 1.33 * b
     s.close()
     per_step.close()
+
+
+def test_a_batch_takes_all_the_steps_there_are(env):
+    """The largest max_steps advances every instance to its end, also after a first advance."""
+    torch, ridc = env
+    for sizes in ((64, 100), (100, 300)):          # whole ranges in one workgroup; grouped launches
+        solvers, x0s, want = [], [], []
+        for n in sizes:
+            x = workloads.grid_points("periodic", n, 2 * math.pi)
+            x0s.append(torch.tensor(np.sin(x), dtype=torch.float64, device="cuda"))
+            prob = dict(dim=1, bc="periodic", n=n, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3,
+                        T=0.05, nt=20, order=3)
+            solvers.append(ridc.Ridc(prob))
+            want.append(solvers[-1].integrate(x0s[-1], 20).clone())
+        for s, x0 in zip(solvers, x0s):
+            s.begin(x0, 20)
+        ridc.advance(solvers, 3)
+        ridc.advance(solvers, 2**63 - 1)
+        for s, x0, w in zip(solvers, x0s, want):
+            assert s.remaining() == 0
+            out = torch.empty_like(x0)
+            s.read(out)
+            s.sync()
+            assert torch.equal(out, w)
+            s.close()
