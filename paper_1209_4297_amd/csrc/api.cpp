@@ -586,17 +586,10 @@ int launch_fused_steps(ridc_handle* h, int64_t first, int64_t last) {
   F.sigma0 = 0;
   F.sigma_first = first - 1;
   F.sigma_last = last;
-  if (!h->small_ok) {
-    RIDC_HIP_TRY(launch_fused_1d(nullptr, &F, 1, h->P, h->fused_threads, h->fused_lds, h->stream));
-    return RIDC_OK;
-  }
-  // at most 2^16 steps (0.2 s) a launch: the default for small systems holds the stream's other work
-  // up no longer
-  for (int64_t f = first - 1; f < last; f += 1 << 16) {
-    F.sigma_first = f;
-    F.sigma_last = std::min<int64_t>(last, f + (1 << 16));
-    RIDC_HIP_TRY(launch_small_1d(nullptr, &F, 1, h->P, h->small_lds, h->stream));
-  }
+  RIDC_HIP_TRY(h->small_ok ? launch_small_1d(nullptr, &F, 1, h->P, last - first + 1, h->small_lds,
+                                             h->stream)
+                           : launch_fused_1d(nullptr, &F, 1, h->P, h->fused_threads, h->fused_lds,
+                                             h->stream));
   return RIDC_OK;
 }
 
@@ -1477,6 +1470,7 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
       rc = arena_reserve_fused(hw.size());
       if (rc != RIDC_OK) return rc;
       int maxP = 1;
+      int64_t longest = 0;
       size_t lds = 0;
       for (size_t i = 0; i < hw.size(); ++i) {
         ridc_handle* h = hw[i];
@@ -1489,6 +1483,7 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
         F.sigma0 = 0;
         F.sigma_first = h->sigma;
         F.sigma_last = h->sigma + std::min(max_steps, h->total - h->sigma);
+        longest = std::max(longest, F.sigma_last - F.sigma_first);
         g_arena.h_fused[i] = F;
       }
       RIDC_HIP_TRY(hipMemcpyAsync(g_arena.d_fused, g_arena.h_fused, sizeof(Fused1D) * hw.size(),
@@ -1496,7 +1491,8 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
       RIDC_HIP_TRY(hipEventRecord(g_arena.done, stream));
       g_arena.pending = true;
       if (small)
-        RIDC_HIP_TRY(launch_small_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, lds, stream));
+        RIDC_HIP_TRY(launch_small_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, longest, lds,
+                                     stream));
       else
         RIDC_HIP_TRY(launch_fused_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, 512, lds,
                                      stream));

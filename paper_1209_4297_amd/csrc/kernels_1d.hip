@@ -580,11 +580,10 @@ __device__ __forceinline__ void fe_points(int fe, double ce, const double (&m)[K
   else all(std::integral_constant<int, RIDC_FE_NONE>{});
 }
 
-// Every step of level J in sigma_first+1 .. sigma_last: one barrier per step, whether the level is
-// active or not.
+// Every step of level J in first+1 .. last: one barrier per step, whether the level is active or not.
 template <int J, int R, bool PER>
 __device__ __forceinline__ void small_run(const Fused1D& F, SmallLvl L, int lane, double gam,
-                                          int shift) {
+                                          int shift, int64_t first, int64_t last) {
   const int n = F.n, M = F.M, st = n + 2, stages = F.stages;
   constexpr int g0 = PER ? 0 : 1;    // cycle row of grid row 0
   constexpr int K = J > 0 ? (J + 2) * R : R;
@@ -593,9 +592,9 @@ __device__ __forceinline__ void small_run(const Fused1D& F, SmallLvl L, int lane
 #pragma unroll
   for (int r = 0; r < R; ++r) row[r] = r * 64 + lane < n ? r * 64 + lane : n - 1;
   double cf[J + 1], cl[J + 1];
-  int64_t m = F.sigma_first + 1 - F.sigma0 - (int64_t)J * (J + 1) / 2;
+  int64_t m = first + 1 - F.sigma0 - (int64_t)J * (J + 1) / 2;
   bool fresh = true;
-  for (int64_t sigma = F.sigma_first + 1; sigma <= F.sigma_last; ++sigma, ++m) {
+  for (int64_t sigma = first + 1; sigma <= last; ++sigma, ++m) {
     if (m >= 1 && m <= F.nt) {
       L.sw = L.su + 1 == Ro ? 0 : L.su + 1;
       if (J > 0 && (fresh || m <= J + 1)) {
@@ -700,13 +699,13 @@ __device__ __forceinline__ void small_run(const Fused1D& F, SmallLvl L, int lane
 }
 
 template <int MJ, int R, bool PER>
-__device__ __forceinline__ void small_rows(const Fused1D& F) {
+__device__ __forceinline__ void small_rows(const Fused1D& F, int64_t first, int64_t last) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x & 63;
   const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // this wave's level
   if (j >= F.P) {                            // a grouped launch's deeper items: barriers only
     __syncthreads();
-    for (int64_t sigma = F.sigma_first + 1; sigma <= F.sigma_last; ++sigma) __syncthreads();
+    for (int64_t sigma = first + 1; sigma <= last; ++sigma) __syncthreads();
     return;
   }
   const int n = F.n, st = n + 2;
@@ -761,18 +760,18 @@ __device__ __forceinline__ void small_rows(const Fused1D& F) {
   const int sl = lane < F.stages ? lane : 0;
   const double gam = gp(F.gamma)[sl];
   const int shift = gp(F.shift)[sl];
-  int64_t m = F.sigma_first + 1 - F.sigma0 - (int64_t)j * (j + 1) / 2;
+  int64_t m = first + 1 - F.sigma0 - (int64_t)j * (j + 1) / 2;
   const int64_t m0 = m > 1 ? m : 1;          // first step this level takes here
   L.su = ring_slot(m0 - 1, Ro);
   L.sp = j > 0 ? ring_slot(m0 > j ? m0 - j : 0, L.R_prev) : 0;
   __syncthreads();
   switch (j) {
-    case 0: small_run<0, R, PER>(F, L, lane, gam, shift); break;
-    case 1: if constexpr (MJ >= 1) small_run<1, R, PER>(F, L, lane, gam, shift); break;
-    case 2: if constexpr (MJ >= 2) small_run<2, R, PER>(F, L, lane, gam, shift); break;
-    case 3: if constexpr (MJ >= 3) small_run<3, R, PER>(F, L, lane, gam, shift); break;
-    case 4: if constexpr (MJ >= 4) small_run<4, R, PER>(F, L, lane, gam, shift); break;
-    default: if constexpr (MJ >= 5) small_run<5, R, PER>(F, L, lane, gam, shift); break;
+    case 0: small_run<0, R, PER>(F, L, lane, gam, shift, first, last); break;
+    case 1: if constexpr (MJ >= 1) small_run<1, R, PER>(F, L, lane, gam, shift, first, last); break;
+    case 2: if constexpr (MJ >= 2) small_run<2, R, PER>(F, L, lane, gam, shift, first, last); break;
+    case 3: if constexpr (MJ >= 3) small_run<3, R, PER>(F, L, lane, gam, shift, first, last); break;
+    case 4: if constexpr (MJ >= 4) small_run<4, R, PER>(F, L, lane, gam, shift, first, last); break;
+    default: if constexpr (MJ >= 5) small_run<5, R, PER>(F, L, lane, gam, shift, first, last); break;
   }
   for (int q = 0; q < Ro; ++q) {
     double v[R];
@@ -785,27 +784,32 @@ __device__ __forceinline__ void small_rows(const Fused1D& F) {
 }
 
 template <int MJ>
-__device__ __forceinline__ void small_body(const Fused1D& F) {
+__device__ __forceinline__ void small_body(const Fused1D& F, int64_t first, int64_t last) {
   if (F.bc == RIDC_BC_PERIODIC) {
-    if (F.n <= 64) small_rows<MJ, 1, true>(F);
-    else if (F.n <= 128) small_rows<MJ, 2, true>(F);
-    else small_rows<MJ, 4, true>(F);
+    if (F.n <= 64) small_rows<MJ, 1, true>(F, first, last);
+    else if (F.n <= 128) small_rows<MJ, 2, true>(F, first, last);
+    else small_rows<MJ, 4, true>(F, first, last);
   } else {
-    if (F.n <= 64) small_rows<MJ, 1, false>(F);
-    else if (F.n <= 128) small_rows<MJ, 2, false>(F);
-    else small_rows<MJ, 4, false>(F);
+    if (F.n <= 64) small_rows<MJ, 1, false>(F, first, last);
+    else if (F.n <= 128) small_rows<MJ, 2, false>(F, first, last);
+    else small_rows<MJ, 4, false>(F, first, last);
   }
 }
 
+// The steps of every instance's range from `skip` on, kSmallSteps at most.
 template <int MJ>
-__global__ __launch_bounds__(64 * (MJ + 1)) void k_small1d(const Fused1D* __restrict__ items) {
-  small_body<MJ>(items[blockIdx.x]);
+__global__ __launch_bounds__(64 * (MJ + 1)) void k_small1d(const Fused1D* __restrict__ items,
+                                                          int64_t skip) {
+  const Fused1D& F = items[blockIdx.x];
+  const int64_t first = F.sigma_first + skip;
+  if (first >= F.sigma_last) return;
+  small_body<MJ>(F, first, F.sigma_last - first > kSmallSteps ? first + kSmallSteps : F.sigma_last);
 }
 
 // One instance, descriptor in the kernel arguments.
 template <int MJ, int R, bool PER>
 __global__ __launch_bounds__(64 * (MJ + 1)) void k_small1d_one(const Fused1D F) {
-  small_rows<MJ, R, PER>(F);
+  small_rows<MJ, R, PER>(F, F.sigma_first, F.sigma_last);
 }
 
 __global__ void k_nonfinite(const double* __restrict__ x, int64_t count, int* flag) {
@@ -1040,16 +1044,24 @@ hipError_t prepare_small_1d(const Fused1D& F, int lds_bytes) {
 }
 
 hipError_t launch_small_1d(const Fused1D* d_items, const Fused1D* one, int count, int max_order,
-                           size_t lds_bytes, hipStream_t stream) {
+                           int64_t steps, size_t lds_bytes, hipStream_t stream) {
   if (max_order > kMaxJ1024 + 1) return hipErrorInvalidValue;
-  if (one) {
-    void* args[] = {const_cast<Fused1D*>(one)};
-    return hipLaunchKernel(small_kernel(one->P, one->n, one->bc), dim3(1), dim3(64 * one->P), args,
-                           lds_bytes, stream);
+  hipError_t e = hipSuccess;
+  for (int64_t skip = 0; skip < steps && e == hipSuccess; skip += kSmallSteps) {
+    if (one) {
+      Fused1D F = *one;
+      F.sigma_first += skip;
+      if (F.sigma_last - F.sigma_first > kSmallSteps) F.sigma_last = F.sigma_first + kSmallSteps;
+      void* args[] = {&F};
+      e = hipLaunchKernel(small_kernel(F.P, F.n, F.bc), dim3(1), dim3(64 * F.P), args, lds_bytes,
+                          stream);
+    } else {
+      void* args[] = {&d_items, &skip};
+      e = hipLaunchKernel(small_items_kernel(max_order), dim3(count), dim3(64 * max_order), args,
+                          lds_bytes, stream);
+    }
   }
-  void* args[] = {&d_items};
-  return hipLaunchKernel(small_items_kernel(max_order), dim3(count), dim3(64 * max_order), args,
-                         lds_bytes, stream);
+  return e;
 }
 
 hipError_t launch_nonfinite_check(const double* x, int64_t count, int* flag, hipStream_t stream) {

@@ -155,13 +155,16 @@ hipError_t launch_fused_1d(const Fused1D* d_items, const Fused1D* one, int count
 
 // As launch_fused_1d for small systems: one workgroup per instance, one wave per level, the rings in
 // LDS.  Every instance has n <= kSmallRows, and lds_bytes covers lds_bytes_small_1d(n, ring slots of
-// all levels, order) of each; max_order <= kMaxJ1024 + 1.  prepare_small_1d (a host call, never inside
+// all levels, order) of each; max_order <= kMaxJ1024 + 1; `steps` covers the longest range.  A launch
+// runs at most kSmallSteps of them (0.2 s), so that the default for small systems holds the stream's
+// other work up no longer.  prepare_small_1d (a host call, never inside
 // graph capture) allows the kernels that can take instance F lds_bytes of LDS.
 constexpr int kSmallRows = 256;
+constexpr int64_t kSmallSteps = 1 << 16;
 size_t lds_bytes_small_1d(int n, int slots, int order);
 hipError_t prepare_small_1d(const Fused1D& F, int lds_bytes);
 hipError_t launch_small_1d(const Fused1D* d_items, const Fused1D* one, int count, int max_order,
-                           size_t lds_bytes, hipStream_t stream);
+                           int64_t steps, size_t lds_bytes, hipStream_t stream);
 
 // One vector copy of a batched copy launch: dst[0..n) = src[0..n); if flag is not null, *flag is
 // set to 1 when a copied value is not finite.

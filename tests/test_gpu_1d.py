@@ -569,3 +569,25 @@ def test_a_batch_takes_all_the_steps_there_are(env):
             s.sync()
             assert torch.equal(out, w)
             s.close()
+
+
+def test_long_ranges_of_a_batch_go_by_several_launches(env):
+    """Instances with more steps than one launch of small systems takes (65536), less and just as many,
+    in a batch: the same bits as launches per step."""
+    torch, ridc = env
+    solvers, x0s, nts, want = [], [], [], []
+    for n, nt in ((5, 65536 + 700), (2, 65536 - 1), (7, 65536), (3, 900), (5, 2 * 65536 + 1)):
+        x = workloads.grid_points("periodic", n, 2 * math.pi)
+        prob = dict(dim=1, bc="periodic", n=n, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3,
+                    T=1e-4 * nt, nt=nt, order=2)
+        u0 = 0.5 + np.cos(x)
+        want.append(run_gpu(env, prob, u0, tile=(256, 0, 0))[0])
+        solvers.append(ridc.Ridc(prob))
+        x0s.append(torch.tensor(u0, dtype=torch.float64, device="cuda"))
+        nts.append(nt)
+    uTs = [torch.empty_like(x0) for x0 in x0s]
+    ridc.integrate_batch(solvers, x0s, nts, uTs)
+    torch.cuda.synchronize()
+    for s, uT, w in zip(solvers, uTs, want):
+        np.testing.assert_array_equal(uT.cpu().numpy(), w)
+        s.close()
