@@ -305,8 +305,10 @@ int ridc_tune_clear(void);
  * stream, starting at the handle's next pipeline step (which must have every level active):
  *  - 1D, one launch per step: `reps` back-to-back launches of that step (each recomputes the
  *    same values; the handle does not advance);
- *  - 1D, whole-integration workgroup (systems that fit one CU's LDS): one launch running
- *    `reps` steps; the handle runs ahead and is left unarmed (call ridc_begin again);
+ *  - 1D, up to 256 rows and order 6, nothing set or tuned: one range of `reps` steps as
+ *    ridc_advance would run it, also past the last step (the handle does not advance);
+ *  - 1D, set or tuned to the whole-integration workgroup (systems that fit one CU's LDS): one
+ *    launch running `reps` steps; the handle runs ahead and is left unarmed (call ridc_begin again);
  *  - 2D: `reps` launches of the first transform pass of that step over all levels (after its
  *    right-hand side once).  These launches rewrite only per-step intermediates (the right-hand
  *    side and transform buffers, which the step recomputes); the level rings and the handle's position are unchanged.
@@ -317,7 +319,8 @@ int ridc_kernel_time(ridc_handle* h, int32_t reps, double* us_per_launch,
 
 /* Average duration of one grouped 1D launch (section III-E's pipeline step for every instance in
  * hs[0..count), with the current batch tiling), from HIP events around `reps` back-to-back
- * launches on the handles' stream.  Every handle must be armed, 1D, not set to the whole-range
+ * launches on the handles' stream; for a batch of small systems only, which ridc_advance runs whole
+ * ranges of in one launch, a step of one range of `reps` steps.  Every handle must be armed, 1D, not set to the whole-range
  * workgroup, and have every level active in its next step, which each launch recomputes (the
  * handles do not advance).  *bytes_per_launch (nullable) receives the algorithmic HBM bytes of
  * that step summed over the instances (as ridc_step_cost).  Errors: RIDC_E_STATE,

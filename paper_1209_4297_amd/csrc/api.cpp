@@ -805,6 +805,96 @@ int stage_batch_1d(const std::vector<ridc_handle*>& hs, const BatchTile& asked, 
   return RIDC_OK;
 }
 
+// A workgroup each for the handles hw (small: all of them small systems): the next max_steps steps of
+// each, or what is left.  timing: max_steps whatever is left.
+int launch_ranges(const std::vector<ridc_handle*>& hw, bool small, int64_t max_steps, bool timing,
+                  hipStream_t stream) {
+  int rc = arena_reserve(1, 1, stream);
+  if (rc != RIDC_OK) return rc;
+  rc = arena_reserve_fused(hw.size());
+  if (rc != RIDC_OK) return rc;
+  int maxP = 1;
+  int64_t longest = 0;
+  size_t lds = 0;
+  for (size_t i = 0; i < hw.size(); ++i) {
+    ridc_handle* h = hw[i];
+    maxP = std::max(maxP, h->P);
+    const FusedPlan fp = plan_fused(&h->p, 512);
+    lds = std::max(lds, small ? h->small_lds : fp.lds);
+    Fused1D F = h->fused_item;
+    F.group = fp.group;
+    F.nt = timing ? (int64_t)1 << 40 : h->nt;
+    F.sigma0 = 0;
+    F.sigma_first = h->sigma;
+    F.sigma_last = h->sigma + (timing ? max_steps : std::min(max_steps, h->total - h->sigma));
+    longest = std::max(longest, F.sigma_last - F.sigma_first);
+    g_arena.h_fused[i] = F;
+  }
+  RIDC_HIP_TRY(hipMemcpyAsync(g_arena.d_fused, g_arena.h_fused, sizeof(Fused1D) * hw.size(),
+                              hipMemcpyHostToDevice, stream));
+  RIDC_HIP_TRY(hipEventRecord(g_arena.done, stream));
+  g_arena.pending = true;
+  if (small)
+    RIDC_HIP_TRY(launch_small_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, longest, lds,
+                                 stream));
+  else
+    RIDC_HIP_TRY(launch_fused_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, 512, lds, stream));
+  return arena_release(stream);
+}
+
+// Average duration (us) of a step of small systems in a range of `reps` steps from each one's next
+// step.  The ranges run past what is left, so the rings are kept aside and put back: the handles come
+// out as they went in.
+int time_ranges(const std::vector<ridc_handle*>& hw, int32_t reps, hipStream_t stream, double* us) {
+  auto ring_bytes = [](const ridc_handle* h) {
+    int64_t slots = 0;
+    for (int j = 0; j < h->P; ++j) slots += h->R[j];
+    return sizeof(double) * (size_t)(slots * h->npts);
+  };
+  size_t total = 0;
+  for (auto* h : hw) total += ring_bytes(h);
+  char* kept = nullptr;
+  if (hipMalloc(&kept, total) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(RIDC_E_NOMEM, "device allocation for the timing failed");
+  }
+  auto rings = [&](bool back) {
+    hipError_t e = hipSuccess;
+    char* at = kept;
+    for (auto* h : hw) {
+      const size_t b = ring_bytes(h);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(back ? (void*)h->ring[0] : at, back ? at : (void*)h->ring[0], b,
+                           hipMemcpyDeviceToDevice, stream);
+      at += b;
+    }
+    return e;
+  };
+  hipEvent_t ev[2] = {};
+  float ms = 0;
+  int rc = RIDC_OK;
+  hipError_t e = hipEventCreate(&ev[0]);
+  if (e == hipSuccess) e = hipEventCreate(&ev[1]);
+  if (e == hipSuccess) e = rings(false);
+  if (e == hipSuccess) {
+    rc = launch_ranges(hw, true, reps, true, stream);                  // warm
+    if (rc == RIDC_OK) (void)hipEventRecord(ev[0], stream);
+    if (rc == RIDC_OK) rc = launch_ranges(hw, true, reps, true, stream);
+    (void)hipEventRecord(ev[1], stream);
+    e = rings(true);
+  }
+  const hipError_t done = hipStreamSynchronize(stream);
+  if (e == hipSuccess) e = done;
+  if (rc == RIDC_OK && e == hipSuccess) e = hipEventElapsedTime(&ms, ev[0], ev[1]);
+  for (auto v : ev)
+    if (v) (void)hipEventDestroy(v);
+  (void)hipFree(kept);
+  if (rc != RIDC_OK) return rc;
+  if (e != hipSuccess) return fail(RIDC_E_HIP, std::string("range timing: ") + hipGetErrorString(e));
+  *us = 1e3 * (double)ms / reps;
+  return RIDC_OK;
+}
+
 // Validate and arm a handle for nsteps time steps (host state and 2D plan; the rings are
 // filled by the caller).
 int arm_handle(ridc_handle* h, const double* u0_dev, int64_t nsteps) {
@@ -1462,43 +1552,10 @@ int ridc_advance(ridc_handle* const* hs, int32_t count, int64_t max_steps) {
     for (auto* h : h1) (h->fused || all_small ? (h->small_ok ? hm : hf) : hs).push_back(h);
     h1.swap(hs);
     for (auto* list : {&hf, &hm}) {
-      const std::vector<ridc_handle*>& hw = *list;
-      if (hw.empty()) continue;
-      const bool small = list == &hm;
-      rc = arena_reserve(1, 1, stream);
+      if (list->empty()) continue;
+      rc = launch_ranges(*list, list == &hm, max_steps, false, stream);
       if (rc != RIDC_OK) return rc;
-      rc = arena_reserve_fused(hw.size());
-      if (rc != RIDC_OK) return rc;
-      int maxP = 1;
-      int64_t longest = 0;
-      size_t lds = 0;
-      for (size_t i = 0; i < hw.size(); ++i) {
-        ridc_handle* h = hw[i];
-        maxP = std::max(maxP, h->P);
-        const FusedPlan fp = plan_fused(&h->p, 512);
-        lds = std::max(lds, small ? h->small_lds : fp.lds);
-        Fused1D F = h->fused_item;
-        F.group = fp.group;
-        F.nt = h->nt;
-        F.sigma0 = 0;
-        F.sigma_first = h->sigma;
-        F.sigma_last = h->sigma + std::min(max_steps, h->total - h->sigma);
-        longest = std::max(longest, F.sigma_last - F.sigma_first);
-        g_arena.h_fused[i] = F;
-      }
-      RIDC_HIP_TRY(hipMemcpyAsync(g_arena.d_fused, g_arena.h_fused, sizeof(Fused1D) * hw.size(),
-                                  hipMemcpyHostToDevice, stream));
-      RIDC_HIP_TRY(hipEventRecord(g_arena.done, stream));
-      g_arena.pending = true;
-      if (small)
-        RIDC_HIP_TRY(launch_small_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, longest, lds,
-                                     stream));
-      else
-        RIDC_HIP_TRY(launch_fused_1d(g_arena.d_fused, nullptr, (int)hw.size(), maxP, 512, lds,
-                                     stream));
-      rc = arena_release(stream);
-      if (rc != RIDC_OK) return rc;
-      for (auto* h : hw) h->sigma += std::min(max_steps, h->total - h->sigma);
+      for (auto* h : *list) h->sigma += std::min(max_steps, h->total - h->sigma);
     }
   }
   if (!h1.empty()) {
@@ -1969,6 +2026,13 @@ int ridc_batch_kernel_time(ridc_handle* const* hs, int32_t count, int32_t reps,
   if (h1.empty()) return fail(RIDC_E_INVAL, "no handles");
   const BatchTile bt = current_batch_tile();
   hipStream_t stream = h1[0]->stream;
+  bool all_small = count > 1;                   // as in ridc_advance
+  for (auto* h : h1) all_small = all_small && h->small;
+  if (all_small) {
+    rc = time_ranges(h1, reps, stream, us_per_launch);
+    if (rc == RIDC_OK && bytes_per_launch) *bytes_per_launch = bytes;
+    return rc;
+  }
   BatchStage st;
   rc = stage_batch_1d(h1, bt, false, stream, &st);
   if (rc != RIDC_OK) return rc;
@@ -2076,6 +2140,11 @@ int ridc_kernel_time(ridc_handle* h, int32_t reps, double* us_per_launch, double
     *us_per_launch = 1e3 * (double)ms / reps;
     if (work_per_launch) *work_per_launch = bytes;
     return RIDC_OK;
+  }
+  if (whole_range(h, reps)) {
+    rc = time_ranges({h}, reps, h->stream, us_per_launch);
+    if (rc == RIDC_OK && work_per_launch) *work_per_launch = bytes;
+    return rc;
   }
   hipEvent_t a, b;
   RIDC_HIP_TRY(hipEventCreate(&a));

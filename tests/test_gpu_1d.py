@@ -591,3 +591,38 @@ def test_long_ranges_of_a_batch_go_by_several_launches(env):
     for s, uT, w in zip(solvers, uTs, want):
         np.testing.assert_array_equal(uT.cpu().numpy(), w)
         s.close()
+
+
+@pytest.mark.parametrize("count", [1, 3])
+def test_kernel_time_of_small_systems(env, count):
+    """The timing of an untuned small system (or a batch of them) is that of the kernel its ranges run,
+    a third of a launch per step; it takes more steps than are left and leaves the handles armed and the
+    integration's bits alone."""
+    torch, ridc = env
+    x = workloads.grid_points("periodic", 128, 2 * math.pi)
+    x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
+    prob = dict(dim=1, bc="periodic", n=128, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3, T=0.05,
+                nt=30, order=4)
+    solvers = [ridc.Ridc(prob) for _ in range(count)]
+    want = solvers[0].integrate(x0, 30).cpu().numpy()
+    for s in solvers:
+        s.begin(x0, 30)
+    ridc.advance(solvers, 10)
+    us, nbytes = ridc.batch_kernel_time(solvers, 200) if count > 1 else solvers[0].kernel_time(200)
+    assert nbytes == sum(s.step_cost()[0] for s in solvers)
+    per_step = ridc.Ridc(prob)
+    per_step.set_tile(256, 0, 0)
+    per_step.begin(x0, 30)
+    ridc.advance([per_step], 10)
+    launch = per_step.kernel_time(200)[0]
+    _say(f"case: {count} small systems {us:.2f} us a step, launches per step {launch:.2f}")
+    assert us < 0.7 * launch
+    while any(s.remaining() > 0 for s in solvers):
+        ridc.advance(solvers, 7)
+    for s in solvers:
+        out = torch.empty_like(x0)
+        s.read(out)
+        s.sync()
+        np.testing.assert_array_equal(out.cpu().numpy(), want)
+        s.close()
+    per_step.close()
