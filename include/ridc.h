@@ -239,8 +239,8 @@ int ridc_step_cost(const ridc_handle* h, double* hbm_bytes, double* flops);
  * ridc_tune_save) for later handles with the same key:
  *  - 1D: candidate tilings (threads per workgroup; whole cycle per workgroup, or chunks of
  *    `rows` rows with a PCR halo; the whole-range workgroup), keyed by (n, boundary, PCR
- *    stages).  threads_out/rows_out/flags_out (nullable) receive the choice (rows 0 = whole
- *    cycle; flags as in ridc_set_tile).
+ *    stages, order).  threads_out/rows_out/flags_out (nullable) receive the choice (rows 0 =
+ *    whole cycle; flags as in ridc_set_tile).
  *  - 2D: the transform-pass shapes the handle's side and precision allow, keyed by (n,
  *    precision): 32- or 64-column waves (FP32/FP64 passes), 64- or 32-wide k-slices
  *    (split-BF16 pass), each timed over whole pipeline steps (10 at n <= 1024, fewer above; best of three rounds).

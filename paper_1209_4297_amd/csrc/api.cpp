@@ -196,9 +196,9 @@ void tile_to(const Tile1D& t, int* threads, int* rows, int* flags) {
 }
 
 // the measured tiling of this system, if the tuning table has one
-bool tuned_tile(int64_t n, int bc, int stages, Tile1D* t) {
+bool tuned_tile(const ridc_problem* p, int stages, Tile1D* t) {
   int th = 0, r = 0, f = 0;
-  if (!tune_get_1d(n, bc, stages, &th, &r, &f)) return false;
+  if (!tune_get_1d(p->n, p->bc, stages, p->order, &th, &r, &f)) return false;
   *t = tile_from(th, r, f);
   return true;
 }
@@ -249,7 +249,7 @@ bool tile_fits(const ridc_problem* p, const PcrPlan& pcr, const Tile1D& t) {
 int choose_tile_1d(const ridc_problem* p, const PcrPlan& pcr, Tile1D* out,
                    bool allow_fused = true) {
   Tile1D t;
-  if (tuned_tile(p->n, p->bc, pcr.stages, &t) && (allow_fused || !t.fused) &&
+  if (tuned_tile(p, pcr.stages, &t) && (allow_fused || !t.fused) &&
       tile_fits(p, pcr, t)) {
     *out = t;
     return RIDC_OK;
@@ -1317,7 +1317,7 @@ int ridc_create(const ridc_problem* p, void* hip_stream, ridc_handle** out) {
         h->small_ok = h->small_lds <= (size_t)max_lds &&
                       prepare_small_1d(h->fused_item, max_lds) == hipSuccess;
       }
-      h->small = h->small_ok && !tuned_tile(p->n, p->bc, h->pcr.stages, &tuned);
+      h->small = h->small_ok && !(tuned_tile(p, h->pcr.stages, &tuned) && tile_fits(p, h->pcr, tuned));
     }
     if (hipMemcpy(h->d_blocks, h->blocks.data(), sizeof(Blk1D) * h->blocks.size(),
                   hipMemcpyHostToDevice) != hipSuccess ||
@@ -1842,7 +1842,7 @@ int ridc_autotune(ridc_handle* h, int32_t* threads_out, int32_t* rows_out, int32
   {
     // a tiling recorded for this system (this process, or the tuning cache) is taken as is
     Tile1D t;
-    if (tuned_tile(h->p.n, h->p.bc, h->pcr.stages, &t) && tile_fits(&h->p, h->pcr, t)) {
+    if (tuned_tile(&h->p, h->pcr.stages, &t) && tile_fits(&h->p, h->pcr, t)) {
       int rc = apply_tile_1d(h, t);
       if (rc != RIDC_OK) return rc;
       int th, r, f;
@@ -1879,7 +1879,7 @@ int ridc_autotune(ridc_handle* h, int32_t* threads_out, int32_t* rows_out, int32
   if (best_ms >= 1e29f) return fail(RIDC_E_UNSUPPORTED, "no tile fits");
   int th, r, f;
   tile_to(best, &th, &r, &f);
-  tune_put_1d(h->p.n, h->p.bc, h->pcr.stages, th, r, f);
+  tune_put_1d(h->p.n, h->p.bc, h->pcr.stages, h->P, th, r, f);
   h->nt = -1;
   h->sigma = h->total = 0;
   int rc = apply_tile_1d(h, best);

@@ -232,9 +232,9 @@ hipError_t launch_imex1d(const ImexLvl* d_items, int count, int M, int threads, 
 // ---------------------------------------------------------------------------------------------
 // persistent table of measured launch shapes (tune.cpp)
 // ---------------------------------------------------------------------------------------------
-// 1D level-step tiling per (n, boundary, PCR stages), as ridc_set_tile's (threads, rows, flags)
-bool tune_get_1d(int64_t n, int bc, int stages, int* threads, int* rows, int* flags);
-void tune_put_1d(int64_t n, int bc, int stages, int threads, int rows, int flags);
+// 1D level-step tiling per (n, boundary, PCR stages, order), as ridc_set_tile's (threads, rows, flags)
+bool tune_get_1d(int64_t n, int bc, int stages, int order, int* threads, int* rows, int* flags);
+void tune_put_1d(int64_t n, int bc, int stages, int order, int threads, int rows, int flags);
 // grouped 1D tiling, as ridc_set_batch_tile's (threads, rows)
 bool tune_get_batch(int* threads, int* rows);
 void tune_put_batch(int threads, int rows);

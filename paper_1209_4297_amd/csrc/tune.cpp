@@ -1,5 +1,5 @@
-// Persistent table of measured launch shapes: 1D level-step tilings (per n, boundary and PCR
-// stage count), the grouped 1D tiling, and the 2D transform-pass shapes (per n and precision).
+// Persistent table of measured launch shapes: 1D level-step tilings (per n, boundary, PCR stage
+// count and order; entries of files without the order hold for all of them), the grouped 1D tiling, and the 2D transform-pass shapes (per n and precision).
 //
 // The autotuners record their choices here; the table is loaded on first use from a JSON file
 // and the file is rewritten after every new entry, so later processes reuse the measurements.
@@ -24,7 +24,10 @@ namespace {
 
 struct Rec1D {
   int64_t n;
-  int bc, stages, threads, rows, flags;
+  int bc, stages, order, threads, rows, flags;
+  bool same_key(const Rec1D& r) const {
+    return n == r.n && bc == r.bc && stages == r.stages && order == r.order;
+  }
 };
 struct Rec2D {
   int64_t n;
@@ -125,6 +128,15 @@ std::string string_field(const std::string& s, const char* key) {
   return e == std::string::npos ? "" : s.substr(p + 1, e - p - 1);
 }
 
+void put_locked(Store& st, const Rec1D& r) {
+  for (auto& e : st.t1)
+    if (e.same_key(r)) {
+      e = r;
+      return;
+    }
+  st.t1.push_back(r);
+}
+
 // Merge the entries of `path` into the table (caller holds the lock).  Returns false when the
 // file cannot be read; a file of another GPU adds nothing.
 bool load_locked(Store& st, const std::string& path) {
@@ -144,15 +156,8 @@ bool load_locked(Store& st, const std::string& path) {
   };
   for (auto& o : objects(s, "tile1d")) {
     if (!has(o, {"n", "bc", "stages", "threads", "rows", "flags"})) continue;
-    Rec1D r{o["n"], (int)o["bc"], (int)o["stages"], (int)o["threads"], (int)o["rows"],
-            (int)o["flags"]};
-    bool found = false;
-    for (auto& e : st.t1)
-      if (e.n == r.n && e.bc == r.bc && e.stages == r.stages) {
-        e = r;
-        found = true;
-      }
-    if (!found) st.t1.push_back(r);
+    put_locked(st, Rec1D{o["n"], (int)o["bc"], (int)o["stages"], o.count("order") ? (int)o["order"] : 0,
+                         (int)o["threads"], (int)o["rows"], (int)o["flags"]});
   }
   for (auto& o : objects(s, "batch1d"))
     if (has(o, {"threads", "rows"})) {
@@ -184,9 +189,10 @@ bool save_locked(const Store& st, const std::string& path) {
   std::fprintf(f, "  \"tile1d\": [");
   for (size_t i = 0; i < st.t1.size(); ++i) {
     const Rec1D& r = st.t1[i];
-    std::fprintf(f, "%s\n    {\"n\": %lld, \"bc\": %d, \"stages\": %d, \"threads\": %d, "
-                 "\"rows\": %d, \"flags\": %d}", i ? "," : "", (long long)r.n, r.bc, r.stages,
-                 r.threads, r.rows, r.flags);
+    std::fprintf(f, "%s\n    {\"n\": %lld, \"bc\": %d, \"stages\": %d, ", i ? "," : "",
+                 (long long)r.n, r.bc, r.stages);
+    if (r.order) std::fprintf(f, "\"order\": %d, ", r.order);
+    std::fprintf(f, "\"threads\": %d, \"rows\": %d, \"flags\": %d}", r.threads, r.rows, r.flags);
   }
   std::fprintf(f, "\n  ],\n");
   if (st.has_batch)
@@ -223,29 +229,24 @@ void persist_locked(const Store& st) {
 
 }  // namespace
 
-bool tune_get_1d(int64_t n, int bc, int stages, int* threads, int* rows, int* flags) {
+bool tune_get_1d(int64_t n, int bc, int stages, int order, int* threads, int* rows, int* flags) {
   std::lock_guard<std::mutex> lk(store().mu);
   Store& st = ready();
-  for (auto& e : st.t1)
-    if (e.n == n && e.bc == bc && e.stages == stages) {
-      *threads = e.threads;
-      *rows = e.rows;
-      *flags = e.flags;
-      return true;
-    }
+  for (int o : {order, 0})
+    for (auto& e : st.t1)
+      if (e.same_key(Rec1D{n, bc, stages, o, 0, 0, 0})) {
+        *threads = e.threads;
+        *rows = e.rows;
+        *flags = e.flags;
+        return true;
+      }
   return false;
 }
 
-void tune_put_1d(int64_t n, int bc, int stages, int threads, int rows, int flags) {
+void tune_put_1d(int64_t n, int bc, int stages, int order, int threads, int rows, int flags) {
   std::lock_guard<std::mutex> lk(store().mu);
   Store& st = ready();
-  bool found = false;
-  for (auto& e : st.t1)
-    if (e.n == n && e.bc == bc && e.stages == stages) {
-      e = Rec1D{n, bc, stages, threads, rows, flags};
-      found = true;
-    }
-  if (!found) st.t1.push_back(Rec1D{n, bc, stages, threads, rows, flags});
+  put_locked(st, Rec1D{n, bc, stages, order, threads, rows, flags});
   persist_locked(st);
 }
 

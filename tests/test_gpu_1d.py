@@ -532,6 +532,7 @@ def test_short_ranges_of_small_systems(env, n, order):
     whole-range workgroup, which loads and stores all rings, takes the ranges that pay for it (it cost up
     to 3.3 times a step).  A third above is left for the spread of the timing."""
     torch, ridc = env
+    ridc.tune_clear()                    # nothing recorded by other tests
     x = workloads.grid_points("periodic", n, 2 * math.pi)
     x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
     prob = dict(dim=1, bc="periodic", n=n, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3, T=0.05,
@@ -599,6 +600,7 @@ def test_kernel_time_of_small_systems(env, count):
     a third of a launch per step; it takes more steps than are left and leaves the handles armed and the
     integration's bits alone."""
     torch, ridc = env
+    ridc.tune_clear()                    # nothing recorded by other tests
     x = workloads.grid_points("periodic", 128, 2 * math.pi)
     x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
     prob = dict(dim=1, bc="periodic", n=128, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3, T=0.05,
@@ -626,3 +628,52 @@ def test_kernel_time_of_small_systems(env, count):
         np.testing.assert_array_equal(out.cpu().numpy(), want)
         s.close()
     per_step.close()
+
+
+def _small_step(env, order):
+    """(us a step of an untouched handle's timing, launches per step) at n = 200."""
+    torch, ridc = env
+    x = workloads.grid_points("periodic", 200, 2 * math.pi)
+    x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
+    prob = dict(dim=1, bc="periodic", n=200, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3, T=0.05,
+                nt=400, order=order)
+    out = []
+    for tile in (None, (256, 0, 0)):
+        s = ridc.Ridc(prob)
+        if tile:
+            s.set_tile(*tile)
+        s.begin(x0, 400)
+        ridc.advance([s], 20)
+        out.append(s.kernel_time(100)[0])
+        s.close()
+    return out
+
+
+def test_other_orders_records_leave_small_systems_alone(env, tmp_path):
+    """A tiling measured at one order is not another order's: after an order 8 handle's, and with a file's
+    entry for all orders that does not fit this one, a small system still runs whole ranges."""
+    import json
+    torch, ridc = env
+    ridc.tune_clear()
+    prob = dict(dim=1, bc="periodic", n=200, length=2 * math.pi, fe="advect", a=0.6, nu=2e-3, T=0.05,
+                nt=400, order=8)
+    s = ridc.Ridc(prob)
+    s.autotune()
+    s.close()
+    small, launch = _small_step(env, 4)
+    _say(f"case: order 4 after order 8's record: {small:.2f} us, launches per step {launch:.2f}")
+    assert small < 0.8 * launch
+    path = tmp_path / "tune.json"
+    ridc.tune_save(str(path))
+    doc = json.loads(path.read_text())
+    (rec,) = doc["tile1d"]
+    assert rec["n"] == 200 and rec["order"] == 8
+    del rec["order"]                              # as an older file has it
+    rec.update(threads=1024, rows=0, flags=2)     # a whole range in 1024 threads: orders up to 4
+    path.write_text(json.dumps(doc))
+    ridc.tune_clear()
+    ridc.tune_load(str(path))
+    small, launch = _small_step(env, 6)
+    _say(f"case: order 6 beside order 4's whole range: {small:.2f} us, launches per step {launch:.2f}")
+    assert small < 0.8 * launch
+    ridc.tune_clear()
