@@ -1114,17 +1114,22 @@ int time_2d_steps(Plan2D* pl, int64_t s, int reps, hipStream_t stream, double* u
 // measured: every shape the plan allows times whole steps with every level active (10 at
 // n <= 1024, fewer above so that the measurement stays near a tenth of a second per shape; on
 // zeroed rings; a shape can change the first pass of a solve and the later ones differently),
-// best of three rounds; the fastest is kept and recorded.  Leaves the handle unarmed.
-// Outputs: threads per block of the chosen shape, 0, and the shape bits.
+// best of three rounds; the fastest is kept and recorded.  Where this handle's passes take smaller
+// block tiles, which the shapes do not change, the default is recorded as not measured, and a handle
+// that they do change measures later.  Leaves the handle unarmed.
+// Outputs: threads per block of the chosen shape's 128 x 128 tiles, 0, and the shape bits.
 int autotune_2d(ridc_handle* h, int32_t* threads_out, int32_t* rows_out, int32_t* flags_out) {
   Plan2D* pl = h->p2;
   const int prec = h->p.prec;
   int tile = 0;
-  if (!tune_get_2d(h->p.n, prec, &tile) || plan2d_set_tile(pl, tile) != RIDC_OK) {
+  bool measured = false;
+  const bool matters = plan2d_tile_matters(pl);
+  if (!tune_get_2d(h->p.n, prec, &tile, &measured) || (matters && !measured) ||
+      plan2d_set_tile(pl, tile) != RIDC_OK) {
     std::vector<int> cands;
     plan2d_tile_candidates(pl, &cands);
-    tile = cands[0];
-    if (cands.size() > 1) {
+    tile = plan2d_default_tile(pl);
+    if (matters && cands.size() > 1) {
       int64_t slots = 0;
       for (int j = 0; j < h->P; ++j) slots += h->R[j];
       RIDC_HIP_TRY(hipMemsetAsync(h->ring[0], 0, sizeof(double) * (size_t)(slots * h->npts),
@@ -1151,7 +1156,7 @@ int autotune_2d(ridc_handle* h, int32_t* threads_out, int32_t* rows_out, int32_t
         if (t[i] < t[bi]) bi = i;
       tile = cands[bi];
     }
-    tune_put_2d(h->p.n, prec, tile);
+    tune_put_2d(h->p.n, prec, tile, matters);
     int rc = plan2d_set_tile(pl, tile);
     if (rc != RIDC_OK) return rc;
   }
@@ -1332,15 +1337,6 @@ int ridc_create(const ridc_problem* p, void* hip_stream, ridc_handle** out) {
     if (rc != RIDC_OK) {
       ridc_destroy(h);
       return rc;
-    }
-    // untuned split-BF16 plans take the 32-wide k-slices where
-    // they are a choice (whole steps at n = 1024: 144 against 156 us)
-    int tuned = 0;
-    if (p->prec == RIDC_PREC_BF16X3_REFINE && !tune_get_2d(p->n, p->prec, &tuned)) {
-      std::vector<int> c;
-      plan2d_tile_candidates(h->p2, &c);
-      if (std::find(c.begin(), c.end(), kPassNarrowK) != c.end())
-        (void)plan2d_set_tile(h->p2, kPassNarrowK);
     }
   }
   *out = h;

@@ -1797,9 +1797,10 @@ int plan2d_create(const ridc_problem* p, double h, double* const* ring, const in
   RIDC_HIP_TRY(hipMemcpy(pl->d_passes, pl->passes.data(), sizeof(Pass2D) * pl->passes.size(),
                          hipMemcpyHostToDevice));
   {
-    // the measured pass shape of this (n, precision), if the tuning table has one
+    // the pass shape recorded for this (n, precision), if the tuning table has one
     int tile = 0;
-    if (tune_get_2d(p->n, p->prec, &tile)) (void)plan2d_set_tile(pl, tile);
+    if (!tune_get_2d(p->n, p->prec, &tile) || plan2d_set_tile(pl, tile) != RIDC_OK)
+      pl->tile = plan2d_default_tile(pl);
     set_error("");
   }
   *out = pl;
@@ -1815,6 +1816,18 @@ void plan2d_tile_candidates(const Plan2D* pl, std::vector<int>* out) {
   out->push_back(0);
   if (pl->prec != PREC_BF16 && (!folded(pl->n) || pl->n % 128 == 0)) out->push_back(kPassWide64);
   if (pl->prec == PREC_BF16 && wide_slices<PREC_BF16>(pl->n)) out->push_back(kPassNarrowK);
+}
+
+// Narrow k-slices where they are a choice: whole steps at n = 1024, order 4, 144 us against 156.
+int plan2d_default_tile(const Plan2D* pl) {
+  return pl->prec == PREC_BF16 && wide_slices<PREC_BF16>(pl->n) ? kPassNarrowK : 0;
+}
+
+bool plan2d_tile_matters(const Plan2D* pl) {
+  const int bt = pl->prec == PREC_F64   ? block_tile<PREC_F64>(pl->n, pl->P)
+                 : pl->prec == PREC_F32 ? block_tile<PREC_F32>(pl->n, pl->P)
+                                        : block_tile<PREC_BF16>(pl->n, pl->P);
+  return bt == BT0;
 }
 
 int plan2d_set_tile(Plan2D* pl, int tile) {

@@ -35,6 +35,10 @@ constexpr int kPassPlainA = 4;
 int plan2d_tile(const Plan2D* pl);
 // The shapes this plan's side and precision allow (0 first).
 void plan2d_tile_candidates(const Plan2D* pl, std::vector<int>* out);
+// The shape of a plan that none is recorded for, and whether the plan's own passes (by itself, every
+// level active) differ between the candidates: the shapes are those of 128 x 128 block tiles.
+int plan2d_default_tile(const Plan2D* pl);
+bool plan2d_tile_matters(const Plan2D* pl);
 // Errors: RIDC_E_INVAL for a shape the plan does not allow.
 int plan2d_set_tile(Plan2D* pl, int tile);
 // Average duration (us) of `reps` back-to-back launches of the first transform pass of step

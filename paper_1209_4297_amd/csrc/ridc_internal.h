@@ -238,9 +238,10 @@ void tune_put_1d(int64_t n, int bc, int stages, int order, int threads, int rows
 // grouped 1D tiling, as ridc_set_batch_tile's (threads, rows)
 bool tune_get_batch(int* threads, int* rows);
 void tune_put_batch(int threads, int rows);
-// 2D transform-pass shape per (n, precision)
-bool tune_get_2d(int64_t n, int prec, int* tile);
-void tune_put_2d(int64_t n, int prec, int tile);
+// 2D transform-pass shape per (n, precision), and whether it was measured (on a handle whose passes
+// the shapes change) or is the default
+bool tune_get_2d(int64_t n, int prec, int* tile, bool* measured = nullptr);
+void tune_put_2d(int64_t n, int prec, int tile, bool measured);
 int tune_save(const char* path);   // nullptr: the default file
 int tune_load(const char* path);
 void tune_clear();

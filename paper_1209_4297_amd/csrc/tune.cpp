@@ -32,6 +32,7 @@ struct Rec1D {
 struct Rec2D {
   int64_t n;
   int prec, tile;
+  bool measured;     // false: the default, by a handle whose passes no shape changes
 };
 
 struct Store {
@@ -167,7 +168,7 @@ bool load_locked(Store& st, const std::string& path) {
     }
   for (auto& o : objects(s, "pass2d")) {
     if (!has(o, {"n", "prec", "tile"})) continue;
-    Rec2D r{o["n"], (int)o["prec"], (int)o["tile"]};
+    Rec2D r{o["n"], (int)o["prec"], (int)o["tile"], true};
     bool found = false;
     for (auto& e : st.t2)
       if (e.n == r.n && e.prec == r.prec) {
@@ -176,6 +177,9 @@ bool load_locked(Store& st, const std::string& path) {
       }
     if (!found) st.t2.push_back(r);
   }
+  for (auto& o : objects(s, "pass2d_default"))
+    for (auto& e : st.t2)
+      if (has(o, {"n", "prec"}) && e.n == o["n"] && e.prec == (int)o["prec"]) e.measured = false;
   return true;
 }
 
@@ -202,7 +206,16 @@ bool save_locked(const Store& st, const std::string& path) {
   for (size_t i = 0; i < st.t2.size(); ++i)
     std::fprintf(f, "%s\n    {\"n\": %lld, \"prec\": %d, \"tile\": %d}", i ? "," : "",
                  (long long)st.t2[i].n, st.t2[i].prec, st.t2[i].tile);
-  std::fprintf(f, "\n  ]\n}\n");
+  std::fprintf(f, "\n  ]");
+  // of these, the ones that no measurement chose
+  bool any = false;
+  for (auto& r : st.t2)
+    if (!r.measured) {
+      std::fprintf(f, "%s\n    {\"n\": %lld, \"prec\": %d}", any ? "," : ",\n  \"pass2d_default\": [",
+                   (long long)r.n, r.prec);
+      any = true;
+    }
+  std::fprintf(f, "%s\n}\n", any ? "\n  ]" : "");
   const bool ok = std::fclose(f) == 0;
   if (!ok || std::rename(tmp.c_str(), path.c_str()) != 0) {
     std::remove(tmp.c_str());
@@ -268,27 +281,29 @@ void tune_put_batch(int threads, int rows) {
   persist_locked(st);
 }
 
-bool tune_get_2d(int64_t n, int prec, int* tile) {
+bool tune_get_2d(int64_t n, int prec, int* tile, bool* measured) {
   std::lock_guard<std::mutex> lk(store().mu);
   Store& st = ready();
   for (auto& e : st.t2)
     if (e.n == n && e.prec == prec) {
       *tile = e.tile;
+      if (measured) *measured = e.measured;
       return true;
     }
   return false;
 }
 
-void tune_put_2d(int64_t n, int prec, int tile) {
+void tune_put_2d(int64_t n, int prec, int tile, bool measured) {
   std::lock_guard<std::mutex> lk(store().mu);
   Store& st = ready();
   bool found = false;
   for (auto& e : st.t2)
     if (e.n == n && e.prec == prec) {
       e.tile = tile;
+      e.measured = measured;
       found = true;
     }
-  if (!found) st.t2.push_back(Rec2D{n, prec, tile});
+  if (!found) st.t2.push_back(Rec2D{n, prec, tile, measured});
   persist_locked(st);
 }
 

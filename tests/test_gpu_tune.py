@@ -76,3 +76,36 @@ def test_autotune_records_the_2d_shape(env, tmp_path):
     assert s2.autotune()[2] == flags
     s2.close()
     ridc.tune_clear()
+
+
+def test_autotune_measures_only_where_the_shapes_differ(env, tmp_path):
+    """The shapes are those of 128 x 128 block tiles.  A handle whose passes take smaller ones (order 1 at
+    these sides) has nothing to measure: it records the default, marked as such also in the file, and an
+    order whose passes the shapes change measures in its place."""
+    torch, ridc = env
+    ridc.tune_clear()
+    path = tmp_path / "tune.json"
+
+    def tune(n, prec, order):
+        prob, _ = workloads.config_reacdiff_2d(n=n, nt=12, order=order, T=0.024)
+        s = ridc.Ridc(prob, prec=prec)
+        flags = s.autotune()[2]
+        s.close()
+        ridc.tune_save(str(path))
+        doc = json.loads(path.read_text())
+        return flags, {(r["n"], r["prec"]) for r in doc.get("pass2d_default", [])}
+
+    unmeasured = set()
+    for n in (256, 512, 768):
+        for k, prec in enumerate(("fp64", "fp32", "bf16x3")):
+            print(f"case: autotune n={n} {prec} order 1", flush=True)
+            flags, marked = tune(n, prec, 1)
+            unmeasured.add((n, k))
+            assert flags == (2 if prec == "bf16x3" else 0) and marked == unmeasured
+    ridc.tune_clear()
+    ridc.tune_load(str(path))
+    for k, prec in enumerate(("fp64", "fp32", "bf16x3")):     # 16 tiles a level, 8 levels
+        flags, marked = tune(512, prec, 8)
+        unmeasured.discard((512, k))
+        assert flags in ((0, 2) if prec == "bf16x3" else (0, 1)) and marked == unmeasured
+    ridc.tune_clear()
