@@ -1836,7 +1836,7 @@ int plan2d_set_tile(Plan2D* pl, int tile) {
   const int shape = pl->n % 256 == 0 ? tile & ~kPassPlainA : tile;
   if (std::find(c.begin(), c.end(), shape) == c.end())
     return fail(RIDC_E_INVAL, "launch shape not available for this side and precision");
-  pl->tile = tile;
+  pl->tile = shape;          // (plans are grouped by it)
   return RIDC_OK;
 }
 

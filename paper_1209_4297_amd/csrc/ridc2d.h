@@ -28,7 +28,7 @@ void plan2d_cost(const Plan2D* pl, double* bytes, double* flops);
 // kPassWide64 = 64-column waves, 4 per block (FP32/FP64 passes, n/2 a multiple of 64 or no
 // fold); kPassNarrowK = 32-wide k-slices in two LDS stages (split-BF16 pass, instead of 64-wide
 // slices in one); kPassPlainA (n a multiple of 256) = row-major intermediates folded while
-// staging, which every shape uses: accepted, and the same launch without it.
+// staging, which every shape uses: accepted and dropped.
 constexpr int kPassWide64 = 1;
 constexpr int kPassNarrowK = 2;
 constexpr int kPassPlainA = 4;
