@@ -1778,13 +1778,11 @@ int ridc_integrate_batch(ridc_handle* const* hs, int32_t count, const double* co
     rc = arm_handle(hs[i], u0[i], nsteps[i]);
     if (rc != RIDC_OK) return rc;
     most = std::max(most, hs[i]->total);
-    if (hs[i]->imex) {
-      rc = load_imex(hs[i], u0[i]);
-      if (rc != RIDC_OK) return rc;
-      continue;
+    for (int j = 0; j < hs[i]->P; ++j) {
+      const int M = hs[i]->imex ? hs[i]->imex_M : 0, T = hs[i]->imex_T;
+      copies.push_back(CopyItem{u0[i], hs[i]->ring[j], M ? (int64_t)M * T : hs[i]->npts, nullptr, M,
+                                T, hs[i]->npts});
     }
-    for (int j = 0; j < hs[i]->P; ++j)
-      copies.push_back(CopyItem{u0[i], hs[i]->ring[j], hs[i]->npts, nullptr});
   }
   hipStream_t stream = hs[0]->stream;
   rc = stage_copies(copies, stream);
@@ -1796,12 +1794,10 @@ int ridc_integrate_batch(ridc_handle* const* hs, int32_t count, const double* co
   for (int32_t i = 0; i < count; ++i) {
     ridc_handle* h = hs[i];
     const int top = h->P - 1;
-    if (h->imex) {
-      RIDC_HIP_TRY(read_imex(h, top, uT[i], h->flag));
-      continue;
-    }
-    copies.push_back(CopyItem{h->ring[top] + (h->nt % h->R[top]) * h->npts, uT[i], h->npts,
-                              h->flag});
+    const int M = h->imex ? h->imex_M : 0, T = h->imex_T;
+    const int64_t vec = M ? (int64_t)M * T : h->npts;
+    copies.push_back(CopyItem{h->ring[top] + (h->nt % h->R[top]) * vec, uT[i], h->npts, h->flag, -M,
+                              T, h->npts});
   }
   return stage_copies(copies, stream);
 }

@@ -828,7 +828,15 @@ __global__ void k_copy_items(const CopyItem* __restrict__ items) {
   int bad = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < it.n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const double v = gp(it.src)[i];
+    double v;
+    if (it.M == 0) {
+      v = gp(it.src)[i];
+    } else if (it.M > 0) {
+      const int64_t g = (i % it.T) * it.M + i / it.T;
+      v = g < it.rows ? gp(it.src)[g] : 0.0;
+    } else {
+      v = gp(it.src)[(i % -it.M) * it.T + i / -it.M];
+    }
     gp(it.dst)[i] = v;
     if (!(v - v == 0.0)) bad = 1;      // NaN or Inf
   }

@@ -173,6 +173,10 @@ struct CopyItem {
   double* dst;
   int64_t n;
   int* flag;
+  // one side in the block order of IMEX rings (ImexRings): rows of |M| to a thread, T threads.  M > 0:
+  // dst, n = M T and `rows` rows real; M < 0: src, n rows real.  0: neither
+  int32_t M = 0, T = 0;
+  int64_t rows = 0;
 };
 
 // Copy every item of d_items[0..count) (count <= 65535; max_n: the longest item) in one launch.

@@ -223,3 +223,64 @@ def test_linear_stages_at_large_r(env, n, nu, pairs, bc):
         prob, _ = workloads.config_advdiff_1d(n=n, nt=nt, order=len(pairs))
         u0 = workloads.fourier_modes_1d(n, np.random.default_rng(n))
     check(env, dict(prob, nu=nu, a=0.01, T=1.0, pairs=list(pairs)), u0, nt)
+
+
+def test_batch_moves_every_handles_data_in_one_launch(env):
+    """A batch's initial data and results go through one launch each, whatever the handles hold: IMEX
+    rings of every shape (rows in block order, padded) beside plain ones give the bits of each handle
+    alone; a value that is not finite is reported for the handle that has it."""
+    torch, ridc = env
+    probs = []
+    for n in (2, 100, 512, 513, 1025, 4097, 8192):
+        prob, u0 = workloads.config_reacdiff_1d(n=n, nt=400, order=2)
+        probs += [(dict(prob, pairs=["fbe", "ark3"]), u0 + 0.1), (prob, u0 + 0.1)]
+    solvers = [ridc.Ridc(p) for p, _ in probs]
+    x = [torch.tensor(u, dtype=torch.float64, device="cuda") for _, u in probs]
+    want = [s.integrate(a, 9).clone() for s, a in zip(solvers, x)]
+    out = [torch.empty_like(a) for a in x]
+    _say("case: mixed batch of IMEX and plain handles")
+    ridc.integrate_batch(solvers, x, [9] * len(x), out)
+    for s, a, b in zip(solvers, out, want):
+        s.sync()
+        assert torch.equal(a, b)
+    x[4][-1] = float("nan")                      # the last row of n = 512, IMEX
+    ridc.integrate_batch(solvers, x, [9] * len(x), out)
+    for i, s in enumerate(solvers):
+        if i == 4:
+            with pytest.raises(ridc.RidcError) as e:
+                s.sync()
+            assert e.value.code == ridc.RIDC_E_NONFINITE
+        else:
+            s.sync()
+        s.close()
+
+
+def test_a_batch_of_imex_handles_costs_few_launches(env):
+    """256 small IMEX handles over 5 steps: the whole call takes no longer than arming them one by one,
+    which costs each the same synchronisation and a launch for its initial data (the call took 1.27
+    times as long with a launch a handle for the data at either end)."""
+    import time
+    torch, ridc = env
+    prob, u0 = workloads.config_reacdiff_1d(n=128, nt=400, order=2)
+    prob["pairs"] = ["ark3", "fbe"]
+    count, nt = 256, 5
+    solvers = [ridc.Ridc(prob) for _ in range(count)]
+    x = [torch.tensor(u0, dtype=torch.float64, device="cuda") for _ in range(count)]
+    out = [torch.empty_like(a) for a in x]
+
+    def best(f):
+        times = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            f()
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        return min(times) * 1e6
+
+    whole = best(lambda: ridc.integrate_batch(solvers, x, [nt] * count, out))
+    begin = best(lambda: [s.begin(a, nt) for s, a in zip(solvers, x)])
+    _say(f"case: 256 IMEX handles: the batch {whole:.0f} us, arming one by one {begin:.0f}")
+    assert whole <= 1.1 * begin
+    for s in solvers:
+        s.close()
