@@ -258,7 +258,9 @@ int choose_tile_1d(const ridc_problem* p, const PcrPlan& pcr, Tile1D* out,
   const int64_t ms = p->bc == RIDC_BC_PERIODIC ? p->n : p->n + 2;
   // Default: chunks, as many as give about 256 workgroups per step over the levels (one per CU: a
   // single system's step is bound by latency, not bytes), at least 128 rows each, 1024 threads
-  // where the order allows (512 above), while a chunk with its halos is no longer than twice the
+  // where the order allows (above: 512, and 256 where there are more than 64 chunks of 1024 rows and
+  // registers decide: n = 50000 11.6 us a step against 12.6, n = 80000 14.9 against 13.4, n =
+  // 200000 29.3 against 22.8, order 8), while a chunk with its halos is no longer than twice the
   // system.  Step times, us, of 128-row chunks against the whole cycle in 256 threads, order 4: n =
   // 300 3.6 / 5.9, 999 4.2 / 11.6, 1500 4.2 / 15.4, 2000 4.5 / 20.9; order 8, n = 1024: 4.5 / 10.9.  Against
   // 1024-row chunks of 256 threads at n = 8192: 5.2 / 10.8.  Whole-range workgroups are chosen in
@@ -267,7 +269,7 @@ int choose_tile_1d(const ridc_problem* p, const PcrPlan& pcr, Tile1D* out,
     const int64_t per_level = std::max<int64_t>(1, 256 / p->order);
     int64_t B = (p->n / per_level) / 64 * 64;
     B = std::min<int64_t>(1024, std::max<int64_t>(128, B));
-    const Tile1D chunk{0, (int)B, p->order <= kMaxJ1024 + 1 ? 1024 : 512};
+    const Tile1D chunk{0, (int)B, p->order <= kMaxJ1024 + 1 ? 1024 : (p->n <= 65536 ? 512 : 256)};
     if (B + 2 * H <= 2 * ms && tile_fits(p, pcr, chunk)) {
       *out = chunk;
       return RIDC_OK;

@@ -677,3 +677,36 @@ def test_other_orders_records_leave_small_systems_alone(env, tmp_path):
     _say(f"case: order 6 beside order 4's whole range: {small:.2f} us, launches per step {launch:.2f}")
     assert small < 0.8 * launch
     ridc.tune_clear()
+
+
+@pytest.mark.parametrize("n", [65536, 65537, 200000])
+def test_long_systems_of_high_order(env, n):
+    """The default tiling of a long system of order 8 takes no longer than either thread count it chooses
+    from (it took 1.28 times as long at n = 200000), and the bits are theirs."""
+    import time
+    torch, ridc = env
+    ridc.tune_clear()
+    x = workloads.grid_points("periodic", n, 2 * math.pi)
+    x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
+    h = 2 * math.pi / n
+    prob = dict(dim=1, bc="periodic", n=n, length=2 * math.pi, fe="advect", a=0.01, nu=3.0 * h * h / 1e-4,
+                T=6e-3, nt=60, order=8)
+    times, outs = [], []
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        for tile in (None, (256, 1024, 0), (512, 1024, 0)):
+            s = ridc.Ridc(prob)
+            if tile:
+                s.set_tile(*tile)
+            outs.append(s.integrate(x0, 60).clone())
+            best = 1e30
+            for _ in range(8):
+                t = time.perf_counter()
+                s.integrate(x0, 60, outs[-1])
+                best = min(best, time.perf_counter() - t)
+            times.append(best * 1e6 / 88)
+            s.close()
+    _say(f"case: order 8 n={n}: default {times[0]:.1f} us a step, 256 threads {times[1]:.1f}, 512 "
+         f"{times[2]:.1f}")
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert times[0] <= 1.1 * min(times[1:])
