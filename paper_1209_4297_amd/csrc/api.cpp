@@ -170,6 +170,7 @@ struct BatchTile {
   int threads = 256;
   int rows = 0;
   bool automatic = true;   // nothing set or measured: stage_batch_1d picks one for each group
+  int least = 64;          // rows a chunk owns at least; else whole cycles
 };
 BatchTile g_batch_tile;
 bool g_batch_tile_set = false;
@@ -715,7 +716,7 @@ Tile1D batch_tile_for(const ridc_handle* h, const BatchTile& bt, int threads) {
   if (bt.rows > 0 && bt.rows > 2 * H) {
     const int64_t B = (bt.rows - 2 * H) / 64 * 64;
     const Tile1D c{0, (int)std::min<int64_t>(B, 1 << 20), threads};
-    if (B >= 64 && tile_fits(&p, h->pcr, c)) return c;
+    if (B >= bt.least && tile_fits(&p, h->pcr, c)) return c;
   }
   if (wrap_ok) return wrap;
   for (int B : {4096, 2048, 1024, 512, 256, kMinChunk}) {
@@ -729,10 +730,12 @@ Tile1D batch_tile_for(const ridc_handle* h, const BatchTile& bt, int threads) {
 // the fewer rows there are to fill the chip with, the finer the cut.  Step times, us, of (threads,
 // rows) choices: 1.6e6 rows (256 instances, n 256..4096, order 4) (256, 1536) 18.9, (512, 1536) 21.0,
 // whole cycles in 256 threads 35.0; 4e5 rows (512, 768) 9.1, (512, 1536) 9.8, whole 30.6; 1e5 rows (512,
-// 512) 6.3, (512, 1536) 8.1, whole 29.4; 2.5e4 rows (512, 384) 5.2, (512, 1536) 7.6, whole 27.4.
+// 512) 6.3, (512, 1536) 8.1, whole 29.4; 2.5e4 rows (512, 384) 5.2, (512, 1536) 7.6, whole 27.4.  A chunk
+// of (512, 768) with a halo of 255 would work on 766 rows for 256, on a chip that is full: 5e5 rows
+// (128 instances, n 700..1400) 24.4 against 15.4 of whole cycles, so it has to own 512.
 BatchTile default_batch_tile(int64_t level_rows) {
   if (level_rows >= 800000) return BatchTile{256, 1536, false};
-  if (level_rows >= 200000) return BatchTile{512, 768, false};
+  if (level_rows >= 200000) return BatchTile{512, 768, false, 512};
   if (level_rows >= 50000) return BatchTile{512, 512, false};
   return BatchTile{512, 384, false};
 }

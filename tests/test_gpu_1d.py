@@ -710,3 +710,51 @@ def test_long_systems_of_high_order(env, n):
          f"{times[2]:.1f}")
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     assert times[0] <= 1.1 * min(times[1:])
+
+
+def _periodic_batch(ridc, torch, sizes, halo, order=4, nt=40):
+    """Handles and initial data of periodic systems whose PCR halo is `halo` rows or the longest that
+    their side has below it."""
+    solvers, x0s = [], []
+    dt = 1e-4
+    for n in sizes:
+        r = max(10.0 ** e for e in np.linspace(-2, 8, 200)
+                if 2 ** ridc.pcr_plan(10.0 ** e, n)[0] - 1 <= halo)
+        h = 2 * math.pi / n
+        prob = dict(dim=1, bc="periodic", n=n, length=2 * math.pi, fe="advect", a=0.01,
+                    nu=r * h * h / dt, T=dt * nt, nt=nt, order=order)
+        x = workloads.grid_points("periodic", n, 2 * math.pi)
+        solvers.append(ridc.Ridc(prob))
+        x0s.append(torch.tensor(np.sin(x) + 0.3 * np.cos(3 * x), dtype=torch.float64, device="cuda"))
+    return solvers, x0s
+
+
+def test_default_grouped_tiling_with_long_halos(env):
+    """128 instances of 700 to 1400 rows with halos of 255: the automatic tiling takes no longer than whole
+    cycles (chunks that recompute two rows of three took 1.6 times as long)."""
+    import time
+    torch, ridc = env
+    sizes = [int(v) for v in np.random.default_rng(0).integers(700, 1400, 128)]
+    nt = 40
+    solvers, x0s = _periodic_batch(ridc, torch, sizes, 255, nt=nt)
+    uTs = [torch.empty_like(a) for a in x0s]
+    times = []
+    try:
+        for tile in (None, (512, 0)):
+            ridc.tune_clear()
+            if tile:
+                ridc.set_batch_tile(*tile)
+            best = 1e30
+            for _ in range(6):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                ridc.integrate_batch(solvers, x0s, [nt] * len(sizes), uTs)
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t)
+            times.append(best * 1e6 / (nt + 6))
+    finally:
+        ridc.tune_clear()
+        for s in solvers:
+            s.close()
+    _say(f"case: 128 instances, halo 255: automatic {times[0]:.1f} us a step, whole cycles {times[1]:.1f}")
+    assert times[0] <= 1.1 * times[1]
