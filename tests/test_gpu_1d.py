@@ -758,3 +758,32 @@ def test_default_grouped_tiling_with_long_halos(env):
             s.close()
     _say(f"case: 128 instances, halo 255: automatic {times[0]:.1f} us a step, whole cycles {times[1]:.1f}")
     assert times[0] <= 1.1 * times[1]
+
+
+# the automatic tiling of a grouped launch goes by the rows it covers: from 8e5 (256, 1536), from 2e5 (512,
+# 768), from 5e4 (512, 512), below (512, 384); instances of odd sides, at the lower edge of each and at the
+# least there is, with halos that give chunks and halos that leave whole cycles
+@pytest.mark.parametrize("halo", [31, 127, 255, 511])
+@pytest.mark.parametrize("count,lo,hi", [(61, 3000, 4000), (40, 1100, 1700), (13, 900, 1200),
+                                         (9, 300, 700), (2, 257, 300)])
+def test_automatic_grouped_tilings_are_bitwise_solo(env, count, lo, hi, halo):
+    torch, ridc = env
+    rng = np.random.default_rng(count)
+    sizes = [int(v) for v in rng.integers(lo, hi, count)]
+    _say(f"case: {count} instances, {4 * sum(sizes)} rows of all levels, halo {halo}")
+    ridc.tune_clear()
+    solvers, x0s = _periodic_batch(ridc, torch, sizes, halo, nt=9)
+    want = [s.integrate(a, 9).clone() for s, a in zip(solvers, x0s)]
+    try:
+        for tile in (None, (256, 1536), (512, 768), (512, 512), (512, 384)):
+            if tile:
+                ridc.set_batch_tile(*tile)
+            uTs = [torch.empty_like(a) for a in x0s]
+            ridc.integrate_batch(solvers, x0s, [9] * count, uTs)
+            torch.cuda.synchronize()
+            for u, w in zip(uTs, want):
+                assert torch.equal(u, w), tile
+    finally:
+        ridc.tune_clear()
+        for s in solvers:
+            s.close()

@@ -395,3 +395,34 @@ def test_batch_mixing_1d_and_2d(env):
         s.sync()
         np.testing.assert_array_equal(uT.cpu().numpy(), ref)
         s.close()
+
+
+# every block tile and its two forms (two slices in flight, or four where the slices are a multiple of
+# four): alone 32-tiles; in a group of `c64` handles 64-tiles, of `c128` 128-tiles (order 1, so a level a
+# handle).  Sides that fold with a multiple of four slices (256, 512), that fold without (192: three
+# slices of split BF16, six of FP64; 384), and that do not fold (352)
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("n,c64,c128", [(192, 30, 32), (256, 17, 32), (352, 9, 15), (384, 8, 15),
+                                        (512, 5, 8)])
+def test_64_tiles_are_bitwise_equal(env, n, c64, c128, prec):
+    torch, ridc = env
+    t64, t128 = ((n + 63) // 64) ** 2, ((n + 127) // 128) ** 2
+    assert c64 * t64 >= 257 and c64 * t128 < 128 <= c128 * t128
+    prob, u0 = workloads.config_reacdiff_2d(n=n, nt=3, order=1, T=6e-3, nu=1e-3)
+    _say(f"case: 2D {prec} n={n}, {c64 * t64} blocks of 64 and {c128 * t128} of 128")
+    ref = oracle2d(prob, u0)
+    top, lvs = run2d(env, prob, u0, prec=prec)
+    err, emax = errs(lvs[0], ref[0])
+    assert err <= tol_of(prec, 0) and emax <= tol_of(prec, 0), (err, emax)
+    x0 = torch.tensor(u0.reshape(-1), dtype=torch.float64, device="cuda")
+    # split BF16 takes 64-tiles also where they are 256 blocks exactly
+    counts = [c64, c128] + ([256 // t64] if prec == "bf16x3" and 256 % t64 == 0 else [])
+    for count in counts:
+        solvers = [ridc.Ridc(prob, prec=prec) for _ in range(count)]
+        uTs = [torch.empty_like(x0) for _ in range(count)]
+        ridc.integrate_batch(solvers, [x0] * count, [prob["nt"]] * count, uTs)
+        torch.cuda.synchronize()
+        for u in uTs:
+            np.testing.assert_array_equal(u.cpu().numpy().reshape(-1), np.asarray(top).reshape(-1))
+        for s in solvers:
+            s.close()
