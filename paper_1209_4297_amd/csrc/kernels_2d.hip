@@ -1594,11 +1594,10 @@ void launch_pass(const Pass2D* d, const Lvl2D* lv, int count, int64_t n, int64_t
   } else {
     // Whole steps, us, with two slices / four in flight: 256^2 FP64 order 4 26.1 / 24.0, 512^2 order 2 FP64
     // 44.5 / 41.4, FP32 57.1 / 55.5 and split BF16 49.6 / 46.1, 768^2 order 2 FP32 116 / 104; split BF16
-    // in 64-tiles with one block a CU (512^2 order 4) 60.4 / 56.6, with more (768^2 order 2) 78.5 / 80.8.
+    // in 64-tiles 1024^2 order 1 (256 blocks) 80.2 / 67.0, 512^2 order 4 (256) 61.0 / 55.7 and order 6
+    // (384) 79.9 / 79.3, 768^2 order 2 (288) 78.7 / 76.4 and order 3 (432) 86.6 / 86.0.
     // Slices that are not a multiple of four need a test at every load (1-2 % slower at 64^2..384^2).
-    const int64_t blocks = ((n + bt - 1) / bt) * ((n + bt - 1) / bt) * count;
-    const bool deep = fold && n / 2 / Tr<PREC>::BK % 4 == 0 &&
-                      !(PREC == PREC_BF16 && bt == 64 && blocks > 256);
+    const bool deep = fold && n / 2 / Tr<PREC>::BK % 4 == 0;
     if (bt == 64) {
       constexpr size_t half = pass_lds_bytes<PREC, 1, 64>(1);
       if (deep) go(k_pass2d<PREC, OUT, 1, 1, 64, 32, true>, 64, pass_threads<64, 32>(), half);

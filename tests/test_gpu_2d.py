@@ -415,7 +415,7 @@ def test_64_tiles_are_bitwise_equal(env, n, c64, c128, prec):
     err, emax = errs(lvs[0], ref[0])
     assert err <= tol_of(prec, 0) and emax <= tol_of(prec, 0), (err, emax)
     x0 = torch.tensor(u0.reshape(-1), dtype=torch.float64, device="cuda")
-    # split BF16 takes 64-tiles also where they are 256 blocks exactly
+    # split BF16 takes 64-tiles from 256 blocks on
     counts = [c64, c128] + ([256 // t64] if prec == "bf16x3" and 256 % t64 == 0 else [])
     for count in counts:
         solvers = [ridc.Ridc(prob, prec=prec) for _ in range(count)]
