@@ -1950,44 +1950,83 @@ int arena2d_reserve(size_t nlv, size_t nps, hipStream_t stream) {
 }
 
 // Side streams that run groups beside the caller's stream: three of the calling thread's own for the
-// device it used last, given back when the thread ends.  The caller's stream waits for them before a
-// call returns, so to the caller everything stays in its stream's order.
+// device it used last.  The caller's stream waits for them before a call returns, so to the caller
+// everything stays in its stream's order.  A thread that ends (or goes to another device) may leave
+// work on them that has not run yet, so they are not destroyed then but kept for the next thread, whose
+// work queues up behind; of more than kSpare idle sets one is drained and given back.
 struct SideStreams {
   static constexpr int N = 3;
   int device = -1;
   hipStream_t s[N] = {};
   hipEvent_t fork = nullptr, join[N] = {};
-  void release() {
+  void destroy() {
     for (auto& x : s)
-      if (x) (void)hipStreamDestroy(x);
+      if (x) {
+        (void)hipStreamSynchronize(x);
+        (void)hipStreamDestroy(x);
+      }
     for (auto& x : join)
       if (x) (void)hipEventDestroy(x);
     if (fork) (void)hipEventDestroy(fork);
     *this = SideStreams{};
   }
-  // the streams of the current device; false (and none) when they cannot be had
-  bool reserve() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    if (device == dev) return true;
-    release();
+  bool create(int dev) {
     bool ok = hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; i < N && ok; ++i)
       ok = hipStreamCreateWithFlags(&s[i], hipStreamNonBlocking) == hipSuccess &&
            hipEventCreateWithFlags(&join[i], hipEventDisableTiming) == hipSuccess;
     if (!ok) {
       (void)hipGetLastError();
-      release();
+      destroy();
       return false;
     }
     device = dev;
     return true;
   }
 };
+struct SpareStreams {
+  static constexpr size_t kSpare = 8;
+  std::mutex mu;
+  std::vector<SideStreams> sets;
+  bool take(int dev, SideStreams* out) {
+    std::lock_guard<std::mutex> lk(mu);
+    for (size_t i = 0; i < sets.size(); ++i)
+      if (sets[i].device == dev) {
+        *out = sets[i];
+        sets.erase(sets.begin() + i);
+        return true;
+      }
+    return false;
+  }
+  void give(SideStreams* in) {
+    if (in->device < 0) return;
+    SideStreams old;
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      if (sets.size() >= kSpare) {
+        old = sets.front();
+        sets.erase(sets.begin());
+      }
+      sets.push_back(*in);
+    }
+    *in = SideStreams{};
+    old.destroy();
+  }
+};
+SpareStreams& spare_streams() {
+  static auto* p = new SpareStreams();   // outlives the threads that end at exit
+  return *p;
+}
 struct SideStreamsOwner {
   SideStreams v;
-  ~SideStreamsOwner() {
-    if (v.device >= 0) v.release();
+  ~SideStreamsOwner() { spare_streams().give(&v); }
+  // the streams of the current device; false when they cannot be had
+  bool reserve() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    if (v.device == dev) return true;
+    spare_streams().give(&v);
+    return spare_streams().take(dev, &v) || v.create(dev);
   }
 };
 thread_local SideStreamsOwner g_side;
@@ -2070,7 +2109,7 @@ int plan2d_advance(Plan2D* const* pls, int count, const int64_t* sigma_before, i
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool known = hipStreamIsCapturing(stream, &cap) == hipSuccess;
     if (!known) (void)hipGetLastError();
-    if (known && cap == hipStreamCaptureStatusNone && g_side.v.reserve()) {
+    if (known && cap == hipStreamCaptureStatusNone && g_side.reserve()) {
       nl = (int)std::min<size_t>(gs.size(), 1 + SideStreams::N);
       RIDC_HIP_TRY(hipEventRecord(g_side.v.fork, stream));
       for (int i = 1; i < nl; ++i) {

@@ -426,3 +426,41 @@ def test_64_tiles_are_bitwise_equal(env, n, c64, c128, prec):
             np.testing.assert_array_equal(u.cpu().numpy().reshape(-1), np.asarray(top).reshape(-1))
         for s in solvers:
             s.close()
+
+
+def test_batches_of_threads_that_end(env):
+    """A batch of several groups forks to streams of the calling thread's.  Threads that end right after
+    the call, with the work still queued, leave it whole, and their streams pass to later threads; more
+    threads than idle sets are kept (8), at once and one after the other, on streams of their own."""
+    import threading
+    torch, ridc = env
+    probs = [workloads.config_reacdiff_2d(n=n, nt=60, order=2, T=0.12, nu=1e-3) for n in (64, 96, 160)]
+    want = []
+    for p, u in probs:
+        s = ridc.Ridc(p)
+        want.append(s.integrate(torch.tensor(u.reshape(-1), device="cuda"), 60).clone())
+        s.close()
+    torch.cuda.synchronize()
+    jobs = []
+
+    def work():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            solvers = [ridc.Ridc(p) for p, _ in probs]
+            x = [torch.tensor(u.reshape(-1), device="cuda") for _, u in probs]
+            out = [torch.empty_like(a) for a in x]
+            ridc.integrate_batch(solvers, x, [60] * len(x), out)
+            jobs.append((solvers, x, out))            # kept until the work has run
+
+    for together in (12, 1, 1, 1):
+        threads = [threading.Thread(target=work) for _ in range(together)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    torch.cuda.synchronize()
+    assert len(jobs) == 15
+    for solvers, _, out in jobs:
+        for o, w in zip(out, want):
+            assert torch.equal(o, w)
+        for s in solvers:
+            s.close()
