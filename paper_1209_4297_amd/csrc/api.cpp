@@ -627,6 +627,9 @@ int check_handles(ridc_handle* const* hs, int32_t count) {
 
 int apply_tile_1d(ridc_handle* h, const Tile1D& t) {
   if (!tile_fits(&h->p, h->pcr, t)) return fail(RIDC_E_INVAL, "tile does not fit this system");
+  const size_t nchunks = t.wrap ? 1 : (size_t)((h->p.n + t.B - 1) / t.B);
+  if (!t.fused && nchunks * h->P > h->blocks_cap)
+    return fail(RIDC_E_INVAL, "tile finer than the minimum chunk");
   h->small = false;                    // a tiling was asked for
   if (t.fused) {
     const FusedPlan fp = plan_fused(&h->p, t.fused);
@@ -642,8 +645,6 @@ int apply_tile_1d(ridc_handle* h, const Tile1D& t) {
     return RIDC_OK;
   }
   h->fused = false;
-  const size_t nchunks = t.wrap ? 1 : (size_t)((h->p.n + t.B - 1) / t.B);
-  if (nchunks * h->P > h->blocks_cap) return fail(RIDC_E_INVAL, "tile finer than the minimum chunk");
   build_items_1d(h, t);
   h->solo.nt = h->nt < 0 ? 0 : h->nt;
   RIDC_HIP_TRY(hipMemcpyAsync(h->d_blocks, h->blocks.data(), sizeof(Blk1D) * h->blocks.size(),

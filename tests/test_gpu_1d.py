@@ -787,3 +787,30 @@ def test_automatic_grouped_tilings_are_bitwise_solo(env, count, lo, hi, halo):
         ridc.tune_clear()
         for s in solvers:
             s.close()
+
+
+def test_a_refused_tile_changes_nothing(env):
+    """A tiling that is refused leaves the handle on the kernel it had: a small system, untouched or set
+    to the whole range, still runs its steps in one workgroup."""
+    torch, ridc = env
+    ridc.tune_clear()
+    x = workloads.grid_points("periodic", 256, 2 * math.pi)
+    x0 = torch.tensor(np.sin(x), dtype=torch.float64, device="cuda")
+    prob = dict(dim=1, bc="periodic", n=256, length=2 * math.pi, fe="advect", a=0.01, nu=1e-4, T=0.02,
+                nt=400, order=2)
+    times = []
+    for tiles in (((256, 0, 0),), (), ((512, 0, 2),)):
+        s = ridc.Ridc(prob)
+        for t in tiles:
+            s.set_tile(*t)
+        if len(times):
+            for bad in ((256, 16, 0), (96, 0, 0), (256, 512, 0)):     # too fine, no such count, too long
+                with pytest.raises(ridc.RidcError) as e:
+                    s.set_tile(*bad)
+                assert e.value.code == ridc.RIDC_E_INVAL
+        s.begin(x0, 400)
+        ridc.advance([s], 20)
+        times.append(s.kernel_time(100)[0])
+        s.close()
+    _say(f"case: launches per step {times[0]:.2f} us, after refused tiles {times[1]:.2f} and {times[2]:.2f}")
+    assert max(times[1:]) < 0.8 * times[0]
