@@ -1472,6 +1472,7 @@ int ridc_create_ext(const ridc_problem* p, const ridc_ext* e, void* hip_stream,
     L.ce = explicit_coeff(p->fe_kind, p->a, hh);
     L.nu_h2 = p->nu / (hh * hh);
     L.kappa = e->fs_kind == RIDC_FS_DIFFUSION ? 0.0 : e->kappa;
+    for (int i = 0; i < kMaxStages; ++i) L.c[i] = i < pr.s ? pr.c[i] : 0.0;
     for (int i = 0; i < kMaxStages; ++i)
       for (int l = 0; l < kMaxStages; ++l) {
         L.AS[i][l] = i < pr.s && l < pr.s ? pr.AS[i][l] : 0.0;

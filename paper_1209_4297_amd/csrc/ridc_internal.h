@@ -211,6 +211,7 @@ struct ImexLvl {
   double dt, ce, nu_h2, kappa;
   double AS[kMaxStages][kMaxStages];
   double AN[kMaxStages][kMaxStages];
+  double c[kMaxStages];   // stage i at t_n + c_i dt
 };
 
 // Rows per thread (2, 4, 8 or 16) and threads per workgroup (a multiple of 64, at most 512)
