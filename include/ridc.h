@@ -258,8 +258,9 @@ int ridc_autotune(ridc_handle* h, int32_t* threads_out, int32_t* rows_out, int32
 /* 2D handles: set the transform-pass shape bits `flags` (1: 64-column waves, FP32/FP64 passes
  * with n/2 a multiple of 64 or no fold; 2: 32-wide k-slices, split-BF16 pass; 4, n a multiple
  * of 256: row-major intermediates folded while staging, which is what every shape does; 0: none
- * of these).  Bits 1 and 2 shape the passes large enough for 128 x 128 tiles.  A handle with no recorded shape starts at 0, split-BF16 handles at 2 where 2 is
- * allowed.  rows must be 0 and threads is ignored; results do not depend on the shape.
+ * of these).  Bits 1 and 2 shape the passes large enough for 128 x 128 tiles.  A handle with no
+ * recorded shape starts at 0, split-BF16 handles at 2 where 2 is allowed.  rows must be 0 and
+ * threads is ignored; results do not depend on the shape.
  * 1D: force a tiling: threads in {64,128,256,512,1024}; rows = 0 for the whole cycle in one
  * workgroup, else chunks of `rows` rows (allowed when the PCR coupling vanishes within a halo
  * shorter than the system); flags bit 0 = write level values with nontemporal stores; flags
@@ -313,7 +314,8 @@ int ridc_tune_clear(void);
  *    launch running `reps` steps; the handle runs ahead and is left unarmed (call ridc_begin again);
  *  - 2D: `reps` launches of the first transform pass of that step over all levels (after its
  *    right-hand side once).  These launches rewrite only per-step intermediates (the right-hand
- *    side and transform buffers, which the step recomputes); the level rings and the handle's position are unchanged.
+ *    side and transform buffers, which the step recomputes); the level rings and the handle's
+ *    position are unchanged.
  * *work_per_launch (nullable) receives the algorithmic HBM bytes (1D, per step) or flops (2D,
  * per pass).  Errors: RIDC_E_STATE if the next step is not a full one or too few remain.     */
 int ridc_kernel_time(ridc_handle* h, int32_t reps, double* us_per_launch,

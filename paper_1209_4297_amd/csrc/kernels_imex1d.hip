@@ -43,8 +43,8 @@
 // Bound: latency and FP64 issue inside one compute unit per level (a solve is some 720 FP64 and 700
 // other instructions a lane with 16 rows; the level's vectors cross its L2 port once a stage).
 // Reducing all 2 T block rows through LDS, one barrier per stage, with every vector in grid order
-// and re-read per stage, took 178 us per step of ARK3 + FBE and 184 us of RIDC4 with the cubic
-// reaction (9 Newton iterates) at n = 8192; this form takes 54 and 70.
+// and re-read per stage, took 180 us per step of ARK3 + FBE and 181 us of RIDC4 with the cubic
+// reaction (9 Newton iterates) at n = 8192; this form takes 63 and 71.
 #include "ridc_internal.h"
 
 namespace ridc {
@@ -542,7 +542,7 @@ __device__ __forceinline__ void with_halo(const Ctx& c, const double (&x)[M], co
 // away beside 2 r; cond: the condition number), the same way in every row and step: one solve alone
 // left 1e-10 of y at r = 6.7e5 (two: 5e-14) and 4e-16 at r = 25 (two: 1.6e-16).  Correctors,
 // whose guess is the level below, take one; predictors two while r times the guess's error shows
-// (ARK3 + FBE at n = 8192, r = 34: one solve 59 us a step, this rule 64).
+// (ARK3 + FBE at n = 8192, r = 34: one solve 59 us a step, this rule 63).
 // Otherwise Newton's method with the stopping rule: the largest update is below 1e-15 max(1,
 // max|y|), or below 1e-11 max(1, max|y|) and above half the previous one (rounding noise); after
 // maxit iterates without stopping, y becomes NaN.  rhs_at(i): the right-hand side of local row i.
@@ -754,7 +754,7 @@ __device__ __forceinline__ void imex_step(const ImexLvl& L, int64_t sigma, bool 
       for (int x = 0; x < M; ++x) rhs[x] = rhs[x] + dt * q[x];
     } else if (i > 1 && (PER || c.fs == RIDC_FS_DIFFUSION)) {
       // the guess follows the line through y_n and the stage before: of the third-order pair's four
-      // solves only the first is off by O(dt), which saves most of the second solves (68 -> 64 us a
+      // solves only the first is off by O(dt), which saves most of the second solves (68 -> 65 us a
       // step, n = 8192).  A stiff reaction's stages start from y_n, on the branch the value is on
       const double f = L.c[i] / L.c[i - 1];
 #pragma unroll
@@ -897,8 +897,8 @@ hipError_t launch_m(int M, const ImexLvl* items, int count, int threads, int64_t
 void imex_shape(int64_t n, int* M, int* threads) {
   // The fewest rows per thread that keep the workgroup within one wave per SIMD (256 threads), 8
   // rows at most up to n = 4096.  Steps of RIDC4 with the cubic reaction, us, at 2 / 4 / 8 / 16 rows:
-  // n = 500 22.0 / 23.1 / 27.0 / 54.0, 999 35.9 / 25.5 / 29.0 / 54.0, 2000 - / 41.1 / 32.3 / 56.1, 4000
-  // - / - / 53.5 / 62.2 (two waves on a SIMD take turns; a longer block is a longer chain).
+  // n = 500 21.5 / 23.0 / 27.2 / 42.8, 999 32.0 / 24.0 / 28.7 / 42.9, 2000 - / 36.5 / 29.9 / 44.9, 4000
+  // - / - / 46.0 / 47.9 (two waves on a SIMD take turns; a longer block is a longer chain).
   int m = 2;
   while (m < 8 && (n + m - 1) / m > 256) m *= 2;
   while (m < kImexMaxRows && (n + m - 1) / m > kImexMaxThreads) m *= 2;
